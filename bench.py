@@ -46,8 +46,8 @@ def kernel_source_hash(algo: str) -> str:
     """Hash of the sources that decide what the kernel of `algo` ("data", "speculative",
     "path" or "forest") does and how it is launched."""
     h = hashlib.sha256()
-    for f in KERNEL_SOURCES[algo] + ("kernels.hpp", "device_common.hpp", "dtree.hip",
-                                     "encode.cpp", "encode.hpp"):
+    for f in KERNEL_SOURCES[algo] + ("kernels.hpp", "device_common.hpp", "row_tile.hpp",
+                                     "tiles.hpp", "dtree.hip", "encode.cpp", "encode.hpp"):
         with open(os.path.join(ROOT, "paper_1111_1373_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]

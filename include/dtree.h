@@ -223,11 +223,13 @@ typedef struct {
     int32_t lds_bytes;             /* dynamic LDS per workgroup                          */
     int32_t result_buffer_tiles;   /* tiles of results each wavefront buffers           */
     int32_t tables_in_lds;         /* 1: tree tables staged in the LDS, 0: read in place */
-    int32_t load_mode;             /* 0: scalar loads, 1: 16-byte loads, 2: 16-byte loads
-                                      of rows exactly one LDS row stride wide            */
-    int32_t tile_rows;             /* records per wavefront tile: 64, or 32 for the
-                                      speculative walk of 64-slot windows on rows of at
-                                      least 32 bytes                                     */
+    int32_t load_mode;             /* 0: dense rows of no multiple of 16 bytes, a tile
+                                      copied as it lies; 1: other rows, row by row;
+                                      2: dense rows of a power of two of words; 3: rows
+                                      that start between words                           */
+    int32_t tile_rows;             /* records per wavefront tile: 64, 32 or 16 of wide
+                                      rows, 32 for the speculative walk of 32- and 64-slot
+                                      windows                                            */
 } dt_launch_info;
 
 /* Fill *info with the launch shape of dt_classify_typed(tree, d_x, x_type, n, ld, ...,

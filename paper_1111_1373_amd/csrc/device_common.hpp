@@ -7,7 +7,9 @@
 // column, so the top levels of a tree (where every lane reads the same feature) are
 // conflict-free, and the staging stores land on distinct banks.  Staging moves whole
 // words and does not depend on the element type; a tree step widens the element it reads
-// to fp32 (exactly) and compares it with the fp32 threshold.
+// to fp32 (exactly) and compares it with the fp32 threshold.  That layout needs rows of a
+// power of two of words; single-tree kernels keep every other row width, stride and
+// alignment in row tiles (RowTile below).
 //
 // Window tables (built on the host, see encode.hpp): for window w, slot p in [1, 2^D)
 // holds the (threshold, feature) of heap node p (children 2p, 2p+1; slot 0 is padding);
@@ -21,21 +23,10 @@
 #include <utility>
 
 #include "kernels.hpp"
+#include "row_tile.hpp"
 
 namespace dtree {
 namespace dev {
-
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-struct alignas(8) Slot {
-    float t;
-    int32_t f;   // byte offset of the feature in an fp32 row: 4 * feature index
-};
-
-// The two children 2p, 2p+1 of a heap slot: one aligned 16-byte LDS read.
-struct alignas(16) Slot2 {
-    Slot l, r;
-};
 
 // Exit codes packed into the window's bottom slots (forest data walk): the 32-bit word of
 // a slot p in [S/2, S) holds the feature's byte offset in bits 0-9 and the exit codes of
@@ -44,101 +35,6 @@ struct alignas(16) Slot2 {
 // last slot of the window, with no read of an exit table.
 struct PackedExits {};
 constexpr int kPackedFeatureMask = 0x3FF;
-
-// Word swizzle of row r for rows of RSW 4-byte words.
-template <int RSW>
-__device__ __forceinline__ int swz(int r) {
-    if constexpr (RSW >= 64) {
-        return r;                                  // r < 64 <= RSW
-    } else {
-        constexpr int sh = __builtin_ctz(64 / RSW);
-        return (r >> sh) & (RSW - 1);
-    }
-}
-
-// Record element types.  widen() is exact for every value (NaN stays NaN, fp16 and bf16
-// subnormals become the same fp32 value), so a decision on a widened element is the
-// decision on the value the element stores.
-template <int XT> struct Elem;
-template <> struct Elem<kXF32> {
-    using T = float;
-    static __device__ __forceinline__ float widen(float v) { return v; }
-};
-template <> struct Elem<kXF16> {
-    using T = uint16_t;   // IEEE binary16 bits
-    static __device__ __forceinline__ float widen(uint16_t b) {
-        return float(__builtin_bit_cast(_Float16, b));
-    }
-};
-template <> struct Elem<kXBF16> {
-    using T = uint16_t;   // bfloat16 bits: the high half of an fp32
-    static __device__ __forceinline__ float widen(uint16_t b) {
-        return __uint_as_float(uint32_t(b) << 16);
-    }
-};
-template <> struct Elem<kXU8> {
-    using T = uint8_t;
-    static __device__ __forceinline__ float widen(uint8_t b) { return float(b); }
-};
-
-// Window-table slots as the kernels for record type XT read them.
-//   fp32 records: Slot {float t; int32 f} (8 bytes), decision !(x < t).
-//   Narrow records: one 32-bit word, the feature index in the high half and in the low
-//   half a key on the record type's grid (built on the host, see encode.hpp): for fp16 and
-//   bf16 the threshold rounded up to the nearest value of the type, for uint8 its integer
-//   ceiling clamped to 0..256.  No value of the type lies strictly between t and the key,
-//   so !(x < key) on the stored element is the decision !(x < t) on its widened value.
-template <int XT> struct Node;
-template <> struct Node<kXF32> {
-    using S = Slot;
-    using Pair = Slot2;
-    static __device__ __forceinline__ int feature(const Slot &s) { return s.f >> 2; }
-    static __device__ __forceinline__ bool right(float x, const Slot &s) { return !(x < s.t); }
-};
-template <> struct Node<kXF16> {
-    using S = uint32_t;
-    struct alignas(8) Pair { uint32_t l, r; };
-    static __device__ __forceinline__ int feature(uint32_t s) { return int(s >> 16); }
-    static __device__ __forceinline__ bool right(uint16_t x, uint32_t s) {
-        return !(Elem<kXF16>::widen(x) < Elem<kXF16>::widen(uint16_t(s)));
-    }
-};
-template <> struct Node<kXBF16> {
-    using S = uint32_t;
-    struct alignas(8) Pair { uint32_t l, r; };
-    static __device__ __forceinline__ int feature(uint32_t s) { return int(s >> 16); }
-    static __device__ __forceinline__ bool right(uint16_t x, uint32_t s) {
-        return !(Elem<kXBF16>::widen(x) < Elem<kXBF16>::widen(uint16_t(s)));
-    }
-};
-template <> struct Node<kXU8> {
-    using S = uint32_t;
-    struct alignas(8) Pair { uint32_t l, r; };
-    static __device__ __forceinline__ int feature(uint32_t s) { return int(s >> 16); }
-    static __device__ __forceinline__ bool right(uint8_t x, uint32_t s) {
-        return uint32_t(x) >= (s & 0xFFFFu);
-    }
-};
-
-// Feature of slot `s` in a record row of the tile: element (feature ^ sw) * STRIDE of `row`.
-// fp32 slots carry the feature as a byte offset, so the address is one xor-add.
-template <int XT, int STRIDE>
-__device__ __forceinline__ typename Elem<XT>::T feature_at(const typename Elem<XT>::T *row,
-                                                           const typename Node<XT>::S &s, int sw) {
-    if constexpr (XT == kXF32)
-        return *reinterpret_cast<const float *>(reinterpret_cast<const char *>(row) +
-                                                (s.f ^ (sw << 2)) * STRIDE);
-    else
-        return row[(Node<XT>::feature(s) ^ sw) * STRIDE];
-}
-
-// Element-level position swizzle for rows of RS elements of type XT: the word swizzle,
-// scaled to elements (the position of an element within its word is unchanged).
-template <int XT, int RS>
-__device__ __forceinline__ int swz_el(int r) {
-    constexpr int kPerWord = 4 / int(sizeof(typename Elem<XT>::T));
-    return swz<RS / kPerWord>(r) * kPerWord;
-}
 
 // Ordering of LDS accesses among the lanes of one wavefront.  A wavefront's LDS
 // instructions execute in order; the fences keep the compiler from moving accesses
@@ -155,13 +51,6 @@ __device__ __forceinline__ uint32_t div_f(uint32_t e, const Rows &in) {
 
 __device__ __forceinline__ uint32_t div_w(uint32_t e, const Rows &in) {
     return in.n_words == 1 ? e : __umulhi(e, in.magic_w);
-}
-
-// Records of tile `tile` (tiles of TR records) that exist in the input.
-template <int TR = kTileRows>
-__device__ __forceinline__ int valid_rows(const Rows &in, int64_t tile) {
-    const int64_t left = in.n - tile * TR;
-    return left < TR ? int(left) : TR;
 }
 
 // Tile layouts.  Row-major (the default): row r at word r*RSW, word w at w ^ swz(r).
@@ -395,6 +284,46 @@ __device__ __forceinline__ void stage_now(const Rows &in, float *tile, int64_t t
     }
 }
 
+// ---- record tiles of the single-tree kernels ---------------------------------------------
+// A tile class holds the next tile's loads in registers (load), writes them into the LDS
+// (store), stages any tile at once, the input's last ones included (stage), and reads
+// feature values (row and swizzle of a record for the data walk, at() for the others).
+
+// Dense rows of a power of two of 4-byte words (4 to 64), 16-byte aligned base.
+template <int XT, int RS, int LAYOUT, int TRv>
+struct ExactTile {
+    using T = typename Elem<XT>::T;
+    static constexpr int TR = TRv;
+    static constexpr bool kPrefetch = true;
+    static constexpr int kRegs = TR * row_words<XT, RS>() / 64;   // prefetch registers per lane
+    VecTile<row_words<XT, RS>(), true, TR> buf;
+
+    static __device__ __forceinline__ int64_t prefetch_end(const Rows &in) { return in.n / TR; }
+    __device__ __forceinline__ void load(const Rows &in, int64_t t, int lane) {
+        buf.load_full(in, t, lane);
+    }
+    __device__ __forceinline__ void store(const Rows &in, float *tile, int lane) const {
+        buf.template store<LAYOUT>(in, tile, lane);
+    }
+    static __device__ __forceinline__ void stage(const Rows &in, float *tile, int64_t t, int lane) {
+        VecTile<row_words<XT, RS>(), true, TR> b;
+        b.load_tail(in, t, lane);
+        b.template store<LAYOUT>(in, tile, lane);
+    }
+    static __device__ __forceinline__ const T *row(const Rows &, const float *tile, int r) {
+        return reinterpret_cast<const T *>(tile) + r * RS;
+    }
+    static __device__ __forceinline__ int swizzle(int r) {
+        return LAYOUT == kRowFlat ? 0 : swz_el<XT, RS>(r);
+    }
+    // Feature of slot `s` in record r + g (g a constant of the unrolled caller).
+    static __device__ __forceinline__ T at(const Rows &, const float *tile, int r, int g,
+                                           const typename Node<XT>::S &s) {
+        return feature_at<XT, 1>(reinterpret_cast<const T *>(tile) + (r + g) * RS, s,
+                                 swizzle(r + g));
+    }
+};
+
 // v_writelane_b32: `value` (wavefront-uniform) written into lane `lane` of `old`.  The
 // compiler's intrinsic has no clang builtin here, so it is declared by its LLVM name.
 extern "C" __device__ int dt_llvm_writelane(int value, int lane, int old)
@@ -556,33 +485,36 @@ __device__ __forceinline__ void walk_data_k(const char *const (&base)[K],
 // wavefront instruction evaluates 64/S records' windows.  One ballot gathers the 64
 // outcomes; record r's segment is handed to lane r, which walks its bits from the window
 // root to the exit.
-template <int XT, int RS, int D, int TR = kTileRows>
+template <int XT, int D, class Tile>
 struct Spec {
     using T = typename Elem<XT>::T;
     using N = Node<XT>;
     using Slot = typename N::S;
     static constexpr int S = 1 << D;
-    // Tiles of TR records: 64, or 32 for 32- and 64-lane groups.  A round evaluates one
-    // record per group, so kRounds = TR S / 64 rounds cover the tile: group s evaluates
-    // records s kRounds .. s kRounds + kRounds - 1, and record s kRounds + g lives in lane
-    // s S + g (its group's lane g).  Only 32-record tiles of 32-lane groups leave lanes
-    // without a record (g >= 16); in_record_order() moves the results to lanes 0 .. TR - 1.
-    static_assert(TR == kTileRows || (S >= 32 && TR == 32), "32-record tiles need 32- or 64-lane groups");
-    static constexpr int kRounds = TR * S / kTileRows;
+    // Tiles of TR records: 64, or 32 for 32- and 64-lane groups, or 32 or 16 for wide rows.
+    // A round evaluates one record per group, so kRounds = TR S / 64 rounds cover the tile:
+    // group s evaluates records s kRounds .. s kRounds + kRounds - 1, and record s kRounds +
+    // g lives in lane s S + g (its group's lane g).  Tiles of fewer than 64 records leave
+    // lanes without a record; record() names each lane's.
+    static constexpr int TR = Tile::TR;
+    static constexpr int kRounds = TR * S >= kTileRows ? TR * S / kTileRows : 1;
     using Bits = typename std::conditional<(S > 32), uint64_t, uint32_t>::type;
     int j;          // slot evaluated by this lane (slot 0 is padding)
     int seg_shift;  // first lane of this lane's segment
     int rec_base;   // first record of this lane's segment (segment index * kRounds)
-
-    // Record tile layout the rounds read.  64- and 32-lane groups read one or two record
-    // rows per round: flat rows, so that a round's row is its group's first row plus a
-    // constant (an instruction offset; a per-row swizzle would be a per-round register).
-    // Narrower groups read 64/S rows at once, and the swizzle keeps rows reading the same
-    // feature on distinct banks.
-    static constexpr int kLayout = S >= 32 ? kRowFlat : kRowMajor;
+    bool has;       // this lane holds a record's result
 
     __device__ __forceinline__ explicit Spec(int lane)
-        : j(lane & (S - 1)), seg_shift(lane & ~(S - 1)), rec_base((lane >> D) * kRounds) {}
+        : j(lane & (S - 1)), seg_shift(lane & ~(S - 1)), rec_base((lane >> D) * kRounds), has(true) {
+        if constexpr (TR < kTileRows) {
+            has = j < kRounds && rec_base + j < TR;
+            // 2-lane groups of a 16-record tile: the groups past the tile repeat its last record
+            if constexpr (TR * S < kTileRows) rec_base = rec_base < TR ? rec_base : TR - 1;
+        }
+    }
+
+    // Record of the tile whose result this lane holds, -1 for none.
+    __device__ __forceinline__ int record() const { return has ? rec_base + j : -1; }
 
     // Value wb of lane seg_shift + G (record seg_shift + G's window byte offset) in every
     // lane of the segment, with the round index G a compile-time constant:
@@ -636,7 +568,7 @@ struct Spec {
     template <int G0, int... G>
     __device__ __forceinline__ void eval_batch(std::integer_sequence<int, G...>, Bits &bits,
                                                const Slot *slots, bool first, const Slot &root,
-                                               int wb, const T *tile) const {
+                                               int wb, const Rows &in, const float *tile) const {
         constexpr int K = sizeof...(G);
         Slot p[K];
         // wb: byte offset of the record's window, window id * 2^D * sizeof(Slot); added to
@@ -646,9 +578,7 @@ struct Spec {
                              reinterpret_cast<const char *>(slots + j) + window_of<G0 + G>(wb))),
          ...);
         T xv[K];
-        ((xv[G] = feature_at<XT, 1>(tile + (rec_base + G0 + G) * RS, p[G],
-                                    kLayout == kRowFlat ? 0 : swz_el<XT, RS>(rec_base + G0 + G))),
-         ...);
+        ((xv[G] = Tile::at(in, tile, rec_base, G0 + G, p[G])), ...);
         (take<G0 + G>(bits, __ballot(N::right(xv[G], p[G]))), ...);
         __builtin_amdgcn_sched_barrier(0);
     }
@@ -657,27 +587,26 @@ struct Spec {
     __device__ __forceinline__ void eval_batches(std::integer_sequence<int, Q...>,
                                                  std::integral_constant<int, K>, Bits &bits,
                                                  const Slot *slots, bool first, const Slot &root,
-                                                 int wb, const T *tile) const {
+                                                 int wb, const Rows &in, const float *tile) const {
         (eval_batch<Q * K>(std::make_integer_sequence<int, K>(), bits, slots, first, root, wb,
-                           tile),
+                           in, tile),
          ...);
     }
 
     // Rounds per batch: 8, or 4 where the tile's prefetch buffer takes 64 registers (16 KiB
     // record tiles), which leaves too few for eight rounds' loads; never more than a level's
     // rounds.
-    static constexpr int kPrefetchRegs = TR * RS * int(sizeof(T)) / 256;
-    static constexpr int kMaxBatch = kPrefetchRegs >= 64 ? 4 : 8;
+    static constexpr int kMaxBatch = Tile::kRegs >= 64 ? 4 : 8;
     static constexpr int kBatch = kRounds < kMaxBatch ? kRounds : kMaxBatch;
     static_assert(kBatch >= 1 && kRounds % kBatch == 0, "batches must cover a level's rounds");
 
     // One window level for the tile's records.
     __device__ __forceinline__ Bits eval(const Slot *slots, bool first, const Slot &root, int w,
-                                         const T *tile) const {
+                                         const Rows &in, const float *tile) const {
         Bits bits = 0;
         eval_batches(std::make_integer_sequence<int, kRounds / kBatch>(),
                      std::integral_constant<int, kBatch>(), bits, slots, first, root,
-                     first ? 0 : w * int(sizeof(Slot) << D), tile);
+                     first ? 0 : w * int(sizeof(Slot) << D), in, tile);
         return bits;
     }
 
@@ -708,19 +637,20 @@ struct Spec {
     // Exit code of every lane's record.  `root` = slots[j] of window 0.  All 64 lanes
     // must be active.
     __device__ __forceinline__ int32_t run(const Slot *slots, const int32_t *exits, int levels,
-                                           const Slot &root, const T *tile) const {
+                                           const Slot &root, const Rows &in,
+                                           const float *tile) const {
         if constexpr (kExitWord) {
             using EW = ExitWord;
             const EW *ew = reinterpret_cast<const EW *>(exits);
             int w = 0;
             const EW e0 = ew[0];
-            int32_t code = pick(e0, walk(eval(slots, true, root, 0, tile)));
-            bool done = code < 0;
+            int32_t code = pick(e0, walk(eval(slots, true, root, 0, in, tile)));
+            bool done = code < 0 || !has;
             if (!done) w = code;
             for (int level = 1; level < levels; ++level) {
                 if (__all(done)) break;
                 const EW e = ew[w];             // w stays a valid window once done
-                const Bits bits = eval(slots, false, root, w, tile);
+                const Bits bits = eval(slots, false, root, w, in, tile);
                 if (!done) {
                     code = pick(e, walk(bits));
                     done = code < 0;
@@ -730,12 +660,12 @@ struct Spec {
             return code;
         } else {
             int w = 0;
-            int32_t code = exits[walk(eval(slots, true, root, 0, tile))];
-            bool done = code < 0 || (TR < kTileRows && j >= kRounds);   // lanes without a record
+            int32_t code = exits[walk(eval(slots, true, root, 0, in, tile))];
+            bool done = code < 0 || !has;
             if (!done) w = code;
             for (int level = 1; level < levels; ++level) {
                 if (__all(done)) break;
-                const Bits bits = eval(slots, false, root, w, tile);
+                const Bits bits = eval(slots, false, root, w, in, tile);
                 if (!done) {
                     code = exits[(w << D) + walk(bits)];
                     done = code < 0;
@@ -743,18 +673,6 @@ struct Spec {
                 }
             }
             return code;
-        }
-    }
-
-    // Lane r's result for record r of the tile (r < TR).  With 32-record tiles of 32-lane
-    // groups, records 16..31 live in lanes 32..47: one ds_bpermute brings them down.
-    __device__ __forceinline__ int32_t in_record_order(int32_t v) const {
-        if constexpr (S == 32 && TR == 32) {
-            const int lane = seg_shift + j;
-            const int src = lane < 16 ? lane : lane + 16;   // lanes >= 32 carry no record
-            return __builtin_amdgcn_ds_bpermute((src & 63) << 2, v);
-        } else {
-            return v;
         }
     }
 };
@@ -809,7 +727,7 @@ __device__ __forceinline__ void flush_results(const KArgs &a, const uint8_t *buf
     const int nbytes = int(r1 - r0) * esize;
     uint8_t *dst = static_cast<uint8_t *>(a.out) + r0 * esize;
     int done = 0;
-    if (a.out_vec) {   // dst is 16-byte aligned: r0 is a multiple of 32 or 64 records
+    if (a.out_vec) {   // dst is 16-byte aligned: r0 is a multiple of 16 records
         typedef int i32x4 __attribute__((ext_vector_type(4)));
         const int nvec = nbytes >> 4;
         for (int i = lane; i < nvec; i += 64)
@@ -825,27 +743,26 @@ __device__ __forceinline__ void flush_results(const KArgs &a, const uint8_t *buf
     }
 }
 
-// Persistent tile loop over tiles of TR records.  Wavefront g of G takes the contiguous
-// tile range [g*chunk, (g+1)*chunk), chunk = ceil(tiles / G), so its results form one
-// contiguous run of the output.  `body(t)` walks staged tile t and returns each lane's
-// result (lane r: record r of the tile; lanes >= TR have none).  No workgroup barrier
+// Persistent tile loop over tiles of Tile::TR records.  Wavefront g of G takes the
+// contiguous tile range [g*chunk, (g+1)*chunk), chunk = ceil(tiles / G), so its results form
+// one contiguous run of the output.  `body()` walks the staged tile and returns each lane's
+// result, that of the tile's record `orow` (-1: the lane has none).  No workgroup barrier
 // inside: the wavefronts of a workgroup process different numbers of tiles.
-template <int XT, int RS, int LOAD, int LAYOUT = kRowMajor, int TR = kTileRows, class Body>
+template <class Tile, class Body>
 __device__ __forceinline__ void tile_loop(const KArgs &a, float *tile, uint8_t *obuf, int lane,
-                                          Body body) {
-    constexpr int RSW = row_words<XT, RS>();
+                                          int orow, Body body) {
+    constexpr int TR = Tile::TR;
     const int64_t G = int64_t(gridDim.x) * a.waves;
     const int64_t gw = int64_t(blockIdx.x) * a.waves + (threadIdx.x >> 6);
     const int64_t chunk = (a.in.n_tiles + G - 1) / G;
     const int64_t t0 = gw * chunk < a.in.n_tiles ? gw * chunk : a.in.n_tiles;
     const int64_t t1 = t0 + chunk < a.in.n_tiles ? t0 + chunk : a.in.n_tiles;
-    const int64_t n_full = a.in.n / TR;            // tiles with TR valid records
     const int esize = a.out_kind == 0 ? 1 : 4;
     int64_t fl = t0;                               // first tile whose results are buffered
 
     auto finish = [&](int64_t t, int32_t v) {
-        const int slot = int(t - fl) * TR + lane;
-        if (TR == kTileRows || lane < TR) {
+        const int slot = int(t - fl) * TR + orow;
+        if (TR == kTileRows || orow >= 0) {
             if (esize == 1)
                 obuf[slot] = uint8_t(v);
             else
@@ -859,46 +776,38 @@ __device__ __forceinline__ void tile_loop(const KArgs &a, float *tile, uint8_t *
         }
     };
 
-    if constexpr (LOAD != kLoadScalar && has_vec_staging<XT, RS, TR>() && RSW <= 64) {
-        // Full tiles: the loads of tile t + 1 are in flight in registers while tile t is
-        // walked.  The partial last tile of the input, if any, is staged on its own.
-        VecTile<RSW, LOAD == kLoadExact, TR> buf;
-        const int64_t tf = t1 < n_full ? t1 : n_full;
-        int64_t t = t0;
-        if (t < tf) buf.load_full(a.in, t, lane);
+    int64_t t = t0;
+    if constexpr (Tile::kPrefetch) {
+        // The loads of tile t + 1 are in flight in registers while tile t is walked.  The
+        // input's last tiles, where loads would leave it, are staged on their own.
+        Tile buf;
+        const int64_t end = Tile::prefetch_end(a.in);
+        const int64_t tf = t1 < end ? t1 : end;
+        if (t < tf) buf.load(a.in, t, lane);
         for (; t < tf; ++t) {
             wave_sync();                 // previous tile fully read
-            buf.template store<LAYOUT>(a.in, tile, lane);
+            buf.store(a.in, tile, lane);
             wave_sync();                 // tile visible to every lane
-            if (t + 1 < tf) buf.load_full(a.in, t + 1, lane);
-            finish(t, body(t));
+            if (t + 1 < tf) buf.load(a.in, t + 1, lane);
+            finish(t, body());
         }
-        if (t < t1) {                         // t == n_full: the partial tile
-            wave_sync();
-            stage_now<XT, RS, LOAD, LAYOUT, TR>(a.in, tile, t, lane);
-            wave_sync();
-            finish(t, body(t));
-        }
-    } else {
-        for (int64_t t = t0; t < t1; ++t) {
-            wave_sync();
-            stage_now<XT, RS, LOAD, LAYOUT, TR>(a.in, tile, t, lane);
-            wave_sync();
-            finish(t, body(t));
-        }
+    }
+    for (; t < t1; ++t) {
+        wave_sync();
+        Tile::stage(a.in, tile, t, lane);
+        wave_sync();
+        finish(t, body());
     }
 }
 
 // LDS layout: [tables (if staged)] [one record tile per wavefront] [one result buffer per
-// wavefront].  `tile` is the word view of this wavefront's tile (TR records).
-template <int XT, int RS, int TR = kTileRows>
-__device__ __forceinline__ void wave_buffers(const KArgs &a, char *after_tables, float *&tile,
-                                             uint8_t *&obuf) {
-    constexpr int kTileBytes = TR * row_words<XT, RS>() * 4;
+// wavefront].  `tile` is the word view of this wavefront's tile (tile_rows records).
+__device__ __forceinline__ void wave_buffers(const KArgs &a, int tile_rows, char *after_tables,
+                                             float *&tile, uint8_t *&obuf) {
     const int wave = threadIdx.x >> 6;
-    tile = reinterpret_cast<float *>(after_tables + wave * kTileBytes);
-    const int obytes = out_buffer_bytes(a.out_cap, a.out_kind == 0 ? 1 : 4, TR);
-    obuf = reinterpret_cast<uint8_t *>(after_tables) + a.waves * kTileBytes + wave * obytes;
+    tile = reinterpret_cast<float *>(after_tables + wave * a.tile_bytes);
+    const int obytes = out_buffer_bytes(a.out_cap, a.out_kind == 0 ? 1 : 4, tile_rows);
+    obuf = reinterpret_cast<uint8_t *>(after_tables) + a.waves * a.tile_bytes + wave * obytes;
 }
 
 template <class T>

@@ -15,8 +15,16 @@
 #include "encode.hpp"
 #include "kernels.hpp"
 #include "library.hpp"
+#include "tiles.hpp"
 
 namespace {
+
+using dtree::align16;
+using dtree::exact_rows;
+using dtree::load_mode_for;
+using dtree::make_rows;
+using dtree::make_tile_rows;
+using dtree::tile_shape;
 
 thread_local std::string g_last_error;
 
@@ -28,8 +36,6 @@ dt_status fail(dt_status s, const std::string &msg) {
 dt_status hip_fail(hipError_t e, const char *what) {
     return fail(DT_ERR_HIP, std::string(what) + ": " + hipGetErrorString(e));
 }
-
-inline int64_t align16(int64_t b) { return (b + 15) & ~int64_t(15); }
 
 int row_stride_for(int32_t n_features) {
     int rs = 4;
@@ -176,7 +182,7 @@ struct Plan {
     int blocks_per_cu = 0;
     int lds_bytes = 0;
     int out_cap = 0;          // single-tree kernels: result tiles buffered per wavefront
-    int tile_rows = dtree::kTileRows;   // records per wavefront tile
+    dtree::TileShape tile;    // single-tree kernels: the record tile
     int tables_in_lds = 0;
     dt_status status = DT_ERR_UNSUPPORTED;
     std::string why;
@@ -196,8 +202,14 @@ std::vector<const void *> g_prepared;
 // records that depth-5 and depth-6 windows use (682 us against 726 us with 12 at depth
 // 6, 710 against 729 us at depth 5).
 // The path reduction is latency-bound and takes as many wavefronts as fit, up to 8.
-int target_waves_per_cu(int algo, int tile_bytes) {
-    const int hbm = std::max(2, std::min(32, (64 * 1024) / tile_bytes));
+// Row tiles count as the next power of two: 8 wavefronts of 48 uint8 features run 31.8 us
+// and 16 run 32.5 us, where 64 KiB of their 3.3 KiB tiles (24 wavefronts) run 34.3 us.  Tiles
+// of 16 records keep 16 lanes walking, and take 8 (250 fp32 features: 79.7 us against 90 us
+// with 4).
+int target_waves_per_cu(int algo, int tile_rows, int tile_bytes) {
+    int size = 256;
+    while (size < tile_bytes) size <<= 1;
+    const int hbm = tile_rows <= 16 ? 8 : std::max(2, std::min(32, (64 * 1024) / size));
     if (algo == DT_ALGO_DATA) return hbm;
     if (algo == DT_ALGO_SPECULATIVE)
         return std::min(16, hbm);
@@ -225,14 +237,13 @@ constexpr int kMaxOutCap = 256;
 // records of element type `elem_type` and results of `out_bytes` bytes (1 or 4).  The path
 // kernel also keeps its path arrays (kPathIntsPerWave ints per wavefront) after the result
 // buffers.
-dt_status make_plan(const DeviceCaps &caps, int algo, int elem_type, int row_stride,
+dt_status make_plan(const DeviceCaps &caps, int algo, int elem_type, int n_features,
                     int load_mode, int depth, int64_t table_bytes, int out_bytes,
                     int waves_per_cu, Plan *plan) {
     const int path_bytes = algo == DT_ALGO_PATH ? dtree::kPathIntsPerWave * 4 : 0;
-    const int tile_rows =
-        dtree::tile_rows_for(algo, depth, row_stride * dtree::elem_bytes(elem_type));
-    plan->tile_rows = tile_rows;
-    const int record_tile_bytes = dtree::tile_bytes_for(row_stride, elem_type, tile_rows);
+    plan->tile = tile_shape(algo, elem_type, n_features, load_mode, depth);
+    const int tile_rows = plan->tile.tile_rows;
+    const int record_tile_bytes = plan->tile.tile_bytes;
     const int tile_bytes = record_tile_bytes + path_bytes;
     const int res_bytes = tile_rows * out_bytes;   // one tile of results
     if (tile_bytes + res_bytes > caps.lds_per_block) {
@@ -243,7 +254,7 @@ dt_status make_plan(const DeviceCaps &caps, int algo, int elem_type, int row_str
         table_bytes + int64_t(kMinLdsWaves) * (tile_bytes + res_bytes) <= caps.lds_per_block;
     const int table_lds = tab_lds ? int(table_bytes) : 0;
     plan->tables_in_lds = tab_lds ? 1 : 0;
-    plan->fn = dtree::kernel_for(algo, elem_type, row_stride, load_mode, tab_lds, depth);
+    plan->fn = dtree::kernel_for(algo, elem_type, plan->tile, tab_lds, depth);
     if (!plan->fn) {
         plan->why = "no kernel instance for this configuration";
         return plan->status = DT_ERR_UNSUPPORTED;
@@ -253,13 +264,14 @@ dt_status make_plan(const DeviceCaps &caps, int algo, int elem_type, int row_str
     if (plan->status != DT_OK) return plan->status;
 
     const int target =
-        waves_per_cu > 0 ? waves_per_cu : target_waves_per_cu(algo, record_tile_bytes);
+        waves_per_cu > 0 ? waves_per_cu
+                         : target_waves_per_cu(algo, tile_rows, tile_rows * plan->tile.row_bytes);
     // Try every workgroup size and count per CU; keep the shape reaching the most resident
     // wavefronts up to the target (registers and the LDS both limit residency); on ties
     // prefer larger workgroups (fewer table copies), then a larger result buffer.
     int best = 0, best_cap = 0;
     const int max_waves =
-        dtree::tree_max_waves(algo, depth, row_stride * dtree::elem_bytes(elem_type));
+        dtree::tree_max_waves(algo, depth, tile_rows, plan->tile.prefetch_regs);
     for (int w = std::min(max_waves, target); w >= 1; --w) {
         for (int bpc = (target + w - 1) / w; bpc >= 1; --bpc) {
             const int budget = std::min(caps.lds_per_block, caps.lds_per_cu / bpc);
@@ -268,6 +280,9 @@ dt_status make_plan(const DeviceCaps &caps, int algo, int elem_type, int row_str
                 std::min(kMaxOutCap, (budget - table_lds - w * tile_bytes) / (w * res_bytes));
             const int lds = dtree::lds_bytes_for(table_lds, record_tile_bytes, w, cap * res_bytes) +
                             w * path_bytes;
+            // a shape that cannot beat the best one is not asked for its occupancy
+            const int most = std::min(target, bpc * w);
+            if (most < best || (most == best && (w != plan->waves || cap <= best_cap))) continue;
             int nb = 0;
             hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, plan->fn, w * 64,
                                                                         size_t(lds));
@@ -351,36 +366,17 @@ struct dt_forest {
     int row_stride = 0;
     int vote_words = 0;
     ForestEncoding enc[2];       // [DT_ALGO_DATA], [DT_ALGO_SPECULATIVE]
-    Plan plan[2][dtree::kLoadModes];  // [algo][load mode]
+    Plan plan[2][dtree::kForestLoadModes];  // [algo][load mode]
 };
 
 namespace {
 
-// The fastest record-tile load path the layout of the features allows.
-int load_mode_for(const void *d_x, int elem_type, int64_t ld, int32_t n_features,
-                  int row_stride) {
-    const bool dense = ld == n_features && (n_features * dtree::elem_bytes(elem_type)) % 16 == 0 &&
+// The fastest record-tile load path of the forest kernels.
+int forest_load_mode_for(const void *d_x, int64_t ld, int32_t n_features, int row_stride) {
+    const bool dense = ld == n_features && n_features % 4 == 0 &&
                        (reinterpret_cast<uintptr_t>(d_x) & 15u) == 0;
     if (!dense) return dtree::kLoadScalar;
     return n_features == row_stride ? dtree::kLoadExact : dtree::kLoadVec;
-}
-
-uint32_t magic_div(int32_t d) {
-    return d >= 2 ? uint32_t(((uint64_t(1) << 32) + uint64_t(d) - 1) / uint64_t(d)) : 0u;
-}
-
-dtree::Rows make_rows(const void *d_x, int elem_type, int64_t n, int64_t ld, int32_t n_features,
-                      int tile_rows = dtree::kTileRows) {
-    dtree::Rows r{};
-    r.x = d_x;
-    r.n = n;
-    r.ld = ld;
-    r.n_tiles = (n + tile_rows - 1) / tile_rows;
-    r.n_features = n_features;
-    r.magic_f = magic_div(n_features);
-    r.n_words = n_features * dtree::elem_bytes(elem_type) / 4;   // used by vector loads only
-    r.magic_w = magic_div(r.n_words);
-    return r;
 }
 
 bool valid_elem_type(dt_dtype t) {
@@ -412,13 +408,13 @@ dt_status classify_impl(const dt_tree *tree, const void *d_x, dt_dtype x_type, i
 
     if ((reinterpret_cast<uintptr_t>(d_x) % uintptr_t(dtree::elem_bytes(x_type))) != 0)
         return fail(DT_ERR_INVALID_ARG, "d_x is not aligned to its element size");
-    const int mode = load_mode_for(d_x, x_type, ld, tree->n_features, tree->row_stride);
+    const int mode = load_mode_for(d_x, x_type, ld, tree->n_features);
     const Plan &plan = tree->plan[algo][x_type][mode][out_kind == DT_OUT_CLASS_U8 ? 0 : 1];
     if (plan.status != DT_OK) return fail(plan.status, plan.why);
     const Encoding &enc = tree->enc[encoding_of(algo)];
 
     dtree::KArgs a{};
-    a.in = make_rows(d_x, x_type, n, ld, tree->n_features, plan.tile_rows);
+    a.in = make_tile_rows(d_x, x_type, n, ld, tree->n_features, plan.tile);
     a.slots = enc.d_slots[x_type];
     a.exits = out_kind == DT_OUT_LEAF_I32 ? enc.d_exit_leaf : enc.d_exit_class;
     a.slot_bytes = int32_t(enc.slot_bytes[x_type]);
@@ -428,6 +424,7 @@ dt_status classify_impl(const dt_tree *tree, const void *d_x, dt_dtype x_type, i
     a.waves = plan.waves;
     a.out_kind = out_kind == DT_OUT_CLASS_U8 ? 0 : 1;
     a.out_cap = plan.out_cap;
+    a.tile_bytes = plan.tile.tile_bytes;
     a.out_vec = (reinterpret_cast<uintptr_t>(d_out) & 15u) == 0 ? 1 : 0;
     a.hops = tree->path_hops;
     a.out = d_out;
@@ -484,11 +481,12 @@ dt_status create_impl(const dt_node *nodes, int32_t n_nodes, int32_t n_features,
                     pl[0].why = pl[1].why = "the path kernel reads fp32 records only";
                     continue;
                 }
-                if (m == dtree::kLoadExact && n_features != t->row_stride) continue;
-                if (m != dtree::kLoadScalar && (n_features * dtree::elem_bytes(xt)) % 16 != 0)
-                    continue;
+                const int es = dtree::elem_bytes(xt);
+                if (m == dtree::kLoadExact && !exact_rows(n_features, es)) continue;
+                if (m == dtree::kLoadFlat && (n_features * es) % 16 == 0) continue;
+                if (m == dtree::kLoadBytes && es == 4) continue;
                 for (int o = 0; o < 2; ++o)
-                    make_plan(t->caps, algo, xt, t->row_stride, m, enc.depth, enc.table_bytes(xt),
+                    make_plan(t->caps, algo, xt, n_features, m, enc.depth, enc.table_bytes(xt),
                               o == 0 ? 1 : 4, opt ? opt->waves_per_cu : 0, &pl[o]);
             }
         }
@@ -787,7 +785,7 @@ dt_status forest_create_impl(const dt_node *nodes, const int32_t *offsets, int32
         }
         st = upload_forest(bytes, &f->enc[algo]);
         if (st != DT_OK) { forest_destroy_impl(f); return st; }
-        for (int m = 0; m < dtree::kLoadModes; ++m) {
+        for (int m = 0; m < dtree::kForestLoadModes; ++m) {
             if (f->row_stride > dtree::kMaxRowStride) {
                 f->plan[algo][m].why = "n_features > 256";
                 continue;
@@ -824,7 +822,7 @@ dt_status forest_classify_impl(const dt_forest *f, const float *d_x, int64_t n, 
     if (dev != f->caps.device)
         return fail(DT_ERR_INVALID_ARG, "current device differs from the forest's device");
     const Plan &plan =
-        f->plan[algo][load_mode_for(d_x, dtree::kXF32, ld, f->n_features, f->row_stride)];
+        f->plan[algo][forest_load_mode_for(d_x, ld, f->n_features, f->row_stride)];
     if (plan.status != DT_OK) return fail(plan.status, plan.why);
     const ForestEncoding &enc = f->enc[algo];
 
@@ -985,7 +983,7 @@ dt_status dt_tree_launch_info(const dt_tree *t, const void *d_x, dt_dtype x_type
     if (out_kind != DT_OUT_CLASS_U8 && out_kind != DT_OUT_CLASS_I32 && out_kind != DT_OUT_LEAF_I32)
         return fail(DT_ERR_INVALID_ARG, "unknown out_kind");
     if (ld < t->n_features) return fail(DT_ERR_INVALID_ARG, "ld must be >= n_features");
-    const int mode = load_mode_for(d_x, x_type, ld, t->n_features, t->row_stride);
+    const int mode = load_mode_for(d_x, x_type, ld, t->n_features);
     const Plan &plan = t->plan[algo][x_type][mode][out_kind == DT_OUT_CLASS_U8 ? 0 : 1];
     if (plan.status != DT_OK) return fail(plan.status, plan.why);
     info->waves_per_workgroup = plan.waves;
@@ -994,7 +992,7 @@ dt_status dt_tree_launch_info(const dt_tree *t, const void *d_x, dt_dtype x_type
     info->result_buffer_tiles = plan.out_cap;
     info->tables_in_lds = plan.tables_in_lds;
     info->load_mode = mode;
-    info->tile_rows = plan.tile_rows;
+    info->tile_rows = plan.tile.tile_rows;
     return DT_OK;
 }
 

@@ -143,11 +143,11 @@ __global__ void __launch_bounds__(64 * forest_max_waves(SD == 0 ? 0 : 1, SD, RS)
     auto eval_tree = [&](const char *base, int levels, int slot_bytes) -> int32_t {
         const Slot *sl = reinterpret_cast<const Slot *>(base);
         const int32_t *ex = reinterpret_cast<const int32_t *>(base + slot_bytes);
-        using Spec = dev::Spec<kXF32, RS, SD == 0 ? 2 : SD>;
-        static_assert(Spec::kLayout == dev::kRowMajor, "forest tiles are staged row-major");
+        using Spec = dev::Spec<kXF32, SD == 0 ? 2 : SD,
+                               dev::ExactTile<kXF32, RS, dev::kRowMajor, kTileRows>>;
         const Spec spec(lane);
         const Slot root = sl[spec.j];
-        return spec.run(sl, ex, levels, root, tile);
+        return spec.run(sl, ex, levels, root, a.in, tile);
     };
 
     // A forest whose tables form one chunk is copied once: the tables then stay for every

@@ -4,20 +4,20 @@
 
 namespace dtree {
 
-const void *kernel_for_f32(int algo, int row_stride, int load_mode, bool tables_in_lds, int depth) {
-    return single_tree_kernel<kXF32>(algo, row_stride, load_mode, tables_in_lds, depth);
+const void *kernel_for_f32(int algo, const TileShape &shape, bool tables_in_lds, int depth) {
+    return single_tree_kernel<kXF32>(algo, shape, tables_in_lds, depth);
 }
 
-const void *kernel_for(int algo, int elem_type, int row_stride, int load_mode, bool tables_in_lds,
+const void *kernel_for(int algo, int elem_type, const TileShape &shape, bool tables_in_lds,
                        int depth) {
     if (algo == kAlgoPath)
-        return elem_type == kXF32 ? path_kernel_for(row_stride, load_mode, tables_in_lds, depth)
+        return elem_type == kXF32 ? path_kernel_for(shape, tables_in_lds, depth)
                                   : nullptr;
     switch (elem_type) {
-        case kXF32: return kernel_for_f32(algo, row_stride, load_mode, tables_in_lds, depth);
-        case kXF16: return kernel_for_f16(algo, row_stride, load_mode, tables_in_lds, depth);
-        case kXBF16: return kernel_for_bf16(algo, row_stride, load_mode, tables_in_lds, depth);
-        case kXU8: return kernel_for_u8(algo, row_stride, load_mode, tables_in_lds, depth);
+        case kXF32: return kernel_for_f32(algo, shape, tables_in_lds, depth);
+        case kXF16: return kernel_for_f16(algo, shape, tables_in_lds, depth);
+        case kXBF16: return kernel_for_bf16(algo, shape, tables_in_lds, depth);
+        case kXU8: return kernel_for_u8(algo, shape, tables_in_lds, depth);
         default: return nullptr;
     }
 }

@@ -39,6 +39,15 @@ struct Rows {
     uint32_t magic_f;        // ceil(2^32 / F) for F >= 2 (row = idx / F via mulhi)
     int32_t n_words;         // 4-byte words per dense row, F * elem_bytes / 4 (vector loads)
     uint32_t magic_w;        // ceil(2^32 / n_words) for n_words >= 2
+    // row tiles of the single-tree kernels (kLoadRows, kLoadFlat)
+    int64_t row_pitch;       // bytes from row to row in the input
+    int64_t row_gap;         // row_pitch - 16 * row_vecs
+    int32_t row_vecs;        // 16-byte vectors of a row
+    uint32_t magic_v;        // ceil(2^32 / row_vecs) for row_vecs >= 2
+    int32_t tile_vecs;       // 16-byte vectors of a full tile
+    int32_t lds_pitch;       // bytes from row to row in the LDS tile
+    int32_t lds_off;         // first byte of row 0 in the LDS tile: x modulo 4
+    int32_t short_rows;      // last rows of the input whose last vector would leave it
 };
 
 // Single-tree kernel arguments (passed by value).
@@ -53,6 +62,7 @@ struct KArgs {
     int32_t waves;           // wavefronts per workgroup
     int32_t out_kind;        // 0: uint8 output, 1: int32 output
     int32_t out_cap;         // tiles of results each wavefront buffers in the LDS (>= 1)
+    int32_t tile_bytes;      // LDS bytes of a wavefront's record tile (multiple of 16)
     int32_t out_vec;         // 1: `out` is 16-byte aligned (flushes use 16-byte stores)
     int32_t hops;            // path-reduction kernel: further entries read per round
     void *out;
@@ -61,21 +71,25 @@ struct KArgs {
 // Path-reduction kernel: per wavefront, 64/S segments of 2S path entries (S lanes each).
 constexpr int kPathIntsPerWave = 128;
 
-// Records per wavefront tile of a kernel: 64 (one per lane), except for the speculative
-// kernel with 32- and 64-slot windows (depths 5 and 6) on rows of at least 32 bytes in the
-// LDS.  That kernel reads one or two record rows per round, so a tile of 32 records serves
-// it as well while taking half the LDS, and twice as many wavefronts then fit next to its
-// window tables.  (Rows under 32 bytes keep 64 records: 16-byte staging needs one vector
-// per lane.)
-__host__ __device__ constexpr int tile_rows_for(int algo, int depth, int row_bytes) {
+// Records per wavefront tile of a kernel on exact rows: 64 (one per lane), except for the
+// speculative kernel with 32- and 64-slot windows (depths 5 and 6) on rows of at least 32
+// bytes in the LDS.  That kernel reads one or two record rows per round, so a tile of 32
+// records serves it as well while taking half the LDS, and twice as many wavefronts then
+// fit next to its window tables.  (Rows under 32 bytes keep 64 records: 16-byte staging
+// needs one vector per lane.)
+__host__ __device__ constexpr int exact_tile_rows(int algo, int depth, int row_bytes) {
     return algo == kAlgoSpec && depth >= 5 && row_bytes >= 32 ? 32 : kTileRows;
 }
 
 // Largest workgroup of a single-tree kernel instance, in wavefronts: 8, or 16 for the
-// speculative walk on 32-record tiles, whose registers (at most 128 per lane) fit 16
-// wavefronts per CU and whose small tiles leave the LDS room for them.
-__host__ __device__ constexpr int tree_max_waves(int algo, int depth, int row_bytes) {
-    return tile_rows_for(algo, depth, row_bytes) < kTileRows ? 16 : kMaxWavesPerBlock;
+// speculative walk of wide windows on small tiles (at most 32 prefetch registers per lane),
+// whose registers (at most 128 per lane) fit 16 wavefronts per CU and whose tiles leave the
+// LDS room for them.
+__host__ __device__ constexpr int tree_max_waves(int algo, int depth, int tile_rows,
+                                                 int prefetch_regs) {
+    return algo == kAlgoSpec && depth >= 5 && tile_rows < kTileRows && prefetch_regs <= 32
+               ? 16
+               : kMaxWavesPerBlock;
 }
 
 // LDS bytes of one wavefront's result buffer: cap tiles of `tile_rows` results of
@@ -104,29 +118,70 @@ struct FArgs {
     void *out;
 };
 
-// How record tiles are read from HBM.
+// How record tiles are read from HBM.  Single-tree kernels:
+//   kLoadExact  dense rows of a power of two of words (4 to 64), 16-byte aligned base
+//   kLoadFlat   other dense rows whose width is no multiple of 16 bytes, 4-byte-aligned base
+//   kLoadRows   other rows that all start on 4-byte boundaries
+//   kLoadBytes  rows (of narrow records) that start between words
+// Forest kernels:
+//   kLoadScalar any ld >= F, element-aligned: one element per load
+//   kLoadVec    ld == F, F * elem_bytes % 16 == 0, 16-byte aligned base: 16-byte loads
+//   kLoadExact  as kLoadVec and F == the LDS row stride: every lane loads the same number
+//               of vectors per tile with no bounds test
 enum LoadMode {
-    kLoadScalar = 0,   // any ld >= F, element-aligned: one element per load
-    kLoadVec = 1,      // ld == F, F * elem_bytes % 16 == 0, 16-byte aligned base: 16-byte loads
-    kLoadExact = 2,    // as kLoadVec and F == the LDS row stride: every lane loads the same
-                       // number of vectors per tile with no bounds test
-    kLoadModes = 3
+    kLoadScalar = 0,
+    kLoadFlat = 0,
+    kLoadVec = 1,
+    kLoadRows = 1,
+    kLoadExact = 2,
+    kLoadBytes = 3,
+    kLoadModes = 4,
+    kForestLoadModes = 3
 };
 
-// Kernel instance for (algorithm, record element type, LDS row stride in elements, load
-// mode, tables staged in the LDS or read from global memory, window depth), or nullptr if
-// no such instance exists.  `depth` is ignored by the data kernel.
-const void *kernel_for(int algo, int elem_type, int row_stride, int load_mode, bool tables_in_lds,
+// Row widths of the exact tiles, in 4-byte words: from one 16-byte vector per row to 64
+// (wider rows would need 16 KiB and more of registers per wavefront: row tiles of fewer
+// records).
+constexpr int kMinExactWords = 4;
+constexpr int kMaxExactWords = 64;
+constexpr int kMaxVecs = 16;          // prefetch vectors per lane
+
+// LDS bytes from row to row of fp32 row tiles of `vecs` prefetch vectors per lane and
+// `tile_rows` records (not flat ones): the widest rows of the class and a word.  0 without
+// prefetch, where the width is not a class.
+__host__ __device__ constexpr int row_tile_pitch(int vecs, int tile_rows) {
+    return vecs > 0 ? 16 * (vecs * 64 / tile_rows) + 4 : 0;
+}
+
+// Record tile of a single-tree kernel.
+struct TileShape {
+    int mode = kLoadRows;
+    int row_stride = 0;     // kLoadExact: elements per row
+    int tile_rows = 0;      // records per tile
+    int row_bytes = 0;      // bytes of a row's features
+    int vecs = 0;           // row tiles: prefetch vectors per lane (0: none)
+    int row_vecs = 0;       // row tiles: 16-byte vectors of a row
+    int tile_vecs = 0;      // row tiles: vectors of a full tile
+    int lds_pitch = 0;      // LDS bytes from row to row (kLoadBytes: less the input pitch
+                            // modulo 4, known at the call)
+    int tile_bytes = 0;     // LDS bytes of the tile (multiple of 16)
+    int prefetch_regs = 0;  // registers per lane that hold the next tile
+};
+
+// Kernel instance for (algorithm, record element type, record tile, tables staged in the
+// LDS or read from global memory, window depth), or nullptr if no such instance exists.
+// `depth` is ignored by the data kernel.
+const void *kernel_for(int algo, int elem_type, const TileShape &shape, bool tables_in_lds,
                        int depth);
 
 // Per element type (one translation unit each): data and speculative kernel instances.
-const void *kernel_for_f32(int algo, int row_stride, int load_mode, bool tables_in_lds, int depth);
-const void *kernel_for_f16(int algo, int row_stride, int load_mode, bool tables_in_lds, int depth);
-const void *kernel_for_bf16(int algo, int row_stride, int load_mode, bool tables_in_lds, int depth);
-const void *kernel_for_u8(int algo, int row_stride, int load_mode, bool tables_in_lds, int depth);
+const void *kernel_for_f32(int algo, const TileShape &shape, bool tables_in_lds, int depth);
+const void *kernel_for_f16(int algo, const TileShape &shape, bool tables_in_lds, int depth);
+const void *kernel_for_bf16(int algo, const TileShape &shape, bool tables_in_lds, int depth);
+const void *kernel_for_u8(int algo, const TileShape &shape, bool tables_in_lds, int depth);
 
 // Path-reduction kernel instance (fp32 records, speculative windows of depth 1..6).
-const void *path_kernel_for(int row_stride, int load_mode, bool tables_in_lds, int depth);
+const void *path_kernel_for(const TileShape &shape, bool tables_in_lds, int depth);
 
 // Forest kernel instance; `vote_words` = 32-bit words of packed 8-bit counters
 // (2, 4 or 16 for up to 8, 16 or 64 classes); `exit_mode`: exit codes stored as int32 (0)

@@ -3,8 +3,8 @@
 
 namespace dtree {
 
-const void *kernel_for_f16(int algo, int row_stride, int load_mode, bool tables_in_lds, int depth) {
-    return single_tree_kernel<kXF16>(algo, row_stride, load_mode, tables_in_lds, depth);
+const void *kernel_for_f16(int algo, const TileShape &shape, bool tables_in_lds, int depth) {
+    return single_tree_kernel<kXF16>(algo, shape, tables_in_lds, depth);
 }
 
 }  // namespace dtree

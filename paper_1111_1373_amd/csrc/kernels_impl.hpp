@@ -25,9 +25,8 @@ namespace {
 
 using dev::Slot;
 
-template <int XT, int RS, int LOAD, bool TAB_LDS>
+template <int XT, class Tile, bool TAB_LDS>
 __global__ void __launch_bounds__(512) data_kernel(KArgs a) {
-    using T = typename dev::Elem<XT>::T;
     extern __shared__ int4 lds[];
     const typename dev::Node<XT>::S *slots;
     const int32_t *exits;
@@ -35,90 +34,147 @@ __global__ void __launch_bounds__(512) data_kernel(KArgs a) {
     const int lane = threadIdx.x & 63;
     float *tile;
     uint8_t *obuf;
-    dev::wave_buffers<XT, RS>(a, tiles, tile, obuf);
-    const T *row = reinterpret_cast<const T *>(tile) + lane * RS;
-    const int sw = dev::swz_el<XT, RS>(lane);
+    dev::wave_buffers(a, Tile::TR, tiles, tile, obuf);
+    const int r = lane & (Tile::TR - 1);     // record walked by this lane
+    const auto *row = Tile::row(a.in, tile, r);
+    const int sw = Tile::swizzle(r);
     const typename dev::Node<XT>::S root0 = slots[1];   // window 0's root, for every record
-    dev::tile_loop<XT, RS, LOAD>(a, tile, obuf, lane, [&](int64_t) -> int32_t {
+    dev::tile_loop<Tile>(a, tile, obuf, lane, lane < Tile::TR ? lane : -1, [&]() -> int32_t {
         return ~dev::walk_data<XT>(slots, exits, a.depth, a.levels, row, sw, root0);
     });
 }
 
-template <int XT, int RS, int LOAD, bool TAB_LDS, int D>
-__global__ void __launch_bounds__(64 * tree_max_waves(kAlgoSpec, D, RS * int(sizeof(typename dev::Elem<XT>::T))))
+template <int XT, class Tile, bool TAB_LDS, int D>
+__global__ void __launch_bounds__(64 * tree_max_waves(kAlgoSpec, D, Tile::TR, Tile::kRegs))
 spec_kernel(KArgs a) {
-    using T = typename dev::Elem<XT>::T;
     using NS = typename dev::Node<XT>::S;
     extern __shared__ int4 lds[];
     const NS *slots;
     const int32_t *exits;
     char *tiles = dev::bind_tables<TAB_LDS>(a, lds, slots, exits);
     const int lane = threadIdx.x & 63;
-    constexpr int TR = tile_rows_for(kAlgoSpec, D, RS * int(sizeof(T)));
     float *tile;
     uint8_t *obuf;
-    dev::wave_buffers<XT, RS, TR>(a, tiles, tile, obuf);
-    using Spec = dev::Spec<XT, RS, D, TR>;
-    const Spec spec(lane);
+    dev::wave_buffers(a, Tile::TR, tiles, tile, obuf);
+    const dev::Spec<XT, D, Tile> spec(lane);
     const NS root = slots[spec.j];   // window 0 is shared by every record
-    const T *el = reinterpret_cast<const T *>(tile);
-    dev::tile_loop<XT, RS, LOAD, Spec::kLayout, TR>(a, tile, obuf, lane, [&](int64_t) -> int32_t {
-        return ~spec.in_record_order(spec.run(slots, exits, a.levels, root, el));
+    dev::tile_loop<Tile>(a, tile, obuf, lane, spec.record(), [&]() -> int32_t {
+        return ~spec.run(slots, exits, a.levels, root, a.in, tile);
     });
 }
 
 // ---- instance tables ------------------------------------------------------------------
-template <int XT, int RS, int LOAD, bool TAB_LDS>
-const void *spec_for(int depth) {
-    switch (depth) {
-        case 1: return reinterpret_cast<const void *>(&spec_kernel<XT, RS, LOAD, TAB_LDS, 1>);
-        case 2: return reinterpret_cast<const void *>(&spec_kernel<XT, RS, LOAD, TAB_LDS, 2>);
-        case 3: return reinterpret_cast<const void *>(&spec_kernel<XT, RS, LOAD, TAB_LDS, 3>);
-        case 4: return reinterpret_cast<const void *>(&spec_kernel<XT, RS, LOAD, TAB_LDS, 4>);
-        case 5: return reinterpret_cast<const void *>(&spec_kernel<XT, RS, LOAD, TAB_LDS, 5>);
-        case 6: return reinterpret_cast<const void *>(&spec_kernel<XT, RS, LOAD, TAB_LDS, 6>);
-        default: return nullptr;
-    }
-}
+// Exact rows: the tile layout of an algorithm.  The speculative walk's 64- and 32-lane
+// groups read one or two record rows per round: flat rows, so that a round's row is its
+// group's first row plus a constant (an instruction offset; a per-row swizzle would be a
+// per-round register).  Narrower groups read 64/S rows at once, and the swizzle keeps rows
+// reading the same feature on distinct banks.
+template <int XT, int RS, int D>   // D = 0: data walk
+using Exact = dev::ExactTile<XT, RS, D >= 5 ? dev::kRowFlat : dev::kRowMajor,
+                             exact_tile_rows(D == 0 ? kAlgoData : kAlgoSpec, D,
+                                             RS * int(sizeof(typename dev::Elem<XT>::T)))>;
 
-template <int XT, int RS, int LOAD, bool TAB_LDS>
-const void *for_variant(int algo, int depth) {
+template <int XT, int RS, bool TAB_LDS>
+const void *exact_for(int algo, int depth) {
     if (algo == kAlgoData)
-        return reinterpret_cast<const void *>(&data_kernel<XT, RS, LOAD, TAB_LDS>);
-    if (algo == kAlgoSpec) return spec_for<XT, RS, LOAD, TAB_LDS>(depth);
-    return nullptr;
-}
-
-template <int XT, int RS, int LOAD>
-const void *for_load(int algo, bool tab_lds, int depth) {
-    if constexpr (LOAD != kLoadScalar && !dev::has_vec_staging<XT, RS>()) {
-        return nullptr;   // rows narrower than one 16-byte vector: scalar loads only
-    } else {
-        return tab_lds ? for_variant<XT, RS, LOAD, true>(algo, depth)
-                       : for_variant<XT, RS, LOAD, false>(algo, depth);
+        return reinterpret_cast<const void *>(&data_kernel<XT, Exact<XT, RS, 0>, TAB_LDS>);
+    switch (depth) {
+        case 1: return reinterpret_cast<const void *>(&spec_kernel<XT, Exact<XT, RS, 1>, TAB_LDS, 1>);
+        case 2: return reinterpret_cast<const void *>(&spec_kernel<XT, Exact<XT, RS, 2>, TAB_LDS, 2>);
+        case 3: return reinterpret_cast<const void *>(&spec_kernel<XT, Exact<XT, RS, 3>, TAB_LDS, 3>);
+        case 4: return reinterpret_cast<const void *>(&spec_kernel<XT, Exact<XT, RS, 4>, TAB_LDS, 4>);
+        case 5: return reinterpret_cast<const void *>(&spec_kernel<XT, Exact<XT, RS, 5>, TAB_LDS, 5>);
+        case 6: return reinterpret_cast<const void *>(&spec_kernel<XT, Exact<XT, RS, 6>, TAB_LDS, 6>);
+        default: return nullptr;
     }
 }
 
 template <int XT, int RS>
-const void *for_stride(int algo, int load_mode, bool tab_lds, int depth) {
-    switch (load_mode) {
-        case kLoadScalar: return for_load<XT, RS, kLoadScalar>(algo, tab_lds, depth);
-        case kLoadVec: return for_load<XT, RS, kLoadVec>(algo, tab_lds, depth);
-        case kLoadExact: return for_load<XT, RS, kLoadExact>(algo, tab_lds, depth);
-        default: return nullptr;
+const void *exact_kernel(int algo, bool tab_lds, int depth) {
+    constexpr int words = dev::row_words<XT, RS>();
+    if constexpr (words < kMinExactWords || words > kMaxExactWords)
+        return nullptr;
+    else
+        return tab_lds ? exact_for<XT, RS, true>(algo, depth) : exact_for<XT, RS, false>(algo, depth);
+}
+
+template <int XT, bool FLAT, bool TAB_LDS, int NV, int TR>
+const void *row_for(int algo, int depth) {
+    using Tile = dev::RowTile<XT, FLAT, NV, TR>;
+    if constexpr (TR < kTileRows) {   // the wide windows' tiles never have more records
+        if (depth == 5 && algo == kAlgoSpec)
+            return reinterpret_cast<const void *>(&spec_kernel<XT, Tile, TAB_LDS, 5>);
+        if (depth == 6 && algo == kAlgoSpec)
+            return reinterpret_cast<const void *>(&spec_kernel<XT, Tile, TAB_LDS, 6>);
     }
+    if constexpr (TR == kTileRows || NV > kMaxVecs / 2) {   // 64 records, or wide rows
+        if (algo == kAlgoData)
+            return reinterpret_cast<const void *>(&data_kernel<XT, Tile, TAB_LDS>);
+        switch (depth) {
+            case 1: return reinterpret_cast<const void *>(&spec_kernel<XT, Tile, TAB_LDS, 1>);
+            case 2: return reinterpret_cast<const void *>(&spec_kernel<XT, Tile, TAB_LDS, 2>);
+            case 3: return reinterpret_cast<const void *>(&spec_kernel<XT, Tile, TAB_LDS, 3>);
+            case 4: return reinterpret_cast<const void *>(&spec_kernel<XT, Tile, TAB_LDS, 4>);
+            default: break;
+        }
+    }
+    return nullptr;
+}
+
+template <int XT, bool FLAT, bool TAB_LDS>
+const void *row_kernel(int algo, int vecs, int tile_rows, int depth) {
+    // tiles of 16 records exist only for rows of more than 32 vectors (256 16-bit features
+    // between words are 33)
+    constexpr int kWidest = kMaxRowStride * int(sizeof(typename dev::Elem<XT>::T));
+    if (tile_rows == 64) {
+        switch (vecs) {
+            case 2: return row_for<XT, FLAT, TAB_LDS, 2, 64>(algo, depth);
+            case 3: return row_for<XT, FLAT, TAB_LDS, 3, 64>(algo, depth);
+            case 4: return row_for<XT, FLAT, TAB_LDS, 4, 64>(algo, depth);
+            case 6: return row_for<XT, FLAT, TAB_LDS, 6, 64>(algo, depth);
+            case 8: return row_for<XT, FLAT, TAB_LDS, 8, 64>(algo, depth);
+            case 12: return row_for<XT, FLAT, TAB_LDS, 12, 64>(algo, depth);
+            case 16: return row_for<XT, FLAT, TAB_LDS, 16, 64>(algo, depth);
+            default: return nullptr;
+        }
+    }
+    if (tile_rows == 32) {
+        switch (vecs) {
+            case 2: return row_for<XT, FLAT, TAB_LDS, 2, 32>(algo, depth);
+            case 3: return row_for<XT, FLAT, TAB_LDS, 3, 32>(algo, depth);
+            case 4: return row_for<XT, FLAT, TAB_LDS, 4, 32>(algo, depth);
+            case 6: return row_for<XT, FLAT, TAB_LDS, 6, 32>(algo, depth);
+            case 8: return row_for<XT, FLAT, TAB_LDS, 8, 32>(algo, depth);
+            case 12: return row_for<XT, FLAT, TAB_LDS, 12, 32>(algo, depth);
+            case 16: return row_for<XT, FLAT, TAB_LDS, 16, 32>(algo, depth);
+            default: return nullptr;
+        }
+    }
+    if constexpr (kWidest >= 512) {
+        if (tile_rows == 16 && vecs == 12) return row_for<XT, FLAT, TAB_LDS, 12, 16>(algo, depth);
+        if (tile_rows == 16 && vecs == 16) return row_for<XT, FLAT, TAB_LDS, 16, 16>(algo, depth);
+    }
+    return nullptr;
 }
 
 template <int XT>
-const void *single_tree_kernel(int algo, int row_stride, int load_mode, bool tab_lds, int depth) {
-    switch (row_stride) {
-        case 4: return for_stride<XT, 4>(algo, load_mode, tab_lds, depth);
-        case 8: return for_stride<XT, 8>(algo, load_mode, tab_lds, depth);
-        case 16: return for_stride<XT, 16>(algo, load_mode, tab_lds, depth);
-        case 32: return for_stride<XT, 32>(algo, load_mode, tab_lds, depth);
-        case 64: return for_stride<XT, 64>(algo, load_mode, tab_lds, depth);
-        case 128: return for_stride<XT, 128>(algo, load_mode, tab_lds, depth);
-        case 256: return for_stride<XT, 256>(algo, load_mode, tab_lds, depth);
+const void *single_tree_kernel(int algo, const TileShape &shape, bool tab_lds, int depth) {
+    if (shape.mode != kLoadExact) {
+        const bool flat = shape.mode == kLoadFlat;
+        if (flat)
+            return tab_lds ? row_kernel<XT, true, true>(algo, shape.vecs, shape.tile_rows, depth)
+                           : row_kernel<XT, true, false>(algo, shape.vecs, shape.tile_rows, depth);
+        return tab_lds ? row_kernel<XT, false, true>(algo, shape.vecs, shape.tile_rows, depth)
+                       : row_kernel<XT, false, false>(algo, shape.vecs, shape.tile_rows, depth);
+    }
+    switch (shape.row_stride) {
+        case 4: return exact_kernel<XT, 4>(algo, tab_lds, depth);
+        case 8: return exact_kernel<XT, 8>(algo, tab_lds, depth);
+        case 16: return exact_kernel<XT, 16>(algo, tab_lds, depth);
+        case 32: return exact_kernel<XT, 32>(algo, tab_lds, depth);
+        case 64: return exact_kernel<XT, 64>(algo, tab_lds, depth);
+        case 128: return exact_kernel<XT, 128>(algo, tab_lds, depth);
+        case 256: return exact_kernel<XT, 256>(algo, tab_lds, depth);
         default: return nullptr;
     }
 }

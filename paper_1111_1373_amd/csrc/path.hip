@@ -21,7 +21,7 @@ namespace {
 
 using dev::Slot;
 
-template <int RS, int D>
+template <class Tile, int D>
 struct PathJump {
     static constexpr int S = 1 << D;
     int j;          // slot this lane evaluates (slot 0 is padding)
@@ -40,7 +40,7 @@ struct PathJump {
     // Exit index of this lane's record for one window level.  Round g evaluates record
     // seg_shift + g in every segment; its result is kept by the lane with j == g.
     __device__ __forceinline__ int eval(const Slot *slots, bool first, const Slot &root, int w,
-                                        const float *tile, int hops) const {
+                                        const Rows &in, const float *tile, int hops) const {
         int mine = 0;
         for (int g = 0; g < S; ++g) {
             const int r = seg_shift + g;
@@ -55,7 +55,7 @@ struct PathJump {
                     wr = __shfl(w, r);
                 p = slots[(wr << D) + j];
             }
-            const float xv = dev::feature_at<kXF32, 1>(tile + r * RS, p, dev::swz<RS>(r));
+            const float xv = Tile::at(in, tile, r, 0, p);
             // node evaluation: the chosen child of slot j
             if (j > 0) path[j] = 2 * j + int(!(xv < p.t));
             dev::wave_sync();
@@ -77,14 +77,15 @@ struct PathJump {
     }
 
     __device__ __forceinline__ int32_t run(const Slot *slots, const int32_t *exits, int levels,
-                                           const Slot &root, const float *tile, int hops) const {
+                                           const Slot &root, const Rows &in, const float *tile,
+                                           int hops) const {
         int w = 0;
-        int32_t code = exits[eval(slots, true, root, 0, tile, hops)];
+        int32_t code = exits[eval(slots, true, root, 0, in, tile, hops)];
         bool done = code < 0;
         if (!done) w = code;
         for (int level = 1; level < levels; ++level) {
             if (__all(done)) break;
-            const int e = eval(slots, false, root, w, tile, hops);
+            const int e = eval(slots, false, root, w, in, tile, hops);
             if (!done) {
                 code = exits[(w << D) + e];
                 done = code < 0;
@@ -95,7 +96,7 @@ struct PathJump {
     }
 };
 
-template <int RS, int LOAD, bool TAB_LDS, int D>
+template <class Tile, bool TAB_LDS, int D>
 __global__ void __launch_bounds__(512) path_kernel(KArgs a) {
     extern __shared__ int4 lds[];
     const Slot *slots;
@@ -104,58 +105,69 @@ __global__ void __launch_bounds__(512) path_kernel(KArgs a) {
     const int lane = threadIdx.x & 63;
     float *tile;
     uint8_t *obuf;
-    dev::wave_buffers<kXF32, RS>(a, tiles, tile, obuf);
+    dev::wave_buffers(a, Tile::TR, tiles, tile, obuf);
     // path arrays follow the result buffers: one int per lane pair (2S per segment)
     int *wave_path = reinterpret_cast<int *>(
-                         tiles + a.waves * (kTileRows * RS * 4 +
+                         tiles + a.waves * (a.tile_bytes +
                                             out_buffer_bytes(a.out_cap, a.out_kind == 0 ? 1 : 4))) +
                      (threadIdx.x >> 6) * kPathIntsPerWave;
-    const PathJump<RS, D> pj(lane, wave_path);
+    const PathJump<Tile, D> pj(lane, wave_path);
     const Slot root = slots[pj.j];
-    dev::tile_loop<kXF32, RS, LOAD>(a, tile, obuf, lane, [&](int64_t) -> int32_t {
-        return ~pj.run(slots, exits, a.levels, root, tile, a.hops);
+    dev::tile_loop<Tile>(a, tile, obuf, lane, lane, [&]() -> int32_t {
+        return ~pj.run(slots, exits, a.levels, root, a.in, tile, a.hops);
     });
 }
 
-template <int RS, int LOAD, bool TAB_LDS>
+template <class Tile, bool TAB_LDS>
 const void *for_depth(int depth) {
     switch (depth) {
-        case 1: return reinterpret_cast<const void *>(&path_kernel<RS, LOAD, TAB_LDS, 1>);
-        case 2: return reinterpret_cast<const void *>(&path_kernel<RS, LOAD, TAB_LDS, 2>);
-        case 3: return reinterpret_cast<const void *>(&path_kernel<RS, LOAD, TAB_LDS, 3>);
-        case 4: return reinterpret_cast<const void *>(&path_kernel<RS, LOAD, TAB_LDS, 4>);
-        case 5: return reinterpret_cast<const void *>(&path_kernel<RS, LOAD, TAB_LDS, 5>);
-        case 6: return reinterpret_cast<const void *>(&path_kernel<RS, LOAD, TAB_LDS, 6>);
+        case 1: return reinterpret_cast<const void *>(&path_kernel<Tile, TAB_LDS, 1>);
+        case 2: return reinterpret_cast<const void *>(&path_kernel<Tile, TAB_LDS, 2>);
+        case 3: return reinterpret_cast<const void *>(&path_kernel<Tile, TAB_LDS, 3>);
+        case 4: return reinterpret_cast<const void *>(&path_kernel<Tile, TAB_LDS, 4>);
+        case 5: return reinterpret_cast<const void *>(&path_kernel<Tile, TAB_LDS, 5>);
+        case 6: return reinterpret_cast<const void *>(&path_kernel<Tile, TAB_LDS, 6>);
         default: return nullptr;
     }
 }
 
-template <int RS, int LOAD>
-const void *for_load(bool tab_lds, int depth) {
-    return tab_lds ? for_depth<RS, LOAD, true>(depth) : for_depth<RS, LOAD, false>(depth);
+template <class Tile>
+const void *for_tables(bool tab_lds, int depth) {
+    return tab_lds ? for_depth<Tile, true>(depth) : for_depth<Tile, false>(depth);
 }
 
 template <int RS>
-const void *for_stride(int load_mode, bool tab_lds, int depth) {
-    switch (load_mode) {
-        case kLoadScalar: return for_load<RS, kLoadScalar>(tab_lds, depth);
-        case kLoadVec: return for_load<RS, kLoadVec>(tab_lds, depth);
-        case kLoadExact: return for_load<RS, kLoadExact>(tab_lds, depth);
+const void *exact(bool tab_lds, int depth) {
+    return for_tables<dev::ExactTile<kXF32, RS, dev::kRowMajor, kTileRows>>(tab_lds, depth);
+}
+
+// Row tiles always hold 64 records here; the widest are staged without prefetch.
+template <bool FLAT>
+const void *rows(int vecs, bool tab_lds, int depth) {
+    switch (vecs) {
+        case 0: return for_tables<dev::RowTile<kXF32, FLAT, 0, kTileRows>>(tab_lds, depth);
+        case 2: return for_tables<dev::RowTile<kXF32, FLAT, 2, kTileRows>>(tab_lds, depth);
+        case 3: return for_tables<dev::RowTile<kXF32, FLAT, 3, kTileRows>>(tab_lds, depth);
+        case 4: return for_tables<dev::RowTile<kXF32, FLAT, 4, kTileRows>>(tab_lds, depth);
+        case 6: return for_tables<dev::RowTile<kXF32, FLAT, 6, kTileRows>>(tab_lds, depth);
+        case 8: return for_tables<dev::RowTile<kXF32, FLAT, 8, kTileRows>>(tab_lds, depth);
+        case 12: return for_tables<dev::RowTile<kXF32, FLAT, 12, kTileRows>>(tab_lds, depth);
+        case 16: return for_tables<dev::RowTile<kXF32, FLAT, 16, kTileRows>>(tab_lds, depth);
         default: return nullptr;
     }
 }
 
 }  // namespace
 
-const void *path_kernel_for(int row_stride, int load_mode, bool tables_in_lds, int depth) {
-    switch (row_stride) {
-        case 4: return for_stride<4>(load_mode, tables_in_lds, depth);
-        case 8: return for_stride<8>(load_mode, tables_in_lds, depth);
-        case 16: return for_stride<16>(load_mode, tables_in_lds, depth);
-        case 32: return for_stride<32>(load_mode, tables_in_lds, depth);
-        case 64: return for_stride<64>(load_mode, tables_in_lds, depth);
-        case 128: return for_stride<128>(load_mode, tables_in_lds, depth);
-        case 256: return for_stride<256>(load_mode, tables_in_lds, depth);
+const void *path_kernel_for(const TileShape &shape, bool tables_in_lds, int depth) {
+    if (shape.mode == kLoadFlat) return rows<true>(shape.vecs, tables_in_lds, depth);
+    if (shape.mode == kLoadRows) return rows<false>(shape.vecs, tables_in_lds, depth);
+    switch (shape.row_stride) {
+        case 4: return exact<4>(tables_in_lds, depth);
+        case 8: return exact<8>(tables_in_lds, depth);
+        case 16: return exact<16>(tables_in_lds, depth);
+        case 32: return exact<32>(tables_in_lds, depth);
+        case 64: return exact<64>(tables_in_lds, depth);
         default: return nullptr;
     }
 }

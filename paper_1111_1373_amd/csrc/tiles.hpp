@@ -1,0 +1,105 @@
+// Host-side choice of the record tiles (see LoadMode and TileShape in kernels.hpp).
+#pragma once
+
+#include <cstdint>
+
+#include "kernels.hpp"
+
+namespace dtree {
+
+inline int64_t align16(int64_t b) { return (b + 15) & ~int64_t(15); }
+
+// Record tile of a single-tree kernel for load mode `mode` (see LoadMode).  Row tiles hold
+// 64 records, or, so that a tile stays within kMaxVecs prefetch vectors per lane, 32 or 16
+// of wide rows.  The speculative walk of wide windows (depths 5 and 6) starts from 32, as
+// on exact rows; the path kernel walks 64 at a time and leaves the prefetch out instead.
+inline TileShape tile_shape(int algo, int elem_type, int n_features, int mode, int depth) {
+    TileShape s;
+    s.mode = mode;
+    const int es = elem_bytes(elem_type);
+    const int row_bytes = n_features * es;
+    s.row_bytes = row_bytes;
+    if (mode == kLoadExact) {
+        s.row_stride = n_features;
+        s.tile_rows = exact_tile_rows(algo, depth, row_bytes);
+        s.lds_pitch = row_bytes;
+        s.tile_bytes = s.tile_rows * row_bytes;
+        s.prefetch_regs = s.tile_bytes / 256;
+        return s;
+    }
+    const bool flat = mode == kLoadFlat, bytes = mode == kLoadBytes;
+    s.row_vecs = (row_bytes + (bytes ? 3 : 0) + 15) / 16;   // a row starts within its first word
+    const auto vecs_of = [&](int rows) { return flat ? rows * row_bytes / 16 : rows * s.row_vecs; };
+    s.tile_rows = algo == kAlgoSpec && depth >= 5 ? 32 : kTileRows;
+    while (algo != kAlgoPath && vecs_of(s.tile_rows) > 64 * kMaxVecs) s.tile_rows /= 2;
+    s.tile_vecs = vecs_of(s.tile_rows);
+    for (int v : {2, 3, 4, 6, 8, 12, kMaxVecs}) {
+        if (v * 64 < s.tile_vecs) continue;
+        s.vecs = v;
+        break;
+    }
+    s.prefetch_regs = 4 * s.vecs;
+    s.lds_pitch = flat ? row_bytes
+                       : es == 4 && s.vecs > 0 ? row_tile_pitch(s.vecs, s.tile_rows)
+                                               : 16 * s.row_vecs + 4;
+    s.tile_bytes = int(align16(s.tile_rows * (s.lds_pitch + (bytes ? 3 : 0)) + (bytes ? 3 : 0)));
+    return s;
+}
+
+inline bool exact_rows(int32_t n_features, int elem_bytes) {
+    const int words = n_features * elem_bytes / 4;
+    return (n_features & (n_features - 1)) == 0 && words >= kMinExactWords &&
+           words <= kMaxExactWords;
+}
+
+// Load path of a single-tree call for the layout of the features (see LoadMode).
+inline int load_mode_for(const void *d_x, int elem_type, int64_t ld, int32_t n_features) {
+    const int es = elem_bytes(elem_type);
+    const bool words = reinterpret_cast<uintptr_t>(d_x) % 4 == 0;
+    if (ld != n_features || !words) return words && ld * es % 4 == 0 ? kLoadRows : kLoadBytes;
+    if ((n_features * es) % 16 != 0) return kLoadFlat;
+    return exact_rows(n_features, es) && (reinterpret_cast<uintptr_t>(d_x) & 15u) == 0
+               ? kLoadExact
+               : kLoadRows;
+}
+
+inline uint32_t magic_div(int32_t d) {
+    return d >= 2 ? uint32_t(((uint64_t(1) << 32) + uint64_t(d) - 1) / uint64_t(d)) : 0u;
+}
+
+inline Rows make_rows(const void *d_x, int elem_type, int64_t n, int64_t ld, int32_t n_features,
+                      int tile_rows = kTileRows) {
+    Rows r{};
+    r.x = d_x;
+    r.n = n;
+    r.ld = ld;
+    r.n_tiles = (n + tile_rows - 1) / tile_rows;
+    r.n_features = n_features;
+    r.magic_f = magic_div(n_features);
+    r.n_words = n_features * elem_bytes(elem_type) / 4;   // used by vector loads only
+    r.magic_w = magic_div(r.n_words);
+    return r;
+}
+
+// Records of a single-tree call, for the tile `s`.
+inline Rows make_tile_rows(const void *d_x, int elem_type, int64_t n, int64_t ld,
+                           int32_t n_features, const TileShape &s) {
+    Rows r = make_rows(d_x, elem_type, n, ld, n_features, s.tile_rows);
+    const int es = elem_bytes(elem_type);
+    r.row_pitch = ld * es;
+    r.row_vecs = s.row_vecs;
+    r.row_gap = r.row_pitch - 16 * s.row_vecs;
+    r.magic_v = magic_div(s.row_vecs);
+    r.tile_vecs = s.tile_vecs;
+    r.lds_pitch = s.lds_pitch + (s.mode == kLoadBytes ? int32_t(r.row_pitch % 4) : 0);
+    r.lds_off = int32_t(reinterpret_cast<uintptr_t>(d_x) % 4);
+    // bytes that a row's vectors read past its end: row i's stay inside the input when at
+    // least that many bytes follow it there, (n - 1 - i) * row_pitch of them
+    const int64_t over = s.mode == kLoadRows || s.mode == kLoadBytes
+                             ? int64_t(16) * s.row_vecs - n_features * es
+                             : 0;
+    r.short_rows = int32_t((over + r.row_pitch - 1) / r.row_pitch);
+    return r;
+}
+
+}  // namespace dtree

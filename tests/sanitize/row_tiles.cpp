@@ -1,0 +1,134 @@
+// The record tiles of any width, stride and alignment (csrc/row_tile.hpp with the shapes of
+// csrc/tiles.hpp), built for the host under AddressSanitizer and driven lane by lane: the
+// input and the LDS tile are heap blocks of exactly their sizes, so a vector that leaves
+// either one ends the run; then every feature of every staged record is read back through
+// the addresses the walks use.
+//   row_tiles SEED CASES
+#include <cstdio>
+#include <cstdlib>
+#include <memory>
+#include <random>
+#include <vector>
+
+#include "row_tile.hpp"
+#include "tiles.hpp"
+
+using namespace dtree;
+
+namespace {
+
+std::mt19937_64 rng;
+int pick(int lo, int hi) { return int(lo + rng() % uint64_t(hi - lo + 1)); }
+
+void fail(const char *what, int xt, int F, int64_t ld, int64_t n, int mode, int off) {
+    std::printf("%s: type %d F %d ld %lld n %lld mode %d offset %d\n", what, xt, F, (long long)ld,
+                (long long)n, mode, off);
+    std::exit(1);
+}
+
+template <int XT, bool FLAT, int NV, int TR>
+void drive(const Rows &in, const TileShape &s, int off) {
+    using Tile = dev::RowTile<XT, FLAT, NV, TR>;
+    using T = typename Tile::T;
+    const T *x = static_cast<const T *>(in.x);
+    const int64_t end = Tile::prefetch_end(in);
+    for (int64_t t = 0; t < in.n_tiles; ++t) {
+        for (int way = 0; way < 2; ++way) {
+            const bool prefetched = way == 0;
+            if (prefetched && (!Tile::kPrefetch || t >= end)) continue;
+            std::unique_ptr<dev::f32x4[]> mem(new dev::f32x4[size_t(s.tile_bytes / 16)]);
+            float *tile = reinterpret_cast<float *>(mem.get());
+            if (prefetched) {
+                std::vector<Tile> lanes(64);
+                for (int l = 0; l < 64; ++l) lanes[size_t(l)].load(in, t, l);
+                for (int l = 0; l < 64; ++l) lanes[size_t(l)].store(in, tile, l);
+            } else {
+                for (int pass = 0; pass < 2; ++pass)   // lanes of a wavefront run together: the
+                    for (int l = 0; l < 64; ++l)       // element loads follow every vector
+                        Tile::stage(in, tile, t, l);
+            }
+            for (int r = 0; r < TR && t * TR + r < in.n; ++r)
+                for (int f = 0; f < in.n_features; ++f) {
+                    const T want = x[(t * TR + r) * in.ld + f];
+                    typename dev::Node<XT>::S slot{};
+                    if constexpr (XT == kXF32) slot.f = 4 * f;
+                    else slot = uint32_t(f) << 16;
+                    const T a = dev::feature_at<XT, 1>(Tile::row(in, tile, r), slot, 0);
+                    const T b = Tile::at(in, tile, r / 2, r - r / 2, slot);
+                    if (std::memcmp(&a, &want, sizeof(T)) || std::memcmp(&b, &want, sizeof(T)))
+                        fail(prefetched ? "prefetched tile" : "staged tile", XT, in.n_features,
+                             in.ld, in.n, s.mode, off);
+                }
+        }
+    }
+}
+
+template <int XT, bool FLAT, int TR>
+bool by_vecs(const Rows &in, const TileShape &s, int off) {
+    switch (s.vecs) {
+        case 0: drive<XT, FLAT, 0, TR>(in, s, off); return true;
+        case 2: drive<XT, FLAT, 2, TR>(in, s, off); return true;
+        case 3: drive<XT, FLAT, 3, TR>(in, s, off); return true;
+        case 4: drive<XT, FLAT, 4, TR>(in, s, off); return true;
+        case 6: drive<XT, FLAT, 6, TR>(in, s, off); return true;
+        case 8: drive<XT, FLAT, 8, TR>(in, s, off); return true;
+        case 12: drive<XT, FLAT, 12, TR>(in, s, off); return true;
+        case 16: drive<XT, FLAT, 16, TR>(in, s, off); return true;
+        default: return false;
+    }
+}
+
+template <int XT, bool FLAT>
+bool by_rows(const Rows &in, const TileShape &s, int off) {
+    switch (s.tile_rows) {
+        case 64: return by_vecs<XT, FLAT, 64>(in, s, off);
+        case 32: return by_vecs<XT, FLAT, 32>(in, s, off);
+        case 16: return by_vecs<XT, FLAT, 16>(in, s, off);
+        default: return false;
+    }
+}
+
+template <int XT>
+void one_case() {
+    using T = typename dev::Elem<XT>::T;
+    const int F = pick(0, 2) ? pick(1, 40) : pick(1, kMaxRowStride);
+    const int64_t ld = F + (pick(0, 1) ? 0 : pick(0, 5) ? pick(0, 9) : pick(0, 700));
+    const int64_t n = pick(0, 3) ? pick(1, 200) : pick(1, 20);
+    const int off = pick(0, 1) ? 0 : pick(0, 15);      // elements before the first record
+    // the block starts on a 16-byte boundary and ends with the last record's last feature
+    const size_t count = size_t(off) + size_t((n - 1) * ld + F);
+    std::unique_ptr<T[]> block(new T[count]);
+    for (size_t i = 0; i < count; ++i) {
+        const uint64_t v = rng();
+        std::memcpy(&block[i], &v, sizeof(T));
+    }
+    const void *x = block.get() + off;
+    const int algos[] = {kAlgoData, kAlgoSpec, kAlgoPath};
+    const int algo = algos[XT == kXF32 ? pick(0, 2) : pick(0, 1)];
+    const int depth = pick(1, 6);
+    int mode = load_mode_for(x, XT, ld, F);
+    if (mode == kLoadExact) mode = kLoadRows;           // such rows come strided, too
+    const TileShape s = tile_shape(algo, XT, F, mode, depth);
+    if (s.tile_bytes % 16 != 0) fail("tile size", XT, F, ld, n, mode, off);
+    const Rows in = make_tile_rows(x, XT, n, ld, F, s);
+    const bool ok = mode == kLoadFlat ? by_rows<XT, true>(in, s, off)
+                                      : by_rows<XT, false>(in, s, off);
+    if (!ok) fail("no tile class", XT, F, ld, n, mode, off);
+}
+
+}  // namespace
+
+int main(int argc, char **argv) {
+    rng.seed(argc > 1 ? std::strtoull(argv[1], nullptr, 10) : 1);
+    const int cases = argc > 2 ? std::atoi(argv[2]) : 1000;
+    for (int i = 0; i < cases; ++i) {
+        switch (i % 4) {
+            case 0: one_case<kXF32>(); break;
+            case 1: one_case<kXF16>(); break;
+            case 2: one_case<kXBF16>(); break;
+            default: one_case<kXU8>(); break;
+        }
+    }
+    std::printf("ok %d\n", cases);
+    return 0;
+}

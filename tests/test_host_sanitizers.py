@@ -6,7 +6,9 @@ window depth 1..8, special values, row strides above the feature count, and corr
 trees (tests/sanitize/*).  Any out-of-bounds access, use of freed memory or undefined
 arithmetic aborts the driver; so does a window walk that reaches another leaf than the
 direct walk of the tree.  The two drivers are separate programs: the oracle and the
-library share no code.
+library share no code.  A third driver runs the record tiles of the kernels (device code
+that consists of plain loads and stores) lane by lane on exactly sized blocks; it is built
+with clang, whose vector types the kernels use.
 """
 import os
 import shutil
@@ -52,3 +54,14 @@ def test_oracle_under_sanitizers(tmp_path):
                  libs=("-lm",))
     for seed in (1, 2, 3):
         _run(exe, seed, 1000)
+
+
+def test_record_tiles_under_sanitizers(tmp_path):
+    """Every width, stride and alignment of the records, each element type and algorithm:
+    no load leaves the input, no store the tile, and every feature of every record is read
+    back from where the walks look for it."""
+    clang = "/opt/rocm/lib/llvm/bin/clang++"
+    exe = _build(tmp_path, clang, "-std=c++17", ["tests/sanitize/row_tiles.cpp"], "row_tiles",
+                 includes=("tests/sanitize/hip_stub", "include", "paper_1111_1373_amd/csrc"))
+    for seed in (1, 2, 3):
+        _run(exe, seed, 5000)
