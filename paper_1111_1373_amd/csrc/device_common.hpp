@@ -34,7 +34,10 @@ namespace dev {
 // above the bottom level hold the byte offset alone.  The exit is then known from the
 // last slot of the window, with no read of an exit table.
 struct PackedExits {};
-constexpr int kPackedFeatureMask = 0x3FF;
+
+// Trees as lists of 8-byte nodes instead of windows (forest data walk, walk_list_k).
+struct NodeList {};
+constexpr uint32_t kListFeatureMask = 0x3FF;
 
 // Ordering of LDS accesses among the lanes of one wavefront.  A wavefront's LDS
 // instructions execute in order; the fences keep the compiler from moving accesses
@@ -45,14 +48,6 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-__device__ __forceinline__ uint32_t div_f(uint32_t e, const Rows &in) {
-    return in.n_features == 1 ? e : __umulhi(e, in.magic_f);
-}
-
-__device__ __forceinline__ uint32_t div_w(uint32_t e, const Rows &in) {
-    return in.n_words == 1 ? e : __umulhi(e, in.magic_w);
-}
-
 // Tile layouts.  Row-major (the default): row r at word r*RSW, word w at w ^ swz(r).
 // Column-major (fp32 only, used where every lane reads its own record): column c at word
 // c*64, row r at c*64 + r, so lane r always reads bank r, whatever column it asks for.
@@ -61,17 +56,10 @@ __device__ __forceinline__ uint32_t div_w(uint32_t e, const Rows &in) {
 // swizzle, and staging then stores whole 16-byte vectors.
 enum TileLayout { kRowMajor = 0, kColMajor = 1, kRowFlat = 2 };
 
-// Store 4 consecutive words (c % 4 == 0) of row r into the tile (rows of RSW words;
+// Store 4 consecutive words (c % 4 == 0) of row r into a row-major tile (rows of RSW words;
 // `tile` is the word view of the tile).
 template <int RSW, int LAYOUT = kRowMajor>
 __device__ __forceinline__ void put4(float *tile, int r, int c, f32x4 v) {
-    if constexpr (LAYOUT == kColMajor) {   // 64-record tiles only
-        tile[(c + 0) * kTileRows + r] = v.x;
-        tile[(c + 1) * kTileRows + r] = v.y;
-        tile[(c + 2) * kTileRows + r] = v.z;
-        tile[(c + 3) * kTileRows + r] = v.w;
-        return;
-    }
     if constexpr (LAYOUT == kRowFlat) {
         *reinterpret_cast<f32x4 *>(tile + r * RSW + c) = v;
         return;
@@ -84,30 +72,38 @@ __device__ __forceinline__ void put4(float *tile, int r, int c, f32x4 v) {
     row[(c + 3) ^ s] = v.w;
 }
 
-// Vectorised staging (dense rows of n_words 4-byte words, n_words % 4 == 0, 16-byte
+// Vectorised staging of exact rows (dense rows of RSW 4-byte words, a power of two, 16-byte
 // aligned base), one tile of TR records held in registers so that the next tile's loads
-// overlap the walk of the current one.  RSW = LDS row stride in words.  The element type
-// does not matter here: words are moved unchanged.
+// overlap the walk of the current one.  Every lane owns RSW/4 vectors of a full tile and the
+// LDS positions are shifts and masks.  The element type does not matter here: words are
+// moved unchanged.
 //
 // Loads are never guarded by a branch: guarded loads compile into branches whose joins
 // copy the loaded registers, which forces a wait for every outstanding load right after
 // the prefetch is issued.  A lane whose vector lies past the tile's valid data re-reads
 // the last valid vector instead, so rows past the end of the input hold copies of valid
-// features; their results are never stored.  EXACT (n_words == RSW): every lane owns
-// RSW/4 vectors of a full tile and the LDS positions are shifts and masks.
-template <int RSW, bool EXACT, int TR = kTileRows>
+// features; their results are never stored.
+template <int RSW, int TR = kTileRows>
 struct VecTile {
-    static constexpr int kVec = TR * RSW / 256;   // 16-byte vectors per lane for n_words == RSW
+    static constexpr int kVec = TR * RSW / 256;   // 16-byte vectors per lane
     static_assert(kVec >= 1, "vector staging needs one 16-byte vector per lane and tile");
     f32x4 v[kVec];
 
     __device__ __forceinline__ const f32x4 *base(const Rows &in, int64_t tile) const {
         return reinterpret_cast<const f32x4 *>(static_cast<const char *>(in.x) +
-                                               tile * TR * in.n_words * 4);
+                                               tile * (TR * RSW * 4));
     }
 
-    // Any tile; nvec = vectors holding valid records (>= 1).
-    __device__ __forceinline__ void load_clamped(const Rows &in, int64_t tile, int lane, int nvec) {
+    // Tile with TR valid records.
+    __device__ __forceinline__ void load_full(const Rows &in, int64_t tile, int lane) {
+        const f32x4 *src = base(in, tile) + lane;
+#pragma unroll
+        for (int k = 0; k < kVec; ++k) v[k] = __builtin_nontemporal_load(src + k * 64);
+    }
+
+    // Any tile, including the partial last one.
+    __device__ __forceinline__ void load_tail(const Rows &in, int64_t tile, int lane) {
+        const int nvec = valid_rows<TR>(in, tile) * (RSW / 4);   // >= 1
         const f32x4 *src = base(in, tile);
 #pragma unroll
         for (int k = 0; k < kVec; ++k) {
@@ -116,173 +112,62 @@ struct VecTile {
         }
     }
 
-    // Tile with 64 valid records.
-    __device__ __forceinline__ void load_full(const Rows &in, int64_t tile, int lane) {
-        if constexpr (EXACT) {
-            const f32x4 *src = base(in, tile) + lane;
-#pragma unroll
-            for (int k = 0; k < kVec; ++k) v[k] = __builtin_nontemporal_load(src + k * 64);
-        } else {
-            load_clamped(in, tile, lane, TR * in.n_words / 4);
-        }
-    }
-
-    __device__ __forceinline__ void store_col_major(float *tile, int lane) const;
-
-    // Any tile, including the partial last one.
-    __device__ __forceinline__ void load_tail(const Rows &in, int64_t tile, int lane) {
-        load_clamped(in, tile, lane, (valid_rows<TR>(in, tile) * in.n_words) >> 2);
-    }
-
     template <int LAYOUT = kRowMajor>
-    __device__ __forceinline__ void store(const Rows &in, float *tile, int lane) const {
-        if constexpr (EXACT && LAYOUT == kColMajor && RSW <= 32) {
-            // (wider rows keep the plain stores: the butterfly's 2 x RSW registers would
-            // not fit the forest kernel's 128)
+    __device__ __forceinline__ void store(float *tile, int lane) const {
+        if constexpr (LAYOUT == kColMajor) {
             store_col_major(tile, lane);
-        } else if constexpr (EXACT) {
+        } else {
             constexpr int sh = __builtin_ctz(RSW);
 #pragma unroll
             for (int k = 0; k < kVec; ++k) {
                 const int e = (k * 64 + lane) * 4;
                 put4<RSW, LAYOUT>(tile, e >> sh, e & (RSW - 1), v[k]);
             }
-        } else {
-            const int full = TR * in.n_words / 4;
+        }
+    }
+
+    // Column-major stores of a full tile without bank conflicts (64-record tiles).  With
+    // L = RSW / 4 lanes per row, lane l = a*L + b holds in v[k] the words 4b..4b+3 of row
+    // k*(64/L) + a.  Storing one register at a time would send 64 lanes to only 64/L rows,
+    // i.e. 64/L banks of a column-major tile (an L-way conflict).  Store j instead takes
+    // v[b ^ j] in every lane: its rows (b ^ j)*(64/L) + a are 64 distinct rows, so each store
+    // touches every bank once.  The per-lane choice of register is an XOR butterfly of selects
+    // (log2 L stages of conditional swaps), after which w[j] == v[b ^ j].
+    __device__ __forceinline__ void store_col_major(float *tile, int lane) const {
+        constexpr int L = RSW / 4;                  // lanes per row = vectors per lane
+        constexpr int R = 64 / L;                   // rows per load instruction
+        static_assert(TR == kTileRows && L >= 1 && (L & (L - 1)) == 0, "64-record exact tiles");
+        const int a = lane / L, b = lane % L;
+        f32x4 w[L];
 #pragma unroll
-            for (int k = 0; k < kVec; ++k) {
-                const int q = k * 64 + lane;
-                if (q < full) {
-                    const uint32_t e = uint32_t(q) * 4u;
-                    const int r = int(div_w(e, in));
-                    put4<RSW, LAYOUT>(tile, r, int(e) - r * in.n_words, v[k]);
-                }
+        for (int k = 0; k < L; ++k) w[k] = v[k];
+#pragma unroll
+        for (int bit = 1; bit < L; bit <<= 1) {
+            const bool swap = (b & bit) != 0;
+#pragma unroll
+            for (int k = 0; k < L; ++k) {
+                if (k & bit) continue;
+                const f32x4 lo = w[k], hi = w[k | bit];
+                w[k] = swap ? hi : lo;
+                w[k | bit] = swap ? lo : hi;
             }
+        }
+        // word (4b + i)*64 + (b ^ j)*R + a of the tile
+        float *col = tile + (4 * b) * kTileRows + a;
+#pragma unroll
+        for (int j = 0; j < L; ++j) {
+            float *dst = col + (b ^ j) * R;
+            dst[0 * kTileRows] = w[j].x;
+            dst[1 * kTileRows] = w[j].y;
+            dst[2 * kTileRows] = w[j].z;
+            dst[3 * kTileRows] = w[j].w;
         }
     }
 };
 
-// Column-major stores of a full exact tile without bank conflicts (64-record tiles).  With
-// L = RSW / 4 lanes per row, lane l = a*L + b holds in v[k] the words 4b..4b+3 of row
-// k*(64/L) + a.  Storing one register at a time would send 64 lanes to only 64/L rows,
-// i.e. 64/L banks of a column-major tile (an L-way conflict).  Store j instead takes
-// v[b ^ j] in every lane: its rows (b ^ j)*(64/L) + a are 64 distinct rows, so each store
-// touches every bank once.  The per-lane choice of register is an XOR butterfly of selects
-// (log2 L stages of conditional swaps), after which w[j] == v[b ^ j].
-template <int RSW, bool EXACT, int TR>
-__device__ __forceinline__ void store_col_major_tile(const f32x4 (&v)[RSW / 4], float *tile, int lane) {
-    constexpr int L = RSW / 4;                  // lanes per row = vectors per lane
-    constexpr int R = 64 / L;                   // rows per load instruction
-    static_assert(TR == kTileRows && L >= 1 && (L & (L - 1)) == 0, "64-record exact tiles");
-    const int a = lane / L, b = lane % L;
-    f32x4 w[L];
-#pragma unroll
-    for (int k = 0; k < L; ++k) w[k] = v[k];
-#pragma unroll
-    for (int bit = 1; bit < L; bit <<= 1) {
-        const bool swap = (b & bit) != 0;
-#pragma unroll
-        for (int k = 0; k < L; ++k) {
-            if (k & bit) continue;
-            const f32x4 lo = w[k], hi = w[k | bit];
-            w[k] = swap ? hi : lo;
-            w[k | bit] = swap ? lo : hi;
-        }
-    }
-    // word (4b + i)*64 + (b ^ j)*R + a of the tile
-    float *col = tile + (4 * b) * kTileRows + a;
-#pragma unroll
-    for (int j = 0; j < L; ++j) {
-        float *dst = col + (b ^ j) * R;
-        dst[0 * kTileRows] = w[j].x;
-        dst[1 * kTileRows] = w[j].y;
-        dst[2 * kTileRows] = w[j].z;
-        dst[3 * kTileRows] = w[j].w;
-    }
-}
-
-template <int RSW, bool EXACT, int TR>
-__device__ __forceinline__ void VecTile<RSW, EXACT, TR>::store_col_major(float *tile, int lane) const {
-    store_col_major_tile<RSW, EXACT, TR>(v, tile, lane);
-}
-
-// Vectorised staging of wide rows (RSW > 64 words) in chunks of 16 vectors per lane,
-// without prefetch (loads clamped to the valid vectors as in VecTile).
-template <int RSW, int LAYOUT = kRowMajor, int TR = kTileRows>
-__device__ __forceinline__ void stage_wide(const Rows &in, float *tile, int64_t t, int lane) {
-    const int nvec = (valid_rows<TR>(in, t) * in.n_words) >> 2;
-    const int full = TR * in.n_words / 4;
-    const f32x4 *src = reinterpret_cast<const f32x4 *>(static_cast<const char *>(in.x) +
-                                                       t * TR * in.n_words * 4);
-#pragma unroll 1
-    for (int k0 = 0; k0 < TR * RSW / 256; k0 += 16) {
-        f32x4 v[16];
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            const int q = (k0 + k) * 64 + lane;
-            v[k] = __builtin_nontemporal_load(src + (q < nvec ? q : nvec - 1));
-        }
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            const int q = (k0 + k) * 64 + lane;
-            if (q < full) {
-                const uint32_t e = uint32_t(q) * 4u;
-                const int r = int(div_w(e, in));
-                put4<RSW, LAYOUT>(tile, r, int(e) - r * in.n_words, v[k]);
-            }
-        }
-    }
-}
-
-// General staging: any ld >= F, element-aligned, one element per load.
-template <int XT, int RS, int LAYOUT = kRowMajor, int TR = kTileRows>
-__device__ __forceinline__ void stage_scalar(const Rows &in, float *tile_words, int64_t t,
-                                             int lane) {
-    static_assert(LAYOUT != kColMajor || XT == kXF32, "column-major tiles hold fp32 records");
-    using T = typename Elem<XT>::T;
-    T *tile = reinterpret_cast<T *>(tile_words);
-    const T *x = static_cast<const T *>(in.x);
-    static_assert(LAYOUT != kColMajor || TR == kTileRows, "column-major tiles hold 64 records");
-    const int64_t row0 = t * TR;
-    const int valid = valid_rows<TR>(in, t);
-    // TR * F elements, 64 per pass (TR is 32 or 64)
-    for (int k = 0; k < (TR == kTileRows ? in.n_features : (in.n_features + 1) >> 1); ++k) {
-        const uint32_t idx = uint32_t(k * 64 + lane);
-        const int r = int(div_f(idx, in));
-        const int c = int(idx) - r * in.n_features;
-        if (r >= TR) break;            // only in the last pass of a 32-record tile, odd F
-        T v = T(0);
-        if (r < valid) v = x[(row0 + r) * in.ld + c];
-        if constexpr (LAYOUT == kColMajor)
-            tile[c * kTileRows + r] = v;
-        else if constexpr (LAYOUT == kRowFlat)
-            tile[r * RS + c] = v;
-        else
-            tile[r * RS + (c ^ swz_el<XT, RS>(r))] = v;
-    }
-}
-
-// LDS row stride in words of a row of RS elements of XT, and whether the vector staging
-// path (16-byte loads, at least one vector per lane and row) exists for it.
+// LDS row stride in words of a row of RS elements of XT.
 template <int XT, int RS>
 constexpr int row_words() { return RS * int(sizeof(typename Elem<XT>::T)) / 4; }
-template <int XT, int RS, int TR = kTileRows>
-constexpr bool has_vec_staging() { return TR * row_words<XT, RS>() >= 256; }
-
-// Stage tile t (of TR records) without register prefetch.
-template <int XT, int RS, int LOAD, int LAYOUT = kRowMajor, int TR = kTileRows>
-__device__ __forceinline__ void stage_now(const Rows &in, float *tile, int64_t t, int lane) {
-    constexpr int RSW = row_words<XT, RS>();
-    if constexpr (LOAD != kLoadScalar && has_vec_staging<XT, RS, TR>() && RSW <= 64) {
-        VecTile<RSW, LOAD == kLoadExact, TR> buf;
-        buf.load_tail(in, t, lane);
-        buf.template store<LAYOUT>(in, tile, lane);
-    } else if constexpr (LOAD != kLoadScalar && has_vec_staging<XT, RS, TR>()) {
-        stage_wide<RSW, LAYOUT, TR>(in, tile, t, lane);
-    } else {
-        stage_scalar<XT, RS, LAYOUT, TR>(in, tile, t, lane);
-    }
-}
 
 // ---- record tiles of the single-tree kernels ---------------------------------------------
 // A tile class holds the next tile's loads in registers (load), writes them into the LDS
@@ -294,21 +179,22 @@ template <int XT, int RS, int LAYOUT, int TRv>
 struct ExactTile {
     using T = typename Elem<XT>::T;
     static constexpr int TR = TRv;
+    static constexpr bool kFewArgs = true;
     static constexpr bool kPrefetch = true;
     static constexpr int kRegs = TR * row_words<XT, RS>() / 64;   // prefetch registers per lane
-    VecTile<row_words<XT, RS>(), true, TR> buf;
+    VecTile<row_words<XT, RS>(), TR> buf;
 
     static __device__ __forceinline__ int64_t prefetch_end(const Rows &in) { return in.n / TR; }
     __device__ __forceinline__ void load(const Rows &in, int64_t t, int lane) {
         buf.load_full(in, t, lane);
     }
-    __device__ __forceinline__ void store(const Rows &in, float *tile, int lane) const {
-        buf.template store<LAYOUT>(in, tile, lane);
+    __device__ __forceinline__ void store(const Rows &, float *tile, int lane) const {
+        buf.template store<LAYOUT>(tile, lane);
     }
     static __device__ __forceinline__ void stage(const Rows &in, float *tile, int64_t t, int lane) {
-        VecTile<row_words<XT, RS>(), true, TR> b;
+        VecTile<row_words<XT, RS>(), TR> b;
         b.load_tail(in, t, lane);
-        b.template store<LAYOUT>(in, tile, lane);
+        b.template store<LAYOUT>(tile, lane);
     }
     static __device__ __forceinline__ const T *row(const Rows &, const float *tile, int r) {
         return reinterpret_cast<const T *>(tile) + r * RS;
@@ -435,12 +321,16 @@ __device__ __forceinline__ void walk_data_k(const char *const (&base)[K],
 #pragma unroll
         for (int i = 0; i < K; ++i) win[i] = reinterpret_cast<const Slot *>(base[i]) + (w[i] << D);
         for (int k = level == 0 ? k0 : 0; k < (kPacked ? D - 1 : D); ++k) {
+            // K slot reads, K feature reads, K steps (short of registers the compiler walks
+            // chain after chain: a 32-tree forest 459 us against 372 us)
+            Slot s[K];
+            float xv[K];
 #pragma unroll
-            for (int i = 0; i < K; ++i) {
-                const Slot s = win[i][p[i]];
-                const float xv = feature_at<kXF32, STRIDE>(row, s, sw);
-                p[i] = heap_step(p[i], !(xv < s.t));
-            }
+            for (int i = 0; i < K; ++i) s[i] = win[i][p[i]];
+#pragma unroll
+            for (int i = 0; i < K; ++i) xv[i] = feature_at<kXF32, STRIDE>(row, s[i], sw);
+#pragma unroll
+            for (int i = 0; i < K; ++i) p[i] = heap_step(p[i], !(xv[i] < s[i].t));
         }
         // Every chain takes its exit, finished or not (a finished chain re-walked its last
         // window, so the index stays inside that window's exits), the K reads issued
@@ -449,13 +339,19 @@ __device__ __forceinline__ void walk_data_k(const char *const (&base)[K],
         if constexpr (kPacked) {
             // the bottom step: the slot's word names the feature and both exits (the 11-bit
             // field at bit 10 or bit 21, sign-extended)
+            Slot s[K];
+            float xv[K];
+#pragma unroll
+            for (int i = 0; i < K; ++i) s[i] = win[i][p[i]];
+            __builtin_amdgcn_sched_barrier(0);   // these reads are all issued first
 #pragma unroll
             for (int i = 0; i < K; ++i) {
-                const Slot s = win[i][p[i]];
-                const Slot node{s.t, int(__builtin_amdgcn_ubfe(uint32_t(s.f), 0, 10))};
-                const float xv = feature_at<kXF32, STRIDE>(row, node, sw);
-                c[i] = __builtin_amdgcn_sbfe(s.f, !(xv < s.t) ? 21u : 10u, 11u);
+                const Slot node{s[i].t, int(__builtin_amdgcn_ubfe(uint32_t(s[i].f), 0, 10))};
+                xv[i] = feature_at<kXF32, STRIDE>(row, node, sw);
             }
+#pragma unroll
+            for (int i = 0; i < K; ++i)
+                c[i] = __builtin_amdgcn_sbfe(s[i].f, !(xv[i] < s[i].t) ? 21u : 10u, 11u);
         } else {
 #pragma unroll
             for (int i = 0; i < K; ++i)
@@ -477,6 +373,70 @@ __device__ __forceinline__ void walk_data_k(const char *const (&base)[K],
         }
         if (__all(all_done)) break;
     }
+}
+
+// Data decomposition over K trees stored as node lists (irregular trees of forests): nodes
+// {t, link} in the order of the node array from index 1, link = left child's index << 10 |
+// byte offset of the feature; one step is i <- left + !(x[f] < t).  A leaf is a node that
+// goes right to itself (its left is its own index - 1, its t a NaN), with the class in the
+// NaN's low bits, so finished chains need no test of their own.  A tree of n nodes takes 8 n
+// bytes and a record exactly its leaf's depth of steps, where windows pad every path to
+// whole windows and end each with an exit: 100 random trees of 255 nodes, 300,001 records,
+// 255 us with one-node windows (the smallest tables).  The chains are bound by LDS latency
+// and stop, every kListCheck steps, when no lane of the wavefront moves any more.
+// `root[i]` is node 1, wavefront-uniform; depth[i] the longest path.  code: ~class.
+constexpr int kListCheck = 4;
+
+template <int K>
+__device__ __forceinline__ void walk_list_k(const char *const (&base)[K], const Slot (&root)[K],
+                                            const int (&depth)[K], const float *row,
+                                            int32_t (&code)[K]) {
+    int p[K];
+    int steps = 0;
+#pragma unroll
+    for (int i = 0; i < K; ++i) steps = depth[i] > steps ? depth[i] : steps;
+    float xr[K];
+#pragma unroll
+    for (int i = 0; i < K; ++i)
+        xr[i] = row[int(uint32_t(root[i].f) & kListFeatureMask) * (kTileRows / 4)];
+#pragma unroll
+    for (int i = 0; i < K; ++i) {
+        const bool right = !(xr[i] < root[i].t);
+        p[i] = int(uint32_t(root[i].f) >> 10) + int(right);
+    }
+    // one step of all K chains (reads grouped as in walk_data_k); q: the nodes reached
+    auto step = [&](int (&q)[K]) {
+        Slot s[K];
+        float xv[K];
+#pragma unroll
+        for (int i = 0; i < K; ++i) s[i] = reinterpret_cast<const Slot *>(base[i])[p[i]];
+#pragma unroll
+        for (int i = 0; i < K; ++i)
+            xv[i] = row[int(uint32_t(s[i].f) & kListFeatureMask) * (kTileRows / 4)];
+#pragma unroll
+        for (int i = 0; i < K; ++i) q[i] = int(uint32_t(s[i].f) >> 10) + int(!(xv[i] < s[i].t));
+    };
+    int k = 1;
+    for (; k + kListCheck <= steps; k += kListCheck) {
+#pragma unroll
+        for (int j = 0; j < kListCheck - 1; ++j) step(p);
+        int q[K];
+        step(q);
+        bool moved = false;
+#pragma unroll
+        for (int i = 0; i < K; ++i) {
+            moved = moved || q[i] != p[i];
+            p[i] = q[i];
+        }
+        if (!__any(moved)) {
+            k = steps;
+            break;
+        }
+    }
+    for (; k < steps; ++k) step(p);
+#pragma unroll
+    for (int i = 0; i < K; ++i)
+        code[i] = ~(__float_as_int(reinterpret_cast<const Slot *>(base[i])[p[i]].t) & 0xFF);
 }
 
 // ---- speculative decomposition: a tile of 64 records through one tree -------------------

@@ -22,7 +22,6 @@ namespace {
 using dtree::align16;
 using dtree::exact_rows;
 using dtree::load_mode_for;
-using dtree::make_rows;
 using dtree::make_tile_rows;
 using dtree::tile_shape;
 
@@ -35,12 +34,6 @@ dt_status fail(dt_status s, const std::string &msg) {
 
 dt_status hip_fail(hipError_t e, const char *what) {
     return fail(DT_ERR_HIP, std::string(what) + ": " + hipGetErrorString(e));
-}
-
-int row_stride_for(int32_t n_features) {
-    int rs = 4;
-    while (rs < n_features) rs <<= 1;
-    return rs;
 }
 
 // Device resources of one window encoding: the exits, and the slots once per record
@@ -317,7 +310,6 @@ struct dt_tree {
     DeviceCaps caps;
     dtree::TreeShape shape;
     int32_t n_features = 0, n_classes = 0;
-    int row_stride = 0;
     int path_hops = kDefaultPathHops;
     Encoding enc[2];              // data windows, speculative windows (also the path kernel's)
     // [algo][record element type][load mode][uint8 / int32 results]
@@ -333,10 +325,10 @@ static bool single_tree_algo(dt_algo algo) {
 
 namespace {
 
-// Device resources of a forest for one decomposition: all trees' window tables back to
-// back (tree k: slots then class exits, each padded to 16 bytes), the per-tree
-// descriptors {byte_off, slot_bytes, levels, 0} and the LDS chunks
-// {first_tree, end_tree, byte_off, bytes}.
+// Device resources of a forest for one decomposition: all trees' tables back to back (tree
+// k: window slots, then class exits where they are a table, each padded to 16 bytes; or the
+// node list), the per-tree descriptors {byte_off, slot_bytes, levels, 0} and the LDS chunks
+// {first_tree, end_tree, byte_off, bytes} of every launch plan.
 struct ForestEncoding {
     int32_t depth = 0;
     void *d_mem = nullptr;
@@ -344,14 +336,27 @@ struct ForestEncoding {
     const int2 *d_roots = nullptr;
     std::vector<int4> trees;     // host copy of the descriptors
     std::vector<int2> roots;     // per tree: slot 1 of window 0 {threshold bits, feature bytes}
-    std::vector<int4> chunks;    // host copy of the chunks
+    std::vector<int4> chunks;    // host copy of the chunks, plan after plan
     int64_t table_bytes = 0;
     int64_t max_tree_bytes = 0;
-    int32_t chunk_lds_bytes = 0; // LDS reserved for one chunk (0: tables read in place)
-    int32_t waves = 0;           // wavefronts per workgroup (one tile each)
-    int exit_mode = 0;           // exit codes: int32 table (0), int16 table (1), or packed
-                                 // into the windows' bottom slots (2)
+    int32_t max_levels = 0;      // most steps of a path: window levels x depth, or the depth
+    int exit_mode = dtree::kExitInt32;
 };
+
+// Launch plan of a forest for one load mode and split.
+struct ForestPlan {
+    const void *fn = nullptr;
+    dtree::TileShape tile;
+    int waves = 0, tiles = 0;    // wavefronts per workgroup, tiles they share
+    int blocks_per_cu = 0;
+    int lds_bytes = 0;
+    int chunk_lds_bytes = 0;     // LDS reserved for one chunk (0: tables read in place)
+    int first_chunk = 0, n_chunks = 0;
+    dt_status status = DT_ERR_UNSUPPORTED;
+    std::string why = "no kernel instance for this configuration";
+};
+
+constexpr int kForestSplits = 5;   // 1, 2, 4, 8 or 16 wavefronts per tile
 
 void free_forest_encoding(ForestEncoding *e) {
     if (e->d_mem) (void)hipFree(e->d_mem);
@@ -363,21 +368,12 @@ void free_forest_encoding(ForestEncoding *e) {
 struct dt_forest {
     DeviceCaps caps;
     int32_t n_trees = 0, n_features = 0, n_classes = 0;
-    int row_stride = 0;
     int vote_words = 0;
     ForestEncoding enc[2];       // [DT_ALGO_DATA], [DT_ALGO_SPECULATIVE]
-    Plan plan[2][dtree::kForestLoadModes];  // [algo][load mode]
+    ForestPlan plan[2][dtree::kForestLoadModes][kForestSplits];   // [algo][load mode][log2 split]
 };
 
 namespace {
-
-// The fastest record-tile load path of the forest kernels.
-int forest_load_mode_for(const void *d_x, int64_t ld, int32_t n_features, int row_stride) {
-    const bool dense = ld == n_features && n_features % 4 == 0 &&
-                       (reinterpret_cast<uintptr_t>(d_x) & 15u) == 0;
-    if (!dense) return dtree::kLoadScalar;
-    return n_features == row_stride ? dtree::kLoadExact : dtree::kLoadVec;
-}
 
 bool valid_elem_type(dt_dtype t) {
     return t == DT_F32 || t == DT_F16 || t == DT_BF16 || t == DT_U8;
@@ -453,7 +449,6 @@ dt_status create_impl(const dt_node *nodes, int32_t n_nodes, int32_t n_features,
     t->shape = shape;
     t->n_features = n_features;
     t->n_classes = n_classes;
-    t->row_stride = row_stride_for(n_features);
     if (opt && opt->path_hops) t->path_hops = opt->path_hops;
     int depth[2];
     window_depths(nodes, shape, n_features, opt, &depth[0], &depth[1]);
@@ -473,7 +468,7 @@ dt_status create_impl(const dt_node *nodes, int32_t n_nodes, int32_t n_features,
         for (int xt = 0; xt < dtree::kElemTypes; ++xt) {
             for (int m = 0; m < dtree::kLoadModes; ++m) {
                 Plan *pl = t->plan[algo][xt][m];
-                if (t->row_stride > dtree::kMaxRowStride) {
+                if (n_features > dtree::kMaxRowStride) {
                     pl[0].why = pl[1].why = "n_features > 256";
                     continue;
                 }
@@ -539,8 +534,10 @@ void encode_forest(const dt_node *nodes, const int32_t *offsets, int32_t n_trees
             fits16 = fits16 && c >= INT16_MIN && c <= INT16_MAX;
         }
     }
-    enc->exit_mode = fits11 ? 2 : fits16 ? 1 : 0;
-    const int64_t exit_size = enc->exit_mode == 2 ? 0 : enc->exit_mode == 1 ? 2 : 4;
+    enc->exit_mode = fits11 ? dtree::kExitPacked : fits16 ? dtree::kExitInt16 : dtree::kExitInt32;
+    const int64_t exit_size = enc->exit_mode == dtree::kExitPacked  ? 0
+                              : enc->exit_mode == dtree::kExitInt16 ? 2
+                                                                    : 4;
     for (int32_t k = 0; k < n_trees; ++k) {
         const dtree::WindowTables &wt = wts[size_t(k)];
         const int64_t n_slots = int64_t(wt.n_windows) * wt.slots;
@@ -552,7 +549,7 @@ void encode_forest(const dt_node *nodes, const int32_t *offsets, int32_t n_trees
         for (int64_t i = 0; i < n_slots; ++i) {
             int32_t fb = 4 * wt.feature[size_t(i)];   // byte offset in an fp32 row
             const int64_t q = i % S;                  // heap position in the window
-            if (enc->exit_mode == 2 && q >= S / 2) {  // bottom level: its children's exits
+            if (enc->exit_mode == dtree::kExitPacked && q >= S / 2) {  // bottom level: its children's exits
                 const int64_t e = i - q + 2 * q - S;  // exit of child 2q in this window
                 const uint32_t lo = uint32_t(wt.exit_class[size_t(e)]) & 0x7FFu;
                 const uint32_t hi = uint32_t(wt.exit_class[size_t(e + 1)]) & 0x7FFu;
@@ -561,12 +558,12 @@ void encode_forest(const dt_node *nodes, const int32_t *offsets, int32_t n_trees
             std::memcpy(p + 8 * i, &wt.threshold[size_t(i)], 4);
             std::memcpy(p + 8 * i + 4, &fb, 4);
         }
-        if (enc->exit_mode == 1) {
+        if (enc->exit_mode == dtree::kExitInt16) {
             for (int64_t i = 0; i < n_slots; ++i) {
                 const int16_t c = int16_t(wt.exit_class[size_t(i)]);
                 std::memcpy(p + sb + 2 * i, &c, 2);
             }
-        } else if (enc->exit_mode == 0) {
+        } else if (enc->exit_mode == dtree::kExitInt32) {
             std::memcpy(p + sb, wt.exit_class.data(), size_t(n_slots * 4));
         }
         enc->trees[size_t(k)] = int4{int(off), int(sb), wt.levels, 0};
@@ -574,28 +571,67 @@ void encode_forest(const dt_node *nodes, const int32_t *offsets, int32_t n_trees
         std::memcpy(&root, p + 8, 8);
         enc->roots[size_t(k)] = root;
         enc->max_tree_bytes = std::max(enc->max_tree_bytes, sb + eb);
+        enc->max_levels = std::max(enc->max_levels, wt.levels * depth);
     }
     enc->table_bytes = int64_t(bytes->size());
 }
+
+// Every tree as a node list (see walk_list_k): node i of the array is list entry i + 1.
+void list_forest(const dt_node *nodes, const int32_t *offsets, int32_t n_trees,
+                 const std::vector<dtree::TreeShape> &shapes, std::vector<unsigned char> *bytes,
+                 ForestEncoding *enc) {
+    enc->depth = 0;
+    enc->exit_mode = dtree::kExitList;
+    for (int32_t k = 0; k < n_trees; ++k) {
+        const dt_node *t = nodes + offsets[k];
+        const int32_t n = offsets[k + 1] - offsets[k];
+        const int64_t off = int64_t(bytes->size()), size = align16((int64_t(n) + 1) * 8);
+        bytes->resize(size_t(off + size), 0);
+        unsigned char *p = bytes->data() + off;
+        for (int32_t i = 0; i < n; ++i) {
+            uint32_t w[2];
+            if (t[i].cls < 0) {
+                std::memcpy(&w[0], &t[i].threshold, 4);
+                w[1] = uint32_t(t[i].left + 1) << 10 | uint32_t(4 * t[i].feature);
+            } else {
+                w[0] = 0x7FC00000u | uint32_t(t[i].cls);
+                w[1] = uint32_t(i) << 10;
+            }
+            std::memcpy(p + 8 * (int64_t(i) + 1), w, 8);
+        }
+        const int32_t depth = shapes[size_t(k)].depth;
+        enc->trees.push_back(int4{int(off), int(size), depth, 0});
+        int2 root{0, 0};
+        std::memcpy(&root, p + 8, 8);
+        enc->roots.push_back(root);
+        enc->max_tree_bytes = std::max(enc->max_tree_bytes, size);
+        enc->max_levels = std::max(enc->max_levels, depth);
+    }
+    enc->table_bytes = int64_t(bytes->size());
+}
+
+// Node lists hold left indices of 22 bits.
+constexpr int32_t kMaxListNodes = (1 << 22) - 2;
 
 // Wavefronts per CU the forest kernel aims for by default (measured: 16 beat 8 by 5% on a
 // 32-tree forest; more gained nothing).
 constexpr int kForestWavesPerCu = 16;
 
-// Choose the workgroup shape and the LDS chunks of consecutive trees.
-void chunk_forest(const DeviceCaps &caps, int algo, int row_stride, int waves_per_cu,
-                  ForestEncoding *enc) {
-    const int64_t tile_bytes = dtree::tile_bytes_for(row_stride, dtree::kXF32);
+// Workgroup shape and LDS chunks of consecutive trees for a forest whose tiles take
+// `tile_bytes` each, 2^split wavefronts to a tile.
+void chunk_forest(const DeviceCaps &caps, int algo, int waves_per_cu, int split, int64_t tile_bytes,
+                  ForestEncoding *enc, ForestPlan *plan) {
     const int target = waves_per_cu > 0 ? waves_per_cu : kForestWavesPerCu;
-    enc->chunks.clear();
-    // Workgroup shape: the most resident wavefronts up to the target whose tiles leave a
-    // chunk buffer that holds the largest tree; ties: larger chunk buffers (fewer passes).
+    plan->first_chunk = int(enc->chunks.size());
+    plan->chunk_lds_bytes = 0;
+    // The most resident wavefronts up to the target whose tiles leave a chunk buffer that
+    // holds the largest tree; ties: larger chunk buffers (fewer passes).
     int best_w = 0, best_score = 0;
     int64_t best_budget = 0;
     for (int bpc = 1; bpc <= 4; ++bpc) {
         const int64_t per_block = std::min<int64_t>(caps.lds_per_block, caps.lds_per_cu / bpc);
-        for (int w = dtree::forest_max_waves(algo, enc->depth, row_stride); w >= 1; --w) {
-            const int64_t budget = per_block - w * tile_bytes;
+        for (int w = dtree::forest_max_waves(algo, enc->depth); w >= 1 << split; --w) {
+            const int64_t budget = per_block - (w >> split) * tile_bytes;
             if (budget < enc->max_tree_bytes) continue;
             const int score = std::min(target, w * bpc);
             if (score > best_score || (score == best_score && budget > best_budget)) {
@@ -605,36 +641,33 @@ void chunk_forest(const DeviceCaps &caps, int algo, int row_stride, int waves_pe
             }
         }
     }
-    if (best_w > 0) {
-        const int w = best_w;
-        const int64_t budget = best_budget;
-        enc->waves = w;
-        int32_t first = 0;
-        int64_t max_chunk = 0;
-        while (first < int32_t(enc->trees.size())) {
-            int32_t end = first;
-            int64_t bytes = 0;
-            while (end < int32_t(enc->trees.size())) {
-                const int64_t off = enc->trees[size_t(end)].x;
-                const int64_t next = end + 1 < int32_t(enc->trees.size())
-                                         ? int64_t(enc->trees[size_t(end + 1)].x)
-                                         : enc->table_bytes;
-                if (bytes + (next - off) > budget) break;
-                bytes += next - off;
-                ++end;
-            }
-            const int32_t off0 = enc->trees[size_t(first)].x;
-            enc->chunks.push_back(int4{first, end, off0, int(bytes)});
-            max_chunk = std::max(max_chunk, bytes);
-            first = end;
-        }
-        enc->chunk_lds_bytes = int32_t(max_chunk);
+    plan->waves = best_w;
+    if (best_w == 0) {   // single trees too large for the LDS: one pass, tables read in place
+        enc->chunks.push_back(int4{0, int(enc->trees.size()), 0, int(enc->table_bytes)});
+        plan->n_chunks = 1;
         return;
     }
-    // single trees too large for the LDS: one pass reading the tables in place
-    enc->waves = 0;
-    enc->chunk_lds_bytes = 0;
-    enc->chunks.push_back(int4{0, int(enc->trees.size()), 0, int(enc->table_bytes)});
+    int32_t first = 0;
+    int64_t max_chunk = 0;
+    while (first < int32_t(enc->trees.size())) {
+        int32_t end = first;
+        int64_t bytes = 0;
+        while (end < int32_t(enc->trees.size())) {
+            const int64_t off = enc->trees[size_t(end)].x;
+            const int64_t next = end + 1 < int32_t(enc->trees.size())
+                                     ? int64_t(enc->trees[size_t(end + 1)].x)
+                                     : enc->table_bytes;
+            if (bytes + (next - off) > best_budget) break;
+            bytes += next - off;
+            ++end;
+        }
+        const int32_t off0 = enc->trees[size_t(first)].x;
+        enc->chunks.push_back(int4{first, end, off0, int(bytes)});
+        max_chunk = std::max(max_chunk, bytes);
+        first = end;
+    }
+    plan->chunk_lds_bytes = int32_t(max_chunk);
+    plan->n_chunks = int(enc->chunks.size()) - plan->first_chunk;
 }
 
 dt_status upload_forest(const std::vector<unsigned char> &bytes, ForestEncoding *enc) {
@@ -662,11 +695,23 @@ dt_status upload_forest(const std::vector<unsigned char> &bytes, ForestEncoding 
     return DT_OK;
 }
 
-dt_status plan_forest(const DeviceCaps &caps, int algo, int row_stride, int load_mode,
-                      int vote_words, const ForestEncoding &enc, Plan *plan) {
-    const bool tab_lds = enc.chunk_lds_bytes > 0;
-    plan->fn = dtree::forest_kernel_for(algo, row_stride, load_mode, tab_lds, vote_words,
-                                        enc.depth, enc.exit_mode);
+dt_status plan_forest(const DeviceCaps &caps, int algo, int n_features, int load_mode, int split,
+                      int vote_words, int waves_per_cu, ForestEncoding *enc, ForestPlan *plan) {
+    dtree::ForestShape s;
+    s.algo = algo;
+    s.vote_words = vote_words;
+    s.depth = enc->depth;
+    s.exit_mode = enc->exit_mode;
+    s.split = split;
+    s.tile = dtree::forest_tile_shape(algo, n_features, load_mode, split == 0);
+    // a split kernel's tiles each have a box of votes beside them
+    const int64_t vote_bytes = split ? int64_t(vote_words) * 256 : 0;
+    chunk_forest(caps, algo, waves_per_cu, split, s.tile.tile_bytes + vote_bytes, enc, plan);
+    s.tables_in_lds = plan->chunk_lds_bytes > 0;
+    if (!s.tables_in_lds && s.tile.mode == dtree::kLoadExact) s.tile.mode = dtree::kLoadRows;
+    if (!s.tables_in_lds) s.tile = dtree::forest_tile_shape(algo, n_features, s.tile.mode, false);
+    plan->tile = s.tile;
+    plan->fn = dtree::forest_kernel_for(s);
     if (!plan->fn) {
         plan->why = "no forest kernel instance for this configuration";
         return plan->status = DT_ERR_UNSUPPORTED;
@@ -683,11 +728,12 @@ dt_status plan_forest(const DeviceCaps &caps, int algo, int row_stride, int load
         }
     }
     int best_waves = 0;
-    for (int w = 1; w <= dtree::forest_max_waves(algo, enc.depth, row_stride); ++w) {
-        if (tab_lds && w != enc.waves) continue;     // the chunks were cut for enc.waves
-        const int lds = dtree::lds_bytes_for(enc.chunk_lds_bytes,
-                                             dtree::tile_bytes_for(row_stride, dtree::kXF32), w);
-        if (lds > caps.lds_per_block) break;
+    const int planned = plan->waves;
+    for (int w = dtree::forest_max_waves(algo, enc->depth); w >= 1 << split; --w) {
+        if (s.tables_in_lds && w != planned) continue;   // the chunks were cut for these
+        const int tiles = w >> split;
+        const int lds = int(plan->chunk_lds_bytes + tiles * (s.tile.tile_bytes + vote_bytes));
+        if (lds > caps.lds_per_block) continue;
         int nb = 0;
         hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, plan->fn, w * 64,
                                                                     size_t(lds));
@@ -696,9 +742,10 @@ dt_status plan_forest(const DeviceCaps &caps, int algo, int row_stride, int load
                         hipGetErrorString(e);
             return plan->status = DT_ERR_HIP;
         }
-        if (nb >= 1 && nb * w >= best_waves) {
+        if (nb >= 1 && nb * w > best_waves) {
             best_waves = nb * w;
             plan->waves = w;
+            plan->tiles = tiles;
             plan->blocks_per_cu = nb;
             plan->lds_bytes = lds;
         }
@@ -709,6 +756,65 @@ dt_status plan_forest(const DeviceCaps &caps, int algo, int row_stride, int load
     }
     plan->why.clear();
     return plan->status = DT_OK;
+}
+
+// Estimated time, in LDS cycles of a CU, of one round of groups (every resident workgroup
+// walks its tiles through all trees): each walk of 64 records through a tree takes about 8
+// cycles of the CU's LDS per step, each byte of tables copied 1/64 cycle, each chunk its
+// barriers, each group its staging.
+double round_cost(const ForestEncoding &enc, const ForestPlan &p) {
+    const double trees = double(enc.trees.size());
+    const double walk = trees * 8.0 * std::max(1, std::min(enc.max_levels, 16));
+    const bool resident = p.chunk_lds_bytes > 0 && p.n_chunks == 1;
+    const double tables = resident ? 0.0 : double(enc.table_bytes) / 64.0 + 800.0 * p.n_chunks;
+    // unsplit kernels prefetch the next tiles; split ones wait for theirs
+    const double wait = p.tile.vecs > 0 || p.tile.mode == dtree::kLoadExact ? 1500.0 : 7000.0;
+    return p.blocks_per_cu * (p.tiles * (walk + p.tile.tile_bytes / 64.0) + tables) + wait;
+}
+
+// How a call's tiles are spread: the first `lead` by the unsplit kernel, the rest by the
+// kernel of 2^split wavefronts per tile (split 0: none of them).
+struct ForestSpread {
+    int64_t lead = 0;
+    int split = 0;
+};
+
+// The unsplit kernel walks a tile per wavefront and is the most efficient with every
+// workgroup busy; what it does badly is a round that few workgroups have part in (one
+// group of 16 tiles more than there are CUs takes two rounds) and inputs of fewer tiles
+// than wavefronts.  Weighed here: all tiles by one of the kernels, or the full rounds by the
+// unsplit one and the rest by a split one (a second launch).
+ForestSpread spread_forest(const ForestEncoding &enc,
+                           const ForestPlan *const (&plan)[kForestSplits], int n_cu,
+                           int64_t tiles) {
+    ForestSpread best;
+    best.lead = tiles;          // where no plan holds, the unsplit one says why
+    double best_cost = -1.0;
+    constexpr double kLaunch = 8000.0;   // a second launch: about 3 us
+    const auto rounds = [&](const ForestPlan &p, int64_t t) {
+        const int64_t groups = (t + p.tiles - 1) / p.tiles, slots = int64_t(p.blocks_per_cu) * n_cu;
+        return double((groups + slots - 1) / slots) * round_cost(enc, p);
+    };
+    const auto weigh = [&](double cost, int64_t lead, int split) {
+        if (best_cost >= 0.0 && cost >= best_cost) return;
+        best_cost = cost;
+        best.lead = lead;
+        best.split = split;
+    };
+    const ForestPlan &whole = *plan[0];
+    int64_t full = 0;
+    if (whole.status == DT_OK) {
+        weigh(rounds(whole, tiles), tiles, 0);
+        const int64_t per_round = int64_t(whole.tiles) * whole.blocks_per_cu * n_cu;
+        full = tiles / per_round * per_round;
+    }
+    for (int s = 1; s < kForestSplits; ++s) {
+        if (plan[s]->status != DT_OK) continue;
+        weigh(rounds(*plan[s], tiles), 0, s);
+        if (full > 0 && full < tiles)
+            weigh(rounds(whole, full) + rounds(*plan[s], tiles - full) + kLaunch, full, s);
+    }
+    return best;
 }
 
 void forest_destroy_impl(dt_forest *f) {
@@ -754,13 +860,15 @@ dt_status forest_create_impl(const dt_node *nodes, const int32_t *offsets, int32
     f->n_trees = n_trees;
     f->n_features = n_features;
     f->n_classes = n_classes;
-    f->row_stride = row_stride_for(n_features);
     f->vote_words = vote_words_for(n_classes);
 
-    // data windows: the depth that makes the forest's tables smallest
+    // data windows: the depth that makes the forest's tables smallest; where no depth has
+    // every tree in one window, or the windows' slots take more than the nodes, node lists
     int data_d = opt && opt->data_window_depth ? opt->data_window_depth : 0;
+    bool list = false;
     if (!data_d) {
-        int64_t best = -1;
+        int64_t best = -1, list_bytes = 0;
+        bool listable = true;
         for (int d = 1; d <= std::min(dtree::kMaxWindowDepth, std::max(1, max_depth)); ++d) {
             int64_t total = 0;
             for (int32_t k = 0; k < n_trees; ++k)
@@ -768,33 +876,43 @@ dt_status forest_create_impl(const dt_node *nodes, const int32_t *offsets, int32
                     dtree::count_windows(nodes + offsets[k], shapes[size_t(k)], d), d);
             if (best < 0 || total <= best) { best = total; data_d = d; }
         }
+        for (int32_t k = 0; k < n_trees; ++k) {
+            list_bytes += 8 * (int64_t(offsets[k + 1] - offsets[k]) + 1);
+            listable = listable && offsets[k + 1] - offsets[k] <= kMaxListNodes;
+        }
+        list = listable && (max_depth > data_d || best / 12 * 8 > list_bytes);
     }
     const int spec_d = opt && opt->spec_window_depth ? opt->spec_window_depth : kForestSpecDepth;
     const int depth[2] = {data_d, spec_d};
     for (int algo = 0; algo < 2; ++algo) {
+        ForestEncoding *enc = &f->enc[algo];
         std::vector<unsigned char> bytes;
-        encode_forest(nodes, offsets, n_trees, shapes, algo, depth[algo], &bytes, &f->enc[algo]);
-        if (f->row_stride <= dtree::kMaxRowStride)
-            chunk_forest(f->caps, algo, f->row_stride, opt ? opt->waves_per_cu : 0,
-                         &f->enc[algo]);
+        if (list && algo == DT_ALGO_DATA)
+            list_forest(nodes, offsets, n_trees, shapes, &bytes, enc);
         else
-            f->enc[algo].chunks.push_back(int4{0, n_trees, 0, int(f->enc[algo].table_bytes)});
-        if (f->enc[algo].table_bytes > (int64_t(1) << 31) - 1) {
+            encode_forest(nodes, offsets, n_trees, shapes, algo, depth[algo], &bytes, enc);
+        if (enc->table_bytes > (int64_t(1) << 31) - 1) {
             forest_destroy_impl(f);
             return fail(DT_ERR_UNSUPPORTED, "forest tables exceed 2 GiB");
         }
-        st = upload_forest(bytes, &f->enc[algo]);
-        if (st != DT_OK) { forest_destroy_impl(f); return st; }
         for (int m = 0; m < dtree::kForestLoadModes; ++m) {
-            if (f->row_stride > dtree::kMaxRowStride) {
-                f->plan[algo][m].why = "n_features > 256";
-                continue;
+            for (int sp = 0; sp < kForestSplits; ++sp) {
+                ForestPlan *p = &f->plan[algo][m][sp];
+                if (n_features > dtree::kMaxRowStride) {
+                    p->why = "n_features > 256";
+                    continue;
+                }
+                if (m == dtree::kLoadExact &&
+                    (!dtree::exact_rows(n_features, 4) || n_features > 32 || sp > 0))
+                    continue;
+                if (m == dtree::kLoadFlat && n_features % 4 == 0) continue;
+                if ((1 << sp) > dtree::forest_max_waves(algo, enc->depth)) continue;
+                plan_forest(f->caps, algo, n_features, m, sp, f->vote_words,
+                            opt ? opt->waves_per_cu : 0, enc, p);
             }
-            if (m == dtree::kLoadExact && n_features != f->row_stride) continue;
-            if (m != dtree::kLoadScalar && n_features % 4 != 0) continue;
-            plan_forest(f->caps, algo, f->row_stride, m, f->vote_words, f->enc[algo],
-                        &f->plan[algo][m]);
         }
+        st = upload_forest(bytes, enc);
+        if (st != DT_OK) { forest_destroy_impl(f); return st; }
     }
     *out = f;
     return DT_OK;
@@ -821,30 +939,46 @@ dt_status forest_classify_impl(const dt_forest *f, const float *d_x, int64_t n, 
     if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
     if (dev != f->caps.device)
         return fail(DT_ERR_INVALID_ARG, "current device differs from the forest's device");
-    const Plan &plan =
-        f->plan[algo][forest_load_mode_for(d_x, ld, f->n_features, f->row_stride)];
-    if (plan.status != DT_OK) return fail(plan.status, plan.why);
+    // a split kernel reads exact rows as any others of a multiple of 16 bytes
+    const int mode = dtree::forest_load_mode(d_x, ld, f->n_features);
+    const int split_mode = mode == dtree::kLoadExact ? int(dtree::kLoadRows) : mode;
+    const ForestPlan *plans[kForestSplits];
+    for (int sp = 0; sp < kForestSplits; ++sp)
+        plans[sp] = &f->plan[algo][sp == 0 ? mode : split_mode][sp];
     const ForestEncoding &enc = f->enc[algo];
+    const int64_t tiles = (n + dtree::kTileRows - 1) / dtree::kTileRows;
+    const ForestSpread spread = spread_forest(enc, plans, f->caps.n_cu, tiles);
 
-    dtree::FArgs a{};
-    a.in = make_rows(d_x, dtree::kXF32, n, ld, f->n_features);
-    a.tables = enc.d_tables;
-    a.trees = enc.d_trees;
-    a.roots = enc.d_roots;
-    a.chunks = enc.d_chunks;
-    a.n_trees = f->n_trees;
-    a.n_chunks = int32_t(enc.chunks.size());
-    a.table_lds_bytes = enc.chunk_lds_bytes;
-    a.depth = enc.depth;
-    a.n_classes = f->n_classes;
-    a.waves = plan.waves;
-    a.out_kind = out_kind == DT_OUT_CLASS_U8 ? 0 : 1;
-    a.out = d_out;
-    const int64_t groups = (a.in.n_tiles + plan.waves - 1) / plan.waves;
-    const int64_t resident = int64_t(plan.blocks_per_cu) * f->caps.n_cu;
-    const int blocks = int(std::max<int64_t>(1, std::min(groups, resident)));
-    e = dtree::launch_forest(plan.fn, a, blocks, plan.lds_bytes, static_cast<hipStream_t>(stream));
-    if (e != hipSuccess) return hip_fail(e, "forest kernel launch");
+    for (int part = 0; part < 2; ++part) {
+        const int64_t first = part == 0 ? 0 : spread.lead, end = part == 0 ? spread.lead : tiles;
+        if (first >= end) continue;
+        const int split = part == 0 ? 0 : spread.split;
+        const ForestPlan &plan = *plans[split];
+        if (plan.status != DT_OK) return fail(plan.status, plan.why);
+        dtree::FArgs a{};
+        a.in = make_tile_rows(d_x, dtree::kXF32, n, ld, f->n_features, plan.tile);
+        a.tables = enc.d_tables;
+        a.trees = enc.d_trees;
+        a.roots = enc.d_roots;
+        a.chunks = enc.d_chunks + plan.first_chunk;
+        a.first_tile = first;
+        a.end_tile = end;
+        a.n_chunks = plan.n_chunks;
+        a.table_lds_bytes = plan.chunk_lds_bytes;
+        a.tile_bytes = plan.tile.tile_bytes;
+        a.split = split;
+        a.depth = enc.depth;
+        a.n_classes = f->n_classes;
+        a.waves = plan.waves;
+        a.out_kind = out_kind == DT_OUT_CLASS_U8 ? 0 : 1;
+        a.out = d_out;
+        const int64_t groups = (end - first + plan.tiles - 1) / plan.tiles;
+        const int64_t resident = int64_t(plan.blocks_per_cu) * f->caps.n_cu;
+        const int blocks = int(std::max<int64_t>(1, std::min(groups, resident)));
+        e = dtree::launch_forest(plan.fn, a, blocks, plan.lds_bytes,
+                                 static_cast<hipStream_t>(stream));
+        if (e != hipSuccess) return hip_fail(e, "forest kernel launch");
+    }
     return DT_OK;
 }
 

@@ -1,19 +1,19 @@
-// gfx950 forest kernel: majority vote of many trees over every record (kernel template in
-// forest_impl.hpp).  This unit holds the instances for int32 exit codes and the launch.
+// gfx950 forest kernels: majority vote of many trees over every record (kernel templates in
+// forest_impl.hpp).  This unit holds the data walk's instances for int32 exit codes, the
+// choice among the units and the launch.
 #include "forest_impl.hpp"
 
 namespace dtree {
 
-const void *forest_kernel_for(int algo, int row_stride, int load_mode, bool tables_in_lds,
-                              int vote_words, int depth, int exit_mode) {
-    if (exit_mode == 2)
-        return forest_kernel_for_packed(algo, row_stride, load_mode, tables_in_lds, vote_words,
-                                        depth);
-    if (exit_mode == 1)
-        return forest_kernel_for_ex16(algo, row_stride, load_mode, tables_in_lds, vote_words,
-                                      depth);
-    return forest_kernel_for_ex<int32_t>(algo, row_stride, load_mode, tables_in_lds,
-                                         vote_words, depth);
+const void *forest_kernel_for(const ForestShape &s) {
+    if (s.algo != kAlgoData) return forest_spec_kernel(s);
+    switch (s.exit_mode) {
+        case kExitInt32: return forest_data_kernel<int32_t>(s);
+        case kExitInt16: return forest_ex16_kernel(s);
+        case kExitPacked: return forest_packed_kernel(s);
+        case kExitList: return forest_list_kernel(s);
+        default: return nullptr;
+    }
 }
 
 hipError_t launch_forest(const void *fn, const FArgs &args, int blocks, int lds_bytes,

@@ -1,5 +1,6 @@
-// gfx950 forest kernel template, instantiated for int32 exit codes in forest.hip and for
-// int16 ones in forest_ex16.hip (two translation units, compiled in parallel).
+// gfx950 forest kernel templates, instantiated per kind of exit codes (int32: forest.hip,
+// int16: forest_ex16.hip, packed: forest_packed.hip, node lists: forest_list.hip) and for
+// the speculative walk (forest_spec.hip): translation units compiled in parallel.
 //
 // Forests are evaluated tree after tree (the concatenated-trees scheme the paper cites
 // in Section 1) and the trees' classes are combined by majority vote, ties going to the
@@ -79,10 +80,37 @@ __device__ __forceinline__ int majority(const uint32_t (&votes)[NV], int n_class
     return best;
 }
 
+// The kernel arguments, for the code around the walk.  The walk needs every scalar register,
+// and the arguments of row tiles held across it spilled to vector lanes (a 32-tree forest
+// 457 us against 373 us): for them the arguments are read again, through a pointer the
+// compiler cannot see through, from the kernel-argument segment (scalar loads, three times
+// per group).  Exact tiles need few arguments and keep them (373 us against 380 us).
+template <class Tile>
+__device__ __forceinline__ const FArgs &cold_args(const FArgs &a) {
+    if constexpr (Tile::kFewArgs) {
+        return a;
+    } else {
+        typedef const __attribute__((address_space(4))) FArgs ConstArgs;
+        ConstArgs *p = (ConstArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+        asm volatile("" : "+s"(p));
+        return *(const FArgs *)p;
+    }
+}
+
+// Lane `v`; for row tiles so that the LDS addresses of a tile's vectors, the same for every
+// tile, are not kept in registers from group to group.
+template <class Tile>
+__device__ __forceinline__ int cold_lane(int v) {
+    if constexpr (!Tile::kFewArgs) asm volatile("" : "+v"(v));
+    return v;
+}
+
 // Trees walked together per lane by the data decomposition.
 constexpr int kIlp = 4;
 
-// The whole chunk buffer, copied by the workgroup.
+// The whole chunk buffer, copied by the workgroup.  (One word per thread at a time: more in
+// flight would take registers the prefetched tile needs.  The split kernel, which has none,
+// copies with dev::copy_to_lds.)
 __device__ __forceinline__ void copy_chunk(const FArgs &a, int4 *tab, const int4 &ch) {
     const int4 *src = a.tables + (ch.z >> 4);
     for (int i = threadIdx.x; i < (ch.w >> 4); i += blockDim.x) tab[i] = src[i];
@@ -117,38 +145,79 @@ __device__ __forceinline__ void copy_chunk_staged(const FArgs &a, int4 *tab, con
     }
 }
 
+// Votes of this lane's record for trees [k, end) of a chunk whose tables start at `cbase` and
+// at byte `cofs` of the forest's tables.  Data decomposition: `row` is the lane's record in a
+// column-major tile; kIlp trees at a time.
+template <class EX, int NV>
+__device__ __forceinline__ void vote_data(const FArgs &a, const char *cbase, int cofs, int k,
+                                          int end, const float *row, uint32_t (&votes)[NV]) {
+    // K trees of the chunk walked together from tree k0
+    auto walk_group = [&](auto kk, int k0) {
+        constexpr int K = decltype(kk)::value;
+        const char *base[K];
+        Slot root[K];
+        int sb[K], lv[K];
+        int32_t code[K];
+#pragma unroll
+        for (int i = 0; i < K; ++i) {
+            const int4 d = read_const(a.trees, k0 + i);   // {byte_off, slot_bytes, levels, 0}
+            root[i] = read_root(a.roots, k0 + i);
+            base[i] = cbase + (d.x - cofs);
+            sb[i] = d.y;
+            lv[i] = d.z;
+        }
+        // Both kinds of scalar loads complete here, before the walk: one wait
+        // for them all, instead of one for the roots and, after the root step,
+        // another for the descriptors (which the compiler would otherwise sink
+        // to their first use).
+#pragma unroll
+        for (int i = 0; i < K; ++i)
+            asm volatile("" ::"s"(base[i]), "s"(sb[i]), "s"(lv[i]), "s"(root[i].t),
+                         "s"(root[i].f));
+        if constexpr (std::is_same<EX, dev::NodeList>::value)
+            dev::walk_list_k<K>(base, root, lv, row, code);
+        else
+            dev::walk_data_k<K, kTileRows, EX>(base, root, sb, lv, a.depth, row, 0, code);
+#pragma unroll
+        for (int i = 0; i < K; ++i) add_vote(votes, ~code[i]);
+    };
+    for (; k + kIlp <= end; k += kIlp) walk_group(std::integral_constant<int, kIlp>(), k);
+    if (end - k == 3)
+        walk_group(std::integral_constant<int, 3>(), k);
+    else if (end - k == 2)
+        walk_group(std::integral_constant<int, 2>(), k);
+    else if (end - k == 1)
+        walk_group(std::integral_constant<int, 1>(), k);
+}
+
+// The same for the speculative decomposition (int32 exit codes), all 64 records of `tile`.
+template <class Tile, int NV, int SD>
+__device__ __forceinline__ void vote_spec(const FArgs &a, const char *cbase, int cofs, int k,
+                                          int end, const float *tile, int lane,
+                                          uint32_t (&votes)[NV]) {
+    for (; k < end; ++k) {
+        const int4 d = read_const(a.trees, k);   // {byte_off, slot_bytes, levels, 0}
+        const char *base = cbase + (d.x - cofs);
+        const Slot *sl = reinterpret_cast<const Slot *>(base);
+        const int32_t *ex = reinterpret_cast<const int32_t *>(base + d.y);
+        const dev::Spec<kXF32, SD, Tile> spec(lane);
+        const Slot root = sl[spec.j];
+        add_vote(votes, ~spec.run(sl, ex, d.z, root, a.in, tile));
+    }
+}
+
 // SD = 0: data decomposition; SD > 0: speculative decomposition with window depth SD.
 // EX: exit codes stored as int32, int16 where every code of the forest fits, or packed
-// into the windows' bottom slots (dev::PackedExits) where every code fits 11 bits.
-template <class EX, int RS, int LOAD, bool TAB_LDS, int NV, int SD>
-__global__ void __launch_bounds__(64 * forest_max_waves(SD == 0 ? 0 : 1, SD, RS)) forest_kernel(FArgs a) {
+// into the windows' bottom slots (dev::PackedExits) where every code fits 11 bits; or no
+// windows but node lists (dev::NodeList).  One wavefront per tile.
+template <class EX, class Tile, bool TAB_LDS, int NV, int SD>
+__global__ void __launch_bounds__(64 * forest_max_waves(SD == 0 ? 0 : 1, SD)) forest_kernel(FArgs a) {
     extern __shared__ int4 lds[];
-    // compute-bound: wide rows unprefetched; the speculative walk with vector loads keeps
-    // no prefetch either (its registers would not fit 16 wavefronts per CU)
-    constexpr bool kPrefetch = LOAD != kLoadScalar && RS <= 32 && !(SD > 0 && LOAD == kLoadVec);
+    constexpr bool kPrefetch = Tile::kPrefetch;
     const int wave = threadIdx.x >> 6;
     const int lane = threadIdx.x & 63;
-    float *tile = reinterpret_cast<float *>(lds) + wave * (kTileRows * RS);
-    int4 *tab = lds + (a.waves * kTileRows * RS) / 4;   // chunk buffer after the tiles
-    // The data decomposition reads each lane's own record: column-major tiles make every
-    // such read conflict-free.  The speculative one reads across a record: row-major.
-    constexpr int kLayout = SD == 0 ? dev::kColMajor : dev::kRowMajor;
-    constexpr int kStride = SD == 0 ? kTileRows : 1;
-    const float *row = SD == 0 ? tile + lane : tile + lane * RS;
-    const int sw = SD == 0 ? 0 : dev::swz<RS>(lane);
-    const int64_t n_groups = (a.in.n_tiles + a.waves - 1) / a.waves;
-
-    // Speculative decomposition: exit code of this lane's record for the tree whose tables
-    // start at `base` (int32 codes).
-    auto eval_tree = [&](const char *base, int levels, int slot_bytes) -> int32_t {
-        const Slot *sl = reinterpret_cast<const Slot *>(base);
-        const int32_t *ex = reinterpret_cast<const int32_t *>(base + slot_bytes);
-        using Spec = dev::Spec<kXF32, SD == 0 ? 2 : SD,
-                               dev::ExactTile<kXF32, RS, dev::kRowMajor, kTileRows>>;
-        const Spec spec(lane);
-        const Slot root = sl[spec.j];
-        return spec.run(sl, ex, levels, root, a.in, tile);
-    };
+    float *tile = reinterpret_cast<float *>(lds) + wave * (a.tile_bytes >> 2);
+    int4 *tab = lds + (a.waves * a.tile_bytes >> 4);    // chunk buffer after the tiles
 
     // A forest whose tables form one chunk is copied once: the tables then stay for every
     // group.  Otherwise the chunks are copied in turn for each group.
@@ -160,23 +229,27 @@ __global__ void __launch_bounds__(64 * forest_max_waves(SD == 0 ? 0 : 1, SD, RS)
     }
     const bool staged = a.table_lds_bytes <= kStage * 16 * int(blockDim.x);
 
-    // Full tiles are prefetched one group ahead; the partial last tile is staged directly.
-    const int64_t n_full = a.in.n / kTileRows;
+    // Tiles are prefetched one group ahead; the input's last ones are staged directly.
+    Tile buf;
+    auto prefetch = [&](int64_t t) {
+        if constexpr (kPrefetch) {
+            const FArgs &f = cold_args<Tile>(a);
+            if (t < f.end_tile && t < Tile::prefetch_end(f.in)) buf.load(f.in, t, cold_lane<Tile>(lane));
+        }
+    };
+    const int64_t n_groups = (a.end_tile + a.waves - 1) / a.waves;
     int64_t g = blockIdx.x;
-    dev::VecTile<(kPrefetch ? RS : 4), LOAD == kLoadExact> buf;
-    if constexpr (kPrefetch) {
-        const int64_t t0 = g * a.waves + wave;
-        if (g < n_groups && t0 < n_full) buf.load_full(a.in, t0, lane);
-    }
+    if (g < n_groups) prefetch(g * a.waves + wave);
     for (; g < n_groups; g += gridDim.x) {
-        const int64_t t = g * a.waves + wave;
-        const bool active = t < a.in.n_tiles;        // uniform per wavefront
+        const int64_t t = g * a.waves + wave;        // this wavefront's tile
+        const bool active = t < a.end_tile;          // uniform per wavefront
         dev::wave_sync();
         if (active) {
-            if (kPrefetch && t < n_full)
-                buf.template store<kLayout>(a.in, tile, lane);
+            const FArgs &f = cold_args<Tile>(a);
+            if (kPrefetch && t < Tile::prefetch_end(f.in))
+                buf.store(f.in, tile, cold_lane<Tile>(lane));
             else
-                dev::stage_now<kXF32, RS, LOAD, kLayout>(a.in, tile, t, lane);
+                Tile::stage(f.in, tile, t, cold_lane<Tile>(lane));
         }
         dev::wave_sync();
         // The next group's tiles are prefetched into registers: here, or, when the chunks
@@ -184,13 +257,7 @@ __global__ void __launch_bounds__(64 * forest_max_waves(SD == 0 ? 0 : 1, SD, RS)
         // otherwise queue behind the prefetch on the in-order vector-memory counter, and the
         // first chunk copy would wait for the prefetch to arrive from HBM).
         const bool prefetch_late = TAB_LDS && a.n_chunks > 1;
-        auto prefetch_next = [&]() {
-            if constexpr (kPrefetch) {
-                const int64_t tn = t + int64_t(gridDim.x) * a.waves;
-                if (tn < n_full) buf.load_full(a.in, tn, lane);
-            }
-        };
-        if (!prefetch_late) prefetch_next();
+        if (!prefetch_late) prefetch(t + int64_t(gridDim.x) * a.waves);
 
         uint32_t votes[NV];
 #pragma unroll
@@ -206,7 +273,7 @@ __global__ void __launch_bounds__(64 * forest_max_waves(SD == 0 ? 0 : 1, SD, RS)
                         copy_chunk(a, tab, ch);
                     }
                     __syncthreads();
-                    if (c == a.n_chunks - 1) prefetch_next();
+                    if (c == a.n_chunks - 1) prefetch(t + int64_t(gridDim.x) * a.waves);
                 }
             }
             if (!active) continue;
@@ -215,106 +282,165 @@ __global__ void __launch_bounds__(64 * forest_max_waves(SD == 0 ? 0 : 1, SD, RS)
             const char *cbase = TAB_LDS ? reinterpret_cast<const char *>(tab)
                                         : reinterpret_cast<const char *>(a.tables);
             const int cofs = TAB_LDS ? ch.z : 0;
-            int k = ch.x;
-            if constexpr (SD == 0) {
-                // K trees of the chunk walked together from tree k0
-                auto walk_group = [&](auto kk, int k0) {
-                    constexpr int K = decltype(kk)::value;
-                    const char *base[K];
-                    Slot root[K];
-                    int sb[K], lv[K];
-                    int32_t code[K];
-#pragma unroll
-                    for (int i = 0; i < K; ++i) {
-                        const int4 d = read_const(a.trees, k0 + i);   // {byte_off, slot_bytes, levels, 0}
-                        root[i] = read_root(a.roots, k0 + i);
-                        base[i] = cbase + (d.x - cofs);
-                        sb[i] = d.y;
-                        lv[i] = d.z;
-                    }
-                    // Both kinds of scalar loads complete here, before the walk: one wait
-                    // for them all, instead of one for the roots and, after the root step,
-                    // another for the descriptors (which the compiler would otherwise sink
-                    // to their first use).
-#pragma unroll
-                    for (int i = 0; i < K; ++i)
-                        asm volatile("" ::"s"(base[i]), "s"(sb[i]), "s"(lv[i]), "s"(root[i].t),
-                                     "s"(root[i].f));
-                    dev::walk_data_k<K, kStride, EX>(base, root, sb, lv, a.depth, row, sw, code);
-#pragma unroll
-                    for (int i = 0; i < K; ++i) add_vote(votes, ~code[i]);
-                };
-                for (; k + kIlp <= ch.y; k += kIlp) walk_group(std::integral_constant<int, kIlp>(), k);
-                if (ch.y - k == 3)
-                    walk_group(std::integral_constant<int, 3>(), k);
-                else if (ch.y - k == 2)
-                    walk_group(std::integral_constant<int, 2>(), k);
-                else if (ch.y - k == 1)
-                    walk_group(std::integral_constant<int, 1>(), k);
-            } else {
-                for (; k < ch.y; ++k) {
-                    const int4 d = read_const(a.trees, k);   // {byte_off, slot_bytes, levels, 0}
-                    add_vote(votes, ~eval_tree(cbase + (d.x - cofs), d.z, d.y));
-                }
-            }
+            if constexpr (SD == 0)
+                vote_data<EX>(a, cbase, cofs, ch.x, ch.y, tile + lane, votes);
+            else
+                vote_spec<Tile, NV, SD>(a, cbase, cofs, ch.x, ch.y, tile, lane, votes);
         }
-        if (active)
-            dev::store_value(a.out, a.out_kind, a.in.n, t * kTileRows + lane,
-                             majority(votes, a.n_classes));
+        if (active) {
+            const FArgs &f = cold_args<Tile>(a);
+            dev::store_value(f.out, f.out_kind, f.in.n, t * kTileRows + lane,
+                             majority(votes, f.n_classes));
+        }
     }
 }
 
-template <class EX, int RS, int LOAD, bool TAB_LDS, int NV>
-const void *for_votes(int algo, int depth) {
-    if (algo == kAlgoData)
-        return reinterpret_cast<const void *>(&forest_kernel<EX, RS, LOAD, TAB_LDS, NV, 0>);
-    if constexpr (std::is_same<EX, int32_t>::value) {   // narrower codes: data walk only
-        if (depth == 2)
-            return reinterpret_cast<const void *>(&forest_kernel<EX, RS, LOAD, TAB_LDS, NV, 2>);
-        if (depth == 4)
-            return reinterpret_cast<const void *>(&forest_kernel<EX, RS, LOAD, TAB_LDS, NV, 4>);
+// The same with 2^split wavefronts per tile, each walking a share of every chunk's trees:
+// for inputs whose tiles would leave wavefronts or CUs idle (few records, or the last,
+// partly filled round of groups), and for rows so wide that the LDS holds fewer tiles than
+// wavefronts.  The fewer tiles also leave the LDS larger chunks.  The wavefronts of a tile
+// stage it together and add their votes up in the LDS.
+template <class EX, class Tile, bool TAB_LDS, int NV, int SD>
+__global__ void __launch_bounds__(64 * forest_max_waves(SD == 0 ? 0 : 1, SD))
+forest_split_kernel(FArgs a) {
+    extern __shared__ int4 lds[];
+    const int wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63;
+    const int parts = 1 << a.split, part = wave & (parts - 1), slot = wave >> a.split;
+    const int tiles = a.waves >> a.split;               // tiles per group, >= 1
+    float *tile = reinterpret_cast<float *>(lds) + slot * (a.tile_bytes >> 2);
+    uint32_t *box = reinterpret_cast<uint32_t *>(lds + (tiles * a.tile_bytes >> 4)) +
+                    slot * (NV * 64) + lane;            // vote word r of this lane at box[64 r]
+    int4 *tab = lds + ((tiles * a.tile_bytes + tiles * NV * 256) >> 4);
+    const int64_t n_groups = (a.end_tile - a.first_tile + tiles - 1) / tiles;
+    const bool resident = TAB_LDS && a.n_chunks == 1;   // copied once, with the first group
+    for (int64_t g = blockIdx.x; g < n_groups; g += gridDim.x) {
+        const int64_t t = a.first_tile + g * tiles + slot;
+        const bool active = slot < tiles && t < a.end_tile;
+        if (active) {
+            Tile::stage(cold_args<Tile>(a).in, tile, t, cold_lane<Tile>(lane), part, parts);
+            if (part == 0)
+#pragma unroll
+                for (int r = 0; r < NV; ++r) box[64 * r] = 0u;
+        }
+        uint32_t votes[NV];
+#pragma unroll
+        for (int r = 0; r < NV; ++r) votes[r] = 0u;
+        for (int c = 0; c < a.n_chunks; ++c) {
+            const int4 ch = read_const(a.chunks, c);             // {first, end, byte_off, bytes}
+            if constexpr (TAB_LDS) {
+                if (c > 0) __syncthreads();              // previous chunk no longer read
+                if (!resident || g == int64_t(blockIdx.x))
+                    dev::copy_to_lds(tab, a.tables + (ch.z >> 4), ch.w >> 4);
+            }
+            if (TAB_LDS || c == 0) __syncthreads();      // chunk and (first) tiles visible
+            if (!active) continue;
+            const char *cbase = TAB_LDS ? reinterpret_cast<const char *>(tab)
+                                        : reinterpret_cast<const char *>(a.tables);
+            const int cofs = TAB_LDS ? ch.z : 0;
+            const int per = (ch.y - ch.x + parts - 1) >> a.split;
+            const int k = ch.x + part * per, end = k + per < ch.y ? k + per : ch.y;
+            if constexpr (SD == 0)
+                vote_data<EX>(a, cbase, cofs, k, end, tile + lane, votes);
+            else
+                vote_spec<Tile, NV, SD>(a, cbase, cofs, k, end, tile, lane, votes);
+        }
+        if (active)
+#pragma unroll
+            for (int r = 0; r < NV; ++r) atomicAdd(&box[64 * r], votes[r]);
+        __syncthreads();                                 // votes complete, tables and tiles free
+        if (active && part == 0) {
+#pragma unroll
+            for (int r = 0; r < NV; ++r) votes[r] = box[64 * r];
+            const FArgs &f = cold_args<Tile>(a);
+            dev::store_value(f.out, f.out_kind, f.in.n, t * kTileRows + lane,
+                             majority(votes, f.n_classes));
+        }
     }
+}
+
+// ---- instance tables ------------------------------------------------------------------
+template <class EX, class Tile, bool TAB_LDS, int NV, int SD>
+const void *kernel_of(bool split) {
+    if constexpr (!Tile::kPrefetch)
+        if (split) return reinterpret_cast<const void *>(&forest_split_kernel<EX, Tile, TAB_LDS, NV, SD>);
+    return split ? nullptr : reinterpret_cast<const void *>(&forest_kernel<EX, Tile, TAB_LDS, NV, SD>);
+}
+
+template <class EX, class Tile, bool TAB_LDS, int SD>
+const void *for_votes(bool split, int vote_words) {
+    switch (vote_words) {
+        case 2: return kernel_of<EX, Tile, TAB_LDS, 2, SD>(split);
+        case 4: return kernel_of<EX, Tile, TAB_LDS, 4, SD>(split);
+        case 16: return kernel_of<EX, Tile, TAB_LDS, 16, SD>(split);
+        default: return nullptr;
+    }
+}
+
+// Tables read in place: tiles without prefetch only.
+template <class EX, class Tile, int SD>
+const void *for_tables(bool split, bool tab_lds, int vote_words) {
+    if (tab_lds) return for_votes<EX, Tile, true, SD>(split, vote_words);
+    if constexpr (!Tile::kPrefetch) return for_votes<EX, Tile, false, SD>(split, vote_words);
     return nullptr;
 }
 
-template <class EX, int RS, int LOAD, bool TAB_LDS>
-const void *for_tab(int algo, int vote_words, int depth) {
-    switch (vote_words) {
-        case 2: return for_votes<EX, RS, LOAD, TAB_LDS, 2>(algo, depth);
-        case 4: return for_votes<EX, RS, LOAD, TAB_LDS, 4>(algo, depth);
-        case 16: return for_votes<EX, RS, LOAD, TAB_LDS, 16>(algo, depth);
+// The data decomposition reads each lane's own record: column-major tiles make every such
+// read conflict-free.
+template <class EX, bool FLAT>
+const void *col_tile(const ForestShape &s) {
+    switch (s.tile.vecs) {
+        case 0: return for_tables<EX, dev::ColTile<FLAT, 0>, 0>(s.split > 0, s.tables_in_lds, s.vote_words);
+        case 2: return for_tables<EX, dev::ColTile<FLAT, 2>, 0>(s.split > 0, s.tables_in_lds, s.vote_words);
+        case 4: return for_tables<EX, dev::ColTile<FLAT, 4>, 0>(s.split > 0, s.tables_in_lds, s.vote_words);
+        case 8: return for_tables<EX, dev::ColTile<FLAT, 8>, 0>(s.split > 0, s.tables_in_lds, s.vote_words);
         default: return nullptr;
     }
-}
-
-template <class EX, int RS, int LOAD>
-const void *for_load(int algo, bool tab_lds, int vote_words, int depth) {
-    return tab_lds ? for_tab<EX, RS, LOAD, true>(algo, vote_words, depth)
-                   : for_tab<EX, RS, LOAD, false>(algo, vote_words, depth);
 }
 
 template <class EX, int RS>
-const void *for_stride(int algo, int load_mode, bool tab_lds, int vote_words, int depth) {
-    switch (load_mode) {
-        case kLoadScalar: return for_load<EX, RS, kLoadScalar>(algo, tab_lds, vote_words, depth);
-        case kLoadVec: return for_load<EX, RS, kLoadVec>(algo, tab_lds, vote_words, depth);
-        case kLoadExact: return for_load<EX, RS, kLoadExact>(algo, tab_lds, vote_words, depth);
+const void *col_exact(const ForestShape &s) {
+    return for_tables<EX, dev::ExactTile<kXF32, RS, dev::kColMajor, kTileRows>, 0>(
+        s.split > 0, s.tables_in_lds, s.vote_words);
+}
+
+// Kernel instance of the data decomposition for exit codes of type EX.
+template <class EX>
+const void *forest_data_kernel(const ForestShape &s) {
+    if (s.tile.mode == kLoadFlat) return col_tile<EX, true>(s);
+    if (s.tile.mode == kLoadRows) return col_tile<EX, false>(s);
+    switch (s.tile.row_stride) {
+        case 4: return col_exact<EX, 4>(s);
+        case 8: return col_exact<EX, 8>(s);
+        case 16: return col_exact<EX, 16>(s);
+        case 32: return col_exact<EX, 32>(s);
         default: return nullptr;
     }
 }
 
-// Kernel instance for exit codes of type EX.
-template <class EX>
-const void *forest_kernel_for_ex(int algo, int row_stride, int load_mode, bool tables_in_lds,
-                                 int vote_words, int depth) {
-    switch (row_stride) {
-        case 4: return for_stride<EX, 4>(algo, load_mode, tables_in_lds, vote_words, depth);
-        case 8: return for_stride<EX, 8>(algo, load_mode, tables_in_lds, vote_words, depth);
-        case 16: return for_stride<EX, 16>(algo, load_mode, tables_in_lds, vote_words, depth);
-        case 32: return for_stride<EX, 32>(algo, load_mode, tables_in_lds, vote_words, depth);
-        case 64: return for_stride<EX, 64>(algo, load_mode, tables_in_lds, vote_words, depth);
-        case 128: return for_stride<EX, 128>(algo, load_mode, tables_in_lds, vote_words, depth);
-        case 256: return for_stride<EX, 256>(algo, load_mode, tables_in_lds, vote_words, depth);
+// The speculative one reads across a record: row-major tiles, which keep no prefetch unless
+// they are exact (its registers would not fit 16 wavefronts per CU).
+template <class Tile>
+const void *spec_tile(const ForestShape &s) {
+    if (s.depth == 2) return for_tables<int32_t, Tile, 2>(s.split > 0, s.tables_in_lds, s.vote_words);
+    if (s.depth == 4) return for_tables<int32_t, Tile, 4>(s.split > 0, s.tables_in_lds, s.vote_words);
+    return nullptr;
+}
+
+template <int RS>
+const void *spec_exact(const ForestShape &s) {
+    return spec_tile<dev::ExactTile<kXF32, RS, dev::kRowMajor, kTileRows>>(s);
+}
+
+inline const void *forest_spec_kernel_impl(const ForestShape &s) {
+    if (s.tile.vecs != 0 && s.tile.mode != kLoadExact) return nullptr;
+    if (s.tile.mode == kLoadFlat) return spec_tile<dev::RowTile<kXF32, true, 0, kTileRows>>(s);
+    if (s.tile.mode == kLoadRows) return spec_tile<dev::RowTile<kXF32, false, 0, kTileRows>>(s);
+    switch (s.tile.row_stride) {
+        case 4: return spec_exact<4>(s);
+        case 8: return spec_exact<8>(s);
+        case 16: return spec_exact<16>(s);
+        case 32: return spec_exact<32>(s);
         default: return nullptr;
     }
 }

@@ -12,14 +12,12 @@ enum KernelAlgo { kAlgoData = 0, kAlgoSpec = 1, kAlgoPath = 2 };
 constexpr int kTileRows = 64;          // records per wavefront tile (one per lane)
 constexpr int kMaxRowStride = 256;     // LDS row stride limit in floats (n_features <= 256)
 constexpr int kMaxWavesPerBlock = 8;   // kernels are built for <= 512 threads, except:
-// forest instances whose registers fit 16 wavefronts per CU without spilling (data walk
-// on rows of up to 128 features, speculative walk with depth-2 windows on rows of up to
-// 32), built for <= 1024.  `depth` is the speculative window depth (unused for data).
+// forest instances whose registers fit 16 wavefronts per CU without spilling (data walk,
+// speculative walk with depth-2 windows), built for <= 1024.  `depth` is the speculative
+// window depth (unused for data).
 constexpr int kMaxForestWavesPerBlock = 16;
-__host__ __device__ constexpr int forest_max_waves(int algo, int depth, int row_stride) {
-    return (algo == 0 ? row_stride <= 128 : depth == 2 && row_stride <= 32)
-               ? kMaxForestWavesPerBlock
-               : kMaxWavesPerBlock;
+__host__ __device__ constexpr int forest_max_waves(int algo, int depth) {
+    return algo == 0 || depth == 2 ? kMaxForestWavesPerBlock : kMaxWavesPerBlock;
 }
 constexpr int kMaxForestTrees = 255;   // 8-bit vote counters
 constexpr int kMaxForestClasses = 64;  // 16 VGPRs of packed counters
@@ -34,12 +32,10 @@ struct Rows {
     const void *x;           // device records, row-major, elements of the kernel's type
     int64_t n;               // records
     int64_t ld;              // row stride in elements
-    int64_t n_tiles;         // ceil(n / 64)
+    int64_t n_tiles;         // tiles of the records
     int32_t n_features;      // F
     uint32_t magic_f;        // ceil(2^32 / F) for F >= 2 (row = idx / F via mulhi)
-    int32_t n_words;         // 4-byte words per dense row, F * elem_bytes / 4 (vector loads)
-    uint32_t magic_w;        // ceil(2^32 / n_words) for n_words >= 2
-    // row tiles of the single-tree kernels (kLoadRows, kLoadFlat)
+    // row tiles
     int64_t row_pitch;       // bytes from row to row in the input
     int64_t row_gap;         // row_pitch - 16 * row_vecs
     int32_t row_vecs;        // 16-byte vectors of a row
@@ -98,9 +94,14 @@ __host__ __device__ inline int out_buffer_bytes(int cap, int out_bytes, int tile
     return cap * tile_rows * out_bytes;
 }
 
+// How a forest's data walk finds its exits: int32 or int16 tables of codes, codes packed
+// into the windows' bottom slots, or no windows at all but lists of nodes.
+enum ExitMode { kExitInt32 = 0, kExitInt16 = 1, kExitPacked = 2, kExitList = 3 };
+
 // Forest kernel arguments.  Tree k's tables are the bytes [off_k, off_k + slot_bytes_k)
-// (slots) followed by its exit codes (int16 when every code of the forest fits, else
-// int32), inside `tables`; trees[k] = {off_k, slot_bytes_k, levels_k, 0}.  Chunks are runs of consecutive trees staged into the LDS together:
+// (slots or nodes) followed by its exit codes, if they are a table, inside `tables`;
+// trees[k] = {off_k, slot_bytes_k, levels_k, 0} (node lists: the tree's depth for levels).
+// Chunks are runs of consecutive trees staged into the LDS together:
 // chunks[c] = {first_tree, end_tree, byte_off, bytes}.
 struct FArgs {
     Rows in;
@@ -108,9 +109,12 @@ struct FArgs {
     const int4 *trees;
     const int2 *roots;       // per tree: the root slot {threshold bits, feature byte offset}
     const int4 *chunks;
-    int32_t n_trees;
+    int64_t first_tile;      // tiles [first_tile, end_tile) (forest_kernel: from 0)
+    int64_t end_tile;
     int32_t n_chunks;
     int32_t table_lds_bytes; // LDS bytes reserved for one chunk (0: tables read in place)
+    int32_t tile_bytes;      // LDS bytes of a record tile (multiple of 16)
+    int32_t split;           // 2^split wavefronts per tile (0: forest_kernel)
     int32_t depth;           // window depth D (every tree)
     int32_t n_classes;
     int32_t waves;
@@ -123,21 +127,9 @@ struct FArgs {
 //   kLoadFlat   other dense rows whose width is no multiple of 16 bytes, 4-byte-aligned base
 //   kLoadRows   other rows that all start on 4-byte boundaries
 //   kLoadBytes  rows (of narrow records) that start between words
-// Forest kernels:
-//   kLoadScalar any ld >= F, element-aligned: one element per load
-//   kLoadVec    ld == F, F * elem_bytes % 16 == 0, 16-byte aligned base: 16-byte loads
-//   kLoadExact  as kLoadVec and F == the LDS row stride: every lane loads the same number
-//               of vectors per tile with no bounds test
-enum LoadMode {
-    kLoadScalar = 0,
-    kLoadFlat = 0,
-    kLoadVec = 1,
-    kLoadRows = 1,
-    kLoadExact = 2,
-    kLoadBytes = 3,
-    kLoadModes = 4,
-    kForestLoadModes = 3
-};
+// Forest kernels use the first two and kLoadExact for rows of 4 to 32 fp32 features.
+enum LoadMode { kLoadFlat = 0, kLoadRows = 1, kLoadExact = 2, kLoadBytes = 3, kLoadModes = 4 };
+constexpr int kForestLoadModes = 3;
 
 // Row widths of the exact tiles, in 4-byte words: from one 16-byte vector per row to 64
 // (wider rows would need 16 KiB and more of registers per wavefront: row tiles of fewer
@@ -183,16 +175,23 @@ const void *kernel_for_u8(int algo, const TileShape &shape, bool tables_in_lds, 
 // Path-reduction kernel instance (fp32 records, speculative windows of depth 1..6).
 const void *path_kernel_for(const TileShape &shape, bool tables_in_lds, int depth);
 
-// Forest kernel instance; `vote_words` = 32-bit words of packed 8-bit counters
-// (2, 4 or 16 for up to 8, 16 or 64 classes); `exit_mode`: exit codes stored as int32 (0)
-// or int16 (1) tables, or packed into the windows' bottom slots (2, data walk only).
-const void *forest_kernel_for(int algo, int row_stride, int load_mode, bool tables_in_lds,
-                              int vote_words, int depth, int exit_mode);
-// The int16 and the packed instances (translation units of their own).
-const void *forest_kernel_for_ex16(int algo, int row_stride, int load_mode, bool tables_in_lds,
-                                   int vote_words, int depth);
-const void *forest_kernel_for_packed(int algo, int row_stride, int load_mode,
-                                     bool tables_in_lds, int vote_words, int depth);
+// Forest kernel instance.
+struct ForestShape {
+    int algo = kAlgoData;
+    TileShape tile;
+    bool tables_in_lds = true;
+    int vote_words = 2;      // 32-bit words of packed 8-bit counters: 2, 4 or 16 for up to
+                             // 8, 16 or 64 classes
+    int depth = 0;           // window depth
+    int exit_mode = kExitInt32;   // data walk
+    int split = 0;           // 2^split wavefronts per tile
+};
+const void *forest_kernel_for(const ForestShape &s);
+// The instances by kind (translation units of their own).
+const void *forest_ex16_kernel(const ForestShape &s);
+const void *forest_packed_kernel(const ForestShape &s);
+const void *forest_list_kernel(const ForestShape &s);
+const void *forest_spec_kernel(const ForestShape &s);
 
 // One-time per-instance setup (raise the dynamic LDS limit to the device maximum).
 hipError_t prepare_kernel(const void *fn, int max_lds_bytes);
@@ -202,11 +201,6 @@ hipError_t launch_kernel(const void *fn, const KArgs &args, int blocks, int lds_
                          hipStream_t stream);
 hipError_t launch_forest(const void *fn, const FArgs &args, int blocks, int lds_bytes,
                          hipStream_t stream);
-
-// LDS bytes of one record tile: tile_rows rows of `row_stride` elements of `elem_type`.
-inline int tile_bytes_for(int row_stride, int elem_type, int tile_rows = kTileRows) {
-    return tile_rows * row_stride * elem_bytes(elem_type);
-}
 
 // Dynamic LDS of a workgroup of `waves` wavefronts: tables, one record tile per wavefront,
 // then (single-tree kernels) one result buffer of `out_bytes_per_wave` per wavefront.

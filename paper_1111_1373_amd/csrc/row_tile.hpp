@@ -155,16 +155,16 @@ __device__ __forceinline__ f32x4 load16(const char *p) {
 // registers and several fit the LDS: lanes share rows then (lane l walks row l % TR), which
 // a stream-bound walk has the time for.  NV: prefetch vectors per lane (a class of sizes;
 // vectors past the tile re-read its last one); 0: no prefetch.
-template <int XT, bool FLAT, int NV, int TRv>
-struct RowTile {
+// Loads of a tile; Derived says where a vector and an element (f of row r: r n_features + f)
+// go in the LDS.
+template <class Derived, int XT, bool FLAT, int NV, int TRv>
+struct RowLoads {
     using T = typename Elem<XT>::T;
     static constexpr int TR = TRv;
+    static constexpr bool kFewArgs = false;
     static constexpr bool kPrefetch = NV > 0;
     static constexpr int kRegs = 4 * NV;
     static constexpr int kES = int(sizeof(T));
-    // fp32 rows: the pitch of the widest rows of the class, so that a row some constant
-    // number of rows further is an instruction offset away; 0: in.lds_pitch.
-    static constexpr int kPitch = FLAT || kES < 4 ? 0 : row_tile_pitch(NV, TR);
     f32x4 v[NV > 0 ? NV : 1];
 
     // Row of vector q (0 for flat tiles, which are one run of vectors).
@@ -181,24 +181,6 @@ struct RowTile {
             const int r = row_of(in, q);
             return base + ((in.lds_off + int64_t(r) * in.row_pitch) & ~int64_t(3)) +
                    (q - r * in.row_vecs) * 16;
-        }
-    }
-    static __device__ __forceinline__ void put(const Rows &in, float *tile, int q, f32x4 x) {
-        if constexpr (FLAT) {
-            reinterpret_cast<f32x4 *>(tile)[q] = x;
-        } else {
-            const int r = row_of(in, q);
-            float *p;
-            if constexpr (kPitch > 0)
-                p = tile + q * 4 + r * (kPitch / 4 - in.row_vecs * 4);
-            else if constexpr (kES == 4)
-                p = tile + q * 4 + r;
-            else
-                p = tile + ((in.lds_off + r * in.lds_pitch) >> 2) + (q - r * in.row_vecs) * 4;
-            p[0] = x.x;
-            p[1] = x.y;
-            p[2] = x.z;
-            p[3] = x.w;
         }
     }
     // First word of tile t in the input (in.x is lds_off bytes past a word; tiles start a
@@ -226,13 +208,15 @@ struct RowTile {
 #pragma unroll
         for (int k = 0; k < NV; ++k) {
             const int q = k * 64 + lane;
-            if (q < in.tile_vecs) put(in, tile, q, v[k]);
+            if (q < in.tile_vecs) Derived::put(in, tile, q, v[k]);
         }
     }
-    // Any tile.  Vectors that would leave the input are not loaded; the elements they hold
-    // of the input are loaded one by one (the last bytes of a flat input's last tile, the
-    // last elements of the input's last short_rows rows).
-    static __device__ __forceinline__ void stage(const Rows &in, float *tile, int64_t t, int lane) {
+    // Any tile, staged by one wavefront or, as part `part` of `parts`, by several.  Vectors
+    // that would leave the input are not loaded; the elements they hold of the input are
+    // loaded one by one (the last bytes of a flat input's last tile, the last elements of
+    // the input's last short_rows rows).
+    static __device__ __forceinline__ void stage(const Rows &in, float *tile, int64_t t, int lane,
+                                                 int part = 0, int parts = 1) {
         const char *base = tile_base(in, t);
         const int64_t row0 = t * TR;
         const int valid = valid_rows<TR>(in, t);
@@ -250,12 +234,12 @@ struct RowTile {
         // batches of loads in flight; a lane without a vector re-reads the tile's first
         constexpr int kBatch = NV == 0 || NV > 8 ? 8 : NV;
 #pragma unroll 1
-        for (int k0 = 0; k0 * 64 < nvec; k0 += kBatch) {
+        for (int k0 = part; k0 * 64 < nvec; k0 += kBatch * parts) {
             f32x4 x[kBatch];
             bool ok[kBatch];
 #pragma unroll
             for (int k = 0; k < kBatch; ++k) {
-                const int q = (k0 + k) * 64 + lane;
+                const int q = (k0 + k * parts) * 64 + lane;
                 ok[k] = q < nvec;
                 if constexpr (!FLAT) {
                     const int r = row_of(in, q);
@@ -265,18 +249,59 @@ struct RowTile {
             }
 #pragma unroll
             for (int k = 0; k < kBatch; ++k)
-                if (ok[k]) put(in, tile, (k0 + k) * 64 + lane, x[k]);
+                if (ok[k]) Derived::put(in, tile, (k0 + k * parts) * 64 + lane, x[k]);
         }
+        if (part != 0) return;
         const T *x = static_cast<const T *>(in.x);
         if constexpr (FLAT) {
             const int e = (nvec << 4) / kES + lane;       // fewer than 16 bytes are left
             if (e < valid * in.n_features)
-                reinterpret_cast<T *>(tile)[e] = x[row0 * in.n_features + e];
+                Derived::put_element(in, tile, e, x[row0 * in.n_features + e]);
         } else {
             // a short row's full vectors start up to 3 bytes before it
             const int e = (full_vecs > 0 ? ((full_vecs << 4) - 4) / kES : 0) + lane;
             for (int r = safe_rows; r < valid; ++r)       // at most short_rows rows
-                if (e < in.n_features) row(in, tile, r)[e] = x[(row0 + r) * in.ld + e];
+                if (e < in.n_features)
+                    Derived::put_element(in, tile, r * in.n_features + e, x[(row0 + r) * in.ld + e]);
+        }
+    }
+};
+
+template <int XT, bool FLAT, int NV, int TRv>
+struct RowTile : RowLoads<RowTile<XT, FLAT, NV, TRv>, XT, FLAT, NV, TRv> {
+    using Loads = RowLoads<RowTile<XT, FLAT, NV, TRv>, XT, FLAT, NV, TRv>;
+    using T = typename Loads::T;
+    using Loads::kES;
+    using Loads::row_of;
+    using Loads::TR;
+    // fp32 rows: the pitch of the widest rows of the class, so that a row some constant
+    // number of rows further is an instruction offset away; 0: in.lds_pitch.
+    static constexpr int kPitch = FLAT || kES < 4 ? 0 : row_tile_pitch(NV, TR);
+
+    static __device__ __forceinline__ void put(const Rows &in, float *tile, int q, f32x4 x) {
+        if constexpr (FLAT) {
+            reinterpret_cast<f32x4 *>(tile)[q] = x;
+        } else {
+            const int r = row_of(in, q);
+            float *p;
+            if constexpr (kPitch > 0)
+                p = tile + q * 4 + r * (kPitch / 4 - in.row_vecs * 4);
+            else if constexpr (kES == 4)
+                p = tile + q * 4 + r;
+            else
+                p = tile + ((in.lds_off + r * in.lds_pitch) >> 2) + (q - r * in.row_vecs) * 4;
+            p[0] = x.x;
+            p[1] = x.y;
+            p[2] = x.z;
+            p[3] = x.w;
+        }
+    }
+    static __device__ __forceinline__ void put_element(const Rows &in, float *tile, int e, T x) {
+        if constexpr (FLAT) {
+            reinterpret_cast<T *>(tile)[e] = x;
+        } else {
+            const int r = e / in.n_features;
+            row(in, tile, r)[e - r * in.n_features] = x;
         }
     }
     static __device__ __forceinline__ const T *row(const Rows &in, const float *tile, int r) {
@@ -299,10 +324,39 @@ struct RowTile {
         // features, 64-slot windows: 29 us against 48 us).
         int ofs = g * in.lds_pitch;
 #if defined(__HIP_DEVICE_COMPILE__)
-        if constexpr (NV > 0 && NV <= 8) asm volatile("" : "+s"(ofs));
+        if constexpr (NV <= 8) asm volatile("" : "+s"(ofs));
 #endif
         return feature_at<XT, 1>(
             reinterpret_cast<const T *>(reinterpret_cast<const char *>(row(in, tile, r)) + ofs), s, 0);
+    }
+};
+
+// Column-major tiles of 64 fp32 records for walks whose lanes each read their own record:
+// feature c of row r is word c * 64 + r, so lane r reads bank r whatever feature it asks for.
+template <bool FLAT, int NV>
+struct ColTile : RowLoads<ColTile<FLAT, NV>, kXF32, FLAT, NV, kTileRows> {
+    static __device__ __forceinline__ void put(const Rows &in, float *tile, int q, f32x4 x) {
+        const float v[4] = {x.x, x.y, x.z, x.w};
+        if constexpr (FLAT) {
+            const uint32_t e = uint32_t(q) * 4u;
+            int r = in.n_features == 1 ? int(e) : int(__umulhi(e, in.magic_f));
+            int c = int(e) - r * in.n_features;
+            for (int j = 0; j < 4; ++j) {
+                tile[c * kTileRows + r] = v[j];
+                if (++c == in.n_features) {
+                    c = 0;
+                    ++r;
+                }
+            }
+        } else {
+            const int r = ColTile::row_of(in, q), c = (q - r * in.row_vecs) * 4;
+            for (int j = 0; j < 4; ++j)        // a row's last vector may reach past its end
+                if (c + j < in.n_features) tile[(c + j) * kTileRows + r] = v[j];
+        }
+    }
+    static __device__ __forceinline__ void put_element(const Rows &in, float *tile, int e, float x) {
+        const int r = e / in.n_features;
+        tile[(e - r * in.n_features) * kTileRows + r] = x;
     }
 };
 

@@ -67,7 +67,7 @@ inline uint32_t magic_div(int32_t d) {
     return d >= 2 ? uint32_t(((uint64_t(1) << 32) + uint64_t(d) - 1) / uint64_t(d)) : 0u;
 }
 
-inline Rows make_rows(const void *d_x, int elem_type, int64_t n, int64_t ld, int32_t n_features,
+inline Rows make_rows(const void *d_x, int64_t n, int64_t ld, int32_t n_features,
                       int tile_rows = kTileRows) {
     Rows r{};
     r.x = d_x;
@@ -76,15 +76,13 @@ inline Rows make_rows(const void *d_x, int elem_type, int64_t n, int64_t ld, int
     r.n_tiles = (n + tile_rows - 1) / tile_rows;
     r.n_features = n_features;
     r.magic_f = magic_div(n_features);
-    r.n_words = n_features * elem_bytes(elem_type) / 4;   // used by vector loads only
-    r.magic_w = magic_div(r.n_words);
     return r;
 }
 
 // Records of a single-tree call, for the tile `s`.
 inline Rows make_tile_rows(const void *d_x, int elem_type, int64_t n, int64_t ld,
                            int32_t n_features, const TileShape &s) {
-    Rows r = make_rows(d_x, elem_type, n, ld, n_features, s.tile_rows);
+    Rows r = make_rows(d_x, n, ld, n_features, s.tile_rows);
     const int es = elem_bytes(elem_type);
     r.row_pitch = ld * es;
     r.row_vecs = s.row_vecs;
@@ -100,6 +98,39 @@ inline Rows make_tile_rows(const void *d_x, int elem_type, int64_t n, int64_t ld
                              : 0;
     r.short_rows = int32_t((over + r.row_pitch - 1) / r.row_pitch);
     return r;
+}
+
+// Record tile of a forest kernel: 64 fp32 records.  Prefetched tiles (unsplit kernels) take
+// up to 8 vectors per lane, as many registers as 16 wavefronts per CU leave; the
+// speculative walk has them for exact tiles only.  The data walk's tiles are column-major.
+inline TileShape forest_tile_shape(int algo, int n_features, int mode, bool prefetch) {
+    TileShape s;
+    s.mode = mode;
+    s.tile_rows = kTileRows;
+    s.row_bytes = n_features * 4;
+    if (mode == kLoadExact) {
+        s.row_stride = n_features;
+        s.tile_bytes = kTileRows * s.row_bytes;
+        return s;
+    }
+    const bool flat = mode == kLoadFlat;
+    s.row_vecs = (s.row_bytes + 15) / 16;
+    s.tile_vecs = flat ? kTileRows * s.row_bytes / 16 : kTileRows * s.row_vecs;
+    if (prefetch && algo == kAlgoData)
+        for (int v : {2, 4, 8}) {
+            if (v * 64 < s.tile_vecs) continue;
+            s.vecs = v;
+            break;
+        }
+    s.lds_pitch = flat ? s.row_bytes : 16 * s.row_vecs + 4;
+    s.tile_bytes = kTileRows * (algo == kAlgoData ? s.row_bytes : s.lds_pitch);
+    return s;
+}
+
+// Load path of a forest call.
+inline int forest_load_mode(const void *d_x, int64_t ld, int32_t n_features) {
+    const int mode = load_mode_for(d_x, kXF32, ld, n_features);
+    return mode == kLoadExact && n_features > 32 ? kLoadRows : mode;
 }
 
 }  // namespace dtree

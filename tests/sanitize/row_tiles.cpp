@@ -63,6 +63,46 @@ void drive(const Rows &in, const TileShape &s, int off) {
     }
 }
 
+// Column-major tiles of the forest kernels, staged by one to four wavefronts.
+template <bool FLAT, int NV>
+void drive_columns(const Rows &in, const TileShape &s, int off, int parts) {
+    using Tile = dev::ColTile<FLAT, NV>;
+    const float *x = static_cast<const float *>(in.x);
+    const int64_t end = Tile::prefetch_end(in);
+    for (int64_t t = 0; t < in.n_tiles; ++t) {
+        std::unique_ptr<dev::f32x4[]> mem(new dev::f32x4[size_t(s.tile_bytes / 16)]);
+        float *tile = reinterpret_cast<float *>(mem.get());
+        if (Tile::kPrefetch && t < end) {
+            std::vector<Tile> lanes(64);
+            for (int l = 0; l < 64; ++l) lanes[size_t(l)].load(in, t, l);
+            for (int l = 0; l < 64; ++l) lanes[size_t(l)].store(in, tile, l);
+        } else {
+            for (int pass = 0; pass < 2; ++pass)
+                for (int part = 0; part < parts; ++part)
+                    for (int l = 0; l < 64; ++l) Tile::stage(in, tile, t, l, part, parts);
+        }
+        for (int r = 0; r < kTileRows && t * kTileRows + r < in.n; ++r)
+            for (int f = 0; f < in.n_features; ++f)
+                if (std::memcmp(&tile[f * kTileRows + r], &x[(t * kTileRows + r) * in.ld + f], 4))
+                    fail("column tile", kXF32, in.n_features, in.ld, in.n, s.mode, off);
+    }
+}
+
+void columns(const void *x, int64_t n, int64_t ld, int F, int mode, int off) {
+    if (mode == kLoadExact) mode = kLoadRows;
+    const TileShape s = forest_tile_shape(kAlgoData, F, mode, pick(0, 1) == 0);
+    const Rows in = make_tile_rows(x, kXF32, n, ld, F, s);
+    const bool flat = mode == kLoadFlat;
+    const int parts = s.vecs ? 1 : 1 << pick(0, 2);
+    switch (s.vecs) {
+        case 0: flat ? drive_columns<true, 0>(in, s, off, parts) : drive_columns<false, 0>(in, s, off, parts); break;
+        case 2: flat ? drive_columns<true, 2>(in, s, off, parts) : drive_columns<false, 2>(in, s, off, parts); break;
+        case 4: flat ? drive_columns<true, 4>(in, s, off, parts) : drive_columns<false, 4>(in, s, off, parts); break;
+        case 8: flat ? drive_columns<true, 8>(in, s, off, parts) : drive_columns<false, 8>(in, s, off, parts); break;
+        default: fail("no column tile class", kXF32, F, ld, n, mode, off);
+    }
+}
+
 template <int XT, bool FLAT, int TR>
 bool by_vecs(const Rows &in, const TileShape &s, int off) {
     switch (s.vecs) {
@@ -107,6 +147,7 @@ void one_case() {
     const int algo = algos[XT == kXF32 ? pick(0, 2) : pick(0, 1)];
     const int depth = pick(1, 6);
     int mode = load_mode_for(x, XT, ld, F);
+    if (XT == kXF32) columns(x, n, ld, F, mode, off);
     if (mode == kLoadExact) mode = kLoadRows;           // such rows come strided, too
     const TileShape s = tile_shape(algo, XT, F, mode, depth);
     if (s.tile_bytes % 16 != 0) fail("tile size", XT, F, ld, n, mode, off);

@@ -51,3 +51,51 @@ def test_row_classes(dt, x_type, F, pad, off):
             for algo in algos:
                 got = tree.classify(xd, algo=algo, out_kind="leaf_i32").cpu().numpy()
                 np.testing.assert_array_equal(got, want[:n], err_msg="%s n=%d sd=%d" % (algo, n, sd))
+
+
+# Forests: every staging class, record counts that take one, a few and all wavefronts per
+# tile and leave a last partly filled round, vote words of each size, and trees that are
+# walked as packed windows ("complete") and as node lists ("random").
+@pytest.mark.parametrize("F,pad,off", [(1, 0, 0), (3, 2, 1), (8, 0, 0), (19, 0, 0), (32, 0, 1),
+                                       (33, 0, 0), (64, 0, 0), (100, 5, 0), (200, 0, 0), (256, 0, 3)])
+@pytest.mark.parametrize("shape,C", [("complete", 5), ("random", 16), ("random", 60), ("leaf", 3)])
+def test_forest_row_classes_and_splits(dt, F, pad, off, shape, C):
+    r = np.random.Generator(np.random.PCG64(7000 + F * 100 + C))
+    trees = []
+    for k in range(37):
+        if shape == "leaf" and k % 2:
+            leaf = np.zeros(1, dtype=W.NODE_DTYPE)
+            leaf[0] = (0, 0.0, -1, int(r.integers(0, C)))
+            trees.append(leaf)
+        elif shape == "complete":
+            trees.append(W.complete_tree(r, 6, F, C))
+        else:
+            trees.append(W.random_full_tree(r, int(r.integers(1, 150)), F, C))
+    nodes = np.concatenate(trees)
+    offsets = np.concatenate([[0], np.cumsum([len(t) for t in trees])]).astype(np.int32)
+    ld, n_max = F + pad, 20_000
+    x = W.uniform_f32(r, (n_max * ld + off,))
+    x[r.integers(0, x.size, 500)] = np.nan
+    rows = x[off:].reshape(n_max, ld)[:, :F]
+    want = oracle.forest_classes(nodes, offsets, np.ascontiguousarray(rows), F, C)
+    dev = torch.from_numpy(x).cuda()
+    f = dt.Forest(nodes, offsets, F, C)
+    for n in (1, 63, 65, 1000, 4097, n_max):
+        xd = dev[off:off + n * ld].view(n, ld)[:, :F]
+        for algo in ("data", "speculative"):
+            got = f.classify(xd, algo=algo, out_kind="class_i32").cpu().numpy()
+            np.testing.assert_array_equal(got, want[:n], err_msg="%s n=%d" % (algo, n))
+
+
+@pytest.mark.parametrize("n", [256 * 16 * 64 + 1, 256 * 16 * 64 + 40 * 64])
+def test_forest_lead_and_rest(dt, n):
+    """A full round of tiles by the unsplit kernel and the rest by a split one."""
+    r = np.random.Generator(np.random.PCG64(n))
+    trees = [W.random_full_tree(r, 255, 6, 9) for _ in range(60)]
+    nodes = np.concatenate(trees)
+    offsets = np.concatenate([[0], np.cumsum([len(t) for t in trees])]).astype(np.int32)
+    x = W.uniform_f32(r, (n, 6))
+    f = dt.Forest(nodes, offsets, 6, 9)
+    got = f.classify(torch.from_numpy(x).cuda(), out_kind="class_i32").cpu().numpy()
+    at = np.concatenate([np.arange(0, n, 97), np.arange(n - 3000, n)])
+    np.testing.assert_array_equal(got[at], oracle.forest_classes(nodes, offsets, x[at], 6, 9))
