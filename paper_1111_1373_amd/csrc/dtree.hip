@@ -352,6 +352,7 @@ struct ForestPlan {
     int lds_bytes = 0;
     int chunk_lds_bytes = 0;     // LDS reserved for one chunk (0: tables read in place)
     int first_chunk = 0, n_chunks = 0;
+    double round_cost = 0.0;
     dt_status status = DT_ERR_UNSUPPORTED;
     std::string why = "no kernel instance for this configuration";
 };
@@ -628,9 +629,14 @@ void chunk_forest(const DeviceCaps &caps, int algo, int waves_per_cu, int split,
     // holds the largest tree; ties: larger chunk buffers (fewer passes).
     int best_w = 0, best_score = 0;
     int64_t best_budget = 0;
+    // Speculative walks of wide rows (more than 8 KiB a tile) keep to 8: a ninth tile would
+    // take half of the chunk (64 features, 100 trees: 331 us with 8, 400 us with 9).
+    const int most = algo == DT_ALGO_SPECULATIVE && split == 0 && tile_bytes > 9 * 1024
+                         ? dtree::kMaxWavesPerBlock
+                         : dtree::forest_max_waves(algo, enc->depth);
     for (int bpc = 1; bpc <= 4; ++bpc) {
         const int64_t per_block = std::min<int64_t>(caps.lds_per_block, caps.lds_per_cu / bpc);
-        for (int w = dtree::forest_max_waves(algo, enc->depth); w >= 1 << split; --w) {
+        for (int w = most; w >= 1 << split; --w) {
             const int64_t budget = per_block - (w >> split) * tile_bytes;
             if (budget < enc->max_tree_bytes) continue;
             const int score = std::min(target, w * bpc);
@@ -660,6 +666,12 @@ void chunk_forest(const DeviceCaps &caps, int algo, int waves_per_cu, int split,
             if (bytes + (next - off) > best_budget) break;
             bytes += next - off;
             ++end;
+        }
+        // every wavefront of a tile gets as many trees of the chunk, where it holds enough
+        const int32_t parts = 1 << split;
+        if (end < int32_t(enc->trees.size()) && end - first > parts) {
+            end = first + (end - first) / parts * parts;
+            bytes = enc->trees[size_t(end)].x - enc->trees[size_t(first)].x;
         }
         const int32_t off0 = enc->trees[size_t(first)].x;
         enc->chunks.push_back(int4{first, end, off0, int(bytes)});
@@ -693,6 +705,30 @@ dt_status upload_forest(const std::vector<unsigned char> &bytes, ForestEncoding 
     enc->d_chunks = reinterpret_cast<const int4 *>(base + tb + db);
     enc->d_roots = reinterpret_cast<const int2 *>(base + tb + db + cb);
     return DT_OK;
+}
+
+// Estimated time, in cycles, of one round of groups (every resident workgroup walks its tiles
+// through all trees).  A walk of 64 records takes the CU's LDS about 8 cycles per step
+// (speculative: 40), and its wavefront at least 260 cycles per step of four trees
+// (speculative: 300 of one), whichever is longer with this many wavefronts; each byte of
+// tables copied takes 1/64 cycle, each chunk its barriers, each group its staging, which
+// kernels without prefetch wait for.
+double round_cost(const ForestEncoding &enc, int algo, const ForestPlan &p, int split) {
+    const double steps = std::max(1, std::min(enc.max_levels, 16));
+    const int parts = 1 << split;
+    double walk = 0.0;
+    for (int c = p.first_chunk; c < p.first_chunk + p.n_chunks; ++c) {
+        const int trees = enc.chunks[size_t(c)].y - enc.chunks[size_t(c)].x;
+        const int share = (trees + parts - 1) / parts;      // of a wavefront
+        const double lds = (algo == DT_ALGO_DATA ? 8.0 : 40.0) * steps * trees * p.tiles;
+        const double chain = algo == DT_ALGO_DATA ? 260.0 * steps * ((share + 3) / 4)
+                                                  : 300.0 * steps * share;
+        walk += std::max(lds, chain);
+    }
+    const bool resident = p.chunk_lds_bytes > 0 && p.n_chunks == 1;
+    const double tables = resident ? 0.0 : double(enc.table_bytes) / 64.0 + 800.0 * p.n_chunks;
+    const double wait = p.tile.vecs > 0 || p.tile.mode == dtree::kLoadExact ? 1500.0 : 7000.0;
+    return p.blocks_per_cu * (walk + p.tiles * (p.tile.tile_bytes / 64.0) + tables) + wait;
 }
 
 dt_status plan_forest(const DeviceCaps &caps, int algo, int n_features, int load_mode, int split,
@@ -754,22 +790,9 @@ dt_status plan_forest(const DeviceCaps &caps, int algo, int n_features, int load
         plan->why = "no workgroup shape fits this forest kernel";
         return plan->status = DT_ERR_UNSUPPORTED;
     }
+    plan->round_cost = round_cost(*enc, algo, *plan, split);
     plan->why.clear();
     return plan->status = DT_OK;
-}
-
-// Estimated time, in LDS cycles of a CU, of one round of groups (every resident workgroup
-// walks its tiles through all trees): each walk of 64 records through a tree takes about 8
-// cycles of the CU's LDS per step, each byte of tables copied 1/64 cycle, each chunk its
-// barriers, each group its staging.
-double round_cost(const ForestEncoding &enc, const ForestPlan &p) {
-    const double trees = double(enc.trees.size());
-    const double walk = trees * 8.0 * std::max(1, std::min(enc.max_levels, 16));
-    const bool resident = p.chunk_lds_bytes > 0 && p.n_chunks == 1;
-    const double tables = resident ? 0.0 : double(enc.table_bytes) / 64.0 + 800.0 * p.n_chunks;
-    // unsplit kernels prefetch the next tiles; split ones wait for theirs
-    const double wait = p.tile.vecs > 0 || p.tile.mode == dtree::kLoadExact ? 1500.0 : 7000.0;
-    return p.blocks_per_cu * (p.tiles * (walk + p.tile.tile_bytes / 64.0) + tables) + wait;
 }
 
 // How a call's tiles are spread: the first `lead` by the unsplit kernel, the rest by the
@@ -784,8 +807,7 @@ struct ForestSpread {
 // group of 16 tiles more than there are CUs takes two rounds) and inputs of fewer tiles
 // than wavefronts.  Weighed here: all tiles by one of the kernels, or the full rounds by the
 // unsplit one and the rest by a split one (a second launch).
-ForestSpread spread_forest(const ForestEncoding &enc,
-                           const ForestPlan *const (&plan)[kForestSplits], int n_cu,
+ForestSpread spread_forest(const ForestPlan *const (&plan)[kForestSplits], int n_cu,
                            int64_t tiles) {
     ForestSpread best;
     best.lead = tiles;          // where no plan holds, the unsplit one says why
@@ -793,7 +815,7 @@ ForestSpread spread_forest(const ForestEncoding &enc,
     constexpr double kLaunch = 8000.0;   // a second launch: about 3 us
     const auto rounds = [&](const ForestPlan &p, int64_t t) {
         const int64_t groups = (t + p.tiles - 1) / p.tiles, slots = int64_t(p.blocks_per_cu) * n_cu;
-        return double((groups + slots - 1) / slots) * round_cost(enc, p);
+        return double((groups + slots - 1) / slots) * p.round_cost;
     };
     const auto weigh = [&](double cost, int64_t lead, int split) {
         if (best_cost >= 0.0 && cost >= best_cost) return;
@@ -947,7 +969,7 @@ dt_status forest_classify_impl(const dt_forest *f, const float *d_x, int64_t n, 
         plans[sp] = &f->plan[algo][sp == 0 ? mode : split_mode][sp];
     const ForestEncoding &enc = f->enc[algo];
     const int64_t tiles = (n + dtree::kTileRows - 1) / dtree::kTileRows;
-    const ForestSpread spread = spread_forest(enc, plans, f->caps.n_cu, tiles);
+    const ForestSpread spread = spread_forest(plans, f->caps.n_cu, tiles);
 
     for (int part = 0; part < 2; ++part) {
         const int64_t first = part == 0 ? 0 : spread.lead, end = part == 0 ? spread.lead : tiles;

@@ -393,6 +393,7 @@ const void *col_tile(const ForestShape &s) {
         case 0: return for_tables<EX, dev::ColTile<FLAT, 0>, 0>(s.split > 0, s.tables_in_lds, s.vote_words);
         case 2: return for_tables<EX, dev::ColTile<FLAT, 2>, 0>(s.split > 0, s.tables_in_lds, s.vote_words);
         case 4: return for_tables<EX, dev::ColTile<FLAT, 4>, 0>(s.split > 0, s.tables_in_lds, s.vote_words);
+        case 6: return for_tables<EX, dev::ColTile<FLAT, 6>, 0>(s.split > 0, s.tables_in_lds, s.vote_words);
         case 8: return for_tables<EX, dev::ColTile<FLAT, 8>, 0>(s.split > 0, s.tables_in_lds, s.vote_words);
         default: return nullptr;
     }
@@ -435,6 +436,9 @@ const void *spec_exact(const ForestShape &s) {
 inline const void *forest_spec_kernel_impl(const ForestShape &s) {
     if (s.tile.vecs != 0 && s.tile.mode != kLoadExact) return nullptr;
     if (s.tile.mode == kLoadFlat) return spec_tile<dev::RowTile<kXF32, true, 0, kTileRows>>(s);
+    // rows of 61 to 64 features: a constant pitch (the rounds' rows are instruction offsets)
+    if (s.tile.mode == kLoadRows && s.tile.lds_pitch == 260)
+        return spec_tile<dev::RowTile<kXF32, false, 0, kTileRows, 260>>(s);
     if (s.tile.mode == kLoadRows) return spec_tile<dev::RowTile<kXF32, false, 0, kTileRows>>(s);
     switch (s.tile.row_stride) {
         case 4: return spec_exact<4>(s);

@@ -267,16 +267,16 @@ struct RowLoads {
     }
 };
 
-template <int XT, bool FLAT, int NV, int TRv>
-struct RowTile : RowLoads<RowTile<XT, FLAT, NV, TRv>, XT, FLAT, NV, TRv> {
-    using Loads = RowLoads<RowTile<XT, FLAT, NV, TRv>, XT, FLAT, NV, TRv>;
+template <int XT, bool FLAT, int NV, int TRv, int PITCH = row_tile_pitch(NV, TRv)>
+struct RowTile : RowLoads<RowTile<XT, FLAT, NV, TRv, PITCH>, XT, FLAT, NV, TRv> {
+    using Loads = RowLoads<RowTile<XT, FLAT, NV, TRv, PITCH>, XT, FLAT, NV, TRv>;
     using T = typename Loads::T;
     using Loads::kES;
     using Loads::row_of;
     using Loads::TR;
     // fp32 rows: the pitch of the widest rows of the class, so that a row some constant
     // number of rows further is an instruction offset away; 0: in.lds_pitch.
-    static constexpr int kPitch = FLAT || kES < 4 ? 0 : row_tile_pitch(NV, TR);
+    static constexpr int kPitch = FLAT || kES < 4 ? 0 : PITCH;
 
     static __device__ __forceinline__ void put(const Rows &in, float *tile, int q, f32x4 x) {
         if constexpr (FLAT) {
@@ -350,8 +350,13 @@ struct ColTile : RowLoads<ColTile<FLAT, NV>, kXF32, FLAT, NV, kTileRows> {
             }
         } else {
             const int r = ColTile::row_of(in, q), c = (q - r * in.row_vecs) * 4;
-            for (int j = 0; j < 4; ++j)        // a row's last vector may reach past its end
-                if (c + j < in.n_features) tile[(c + j) * kTileRows + r] = v[j];
+            float *p = tile + c * kTileRows + r;
+            if ((in.n_features & 3) == 0) {
+                for (int j = 0; j < 4; ++j) p[j * kTileRows] = v[j];
+            } else {                           // a row's last vector reaches past its end
+                for (int j = 0; j < 4; ++j)
+                    if (c + j < in.n_features) p[j * kTileRows] = v[j];
+            }
         }
     }
     static __device__ __forceinline__ void put_element(const Rows &in, float *tile, int e, float x) {

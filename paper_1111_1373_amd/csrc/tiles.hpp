@@ -117,7 +117,7 @@ inline TileShape forest_tile_shape(int algo, int n_features, int mode, bool pref
     s.row_vecs = (s.row_bytes + 15) / 16;
     s.tile_vecs = flat ? kTileRows * s.row_bytes / 16 : kTileRows * s.row_vecs;
     if (prefetch && algo == kAlgoData)
-        for (int v : {2, 4, 8}) {
+        for (int v : {2, 4, 6, 8}) {
             if (v * 64 < s.tile_vecs) continue;
             s.vecs = v;
             break;

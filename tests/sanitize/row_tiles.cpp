@@ -98,6 +98,7 @@ void columns(const void *x, int64_t n, int64_t ld, int F, int mode, int off) {
         case 0: flat ? drive_columns<true, 0>(in, s, off, parts) : drive_columns<false, 0>(in, s, off, parts); break;
         case 2: flat ? drive_columns<true, 2>(in, s, off, parts) : drive_columns<false, 2>(in, s, off, parts); break;
         case 4: flat ? drive_columns<true, 4>(in, s, off, parts) : drive_columns<false, 4>(in, s, off, parts); break;
+        case 6: flat ? drive_columns<true, 6>(in, s, off, parts) : drive_columns<false, 6>(in, s, off, parts); break;
         case 8: flat ? drive_columns<true, 8>(in, s, off, parts) : drive_columns<false, 8>(in, s, off, parts); break;
         default: fail("no column tile class", kXF32, F, ld, n, mode, off);
     }
