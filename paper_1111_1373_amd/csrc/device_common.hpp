@@ -277,6 +277,41 @@ __device__ __forceinline__ int32_t walk_data(const typename Node<XT>::S *slots,
     return code;
 }
 
+// One record through a tree stored as a list of 8-byte nodes in pairs of siblings: pair k
+// holds entries 2k and 2k + 1, node i is entry i + 1 (siblings are neighbours from an odd
+// index on, so every pair is one aligned 16-byte read), entry 0 is unused.  A decision node is
+// {threshold (fp32: its bits; narrow: feature << 16 | key, as in the windows' slots), link},
+// link = index of its children's pair, for fp32 records << 10 with the feature's byte offset
+// below.  A leaf is {leaf index, ~class}: its link is negative.
+// As in walk_data the children are read together with the node's feature, so a level costs
+// one LDS round trip; unlike there a record takes exactly the steps of its path, whatever the
+// tree's shape, and a tree of n nodes 8 (n + 1) bytes.  Pairs below `cut` are in the LDS, the
+// others (of trees larger than the LDS can spare) in global memory; children come after their
+// parents in the list, so a path that has left the LDS does not return to it.
+// Returns the class, or the leaf index.
+template <int XT>
+__device__ __forceinline__ int32_t walk_list(const int4 *lds, const int4 *global, int cut,
+                                             bool want_leaf, const typename Elem<XT>::T *row, int sw,
+                                             int2 node) {
+    using N = Node<XT>;
+    constexpr int kShift = XT == kXF32 ? 10 : 0;
+    auto step = [&](const int4 *pairs) {
+        typename N::S s;
+        if constexpr (XT == kXF32)
+            s = Slot{__int_as_float(node.x), int(node.y & int(kListFeatureMask))};
+        else
+            s = uint32_t(node.x);
+        const auto xv = feature_at<XT, 1>(row, s, sw);
+        const int4 kids = pairs[node.y >> kShift];
+        const bool right = N::right(xv, s);
+        node.x = right ? kids.z : kids.x;
+        node.y = right ? kids.w : kids.y;
+    };
+    while (node.y >= 0 && (node.y >> kShift) < cut) step(lds);
+    while (node.y >= 0) step(global);
+    return want_leaf ? node.x : ~node.y;
+}
+
 // Data decomposition over K trees at once (forests): the K walks of one record are
 // independent, so interleaving them keeps K LDS dependency chains in flight per lane.
 // Tree i's tables start at base[i] (LDS or global memory) and its window 0's root slot

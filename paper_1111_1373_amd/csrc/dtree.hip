@@ -36,6 +36,11 @@ dt_status hip_fail(hipError_t e, const char *what) {
     return fail(DT_ERR_HIP, std::string(what) + ": " + hipGetErrorString(e));
 }
 
+// Most LDS a node list takes; the nodes of larger lists' lower levels stay in global memory.
+constexpr int64_t kListLdsBytes = 48 * 1024;
+// Node lists address 2^21 pairs of nodes.
+constexpr int32_t kMaxTreeListNodes = (1 << 22) - 2;
+
 // Device resources of one window encoding: the exits, and the slots once per record
 // type (8-byte fp32 slots; 4-byte words on each narrow type's grid).
 struct Encoding {
@@ -47,7 +52,12 @@ struct Encoding {
     const int4 *d_slots[dtree::kElemTypes] = {};
     const int4 *d_exit_class = nullptr;
     const int4 *d_exit_leaf = nullptr;
-    int64_t table_bytes(int elem_type) const { return slot_bytes[elem_type] + exit_bytes; }
+    // A node list instead of windows (data decomposition, see walk_list): d_slots then hold
+    // the lists, of slot_bytes each, and the first list_lds_bytes of one go to the LDS.
+    bool list = false;
+    int64_t table_bytes(int elem_type) const {
+        return list ? std::min(slot_bytes[elem_type], kListLdsBytes) : slot_bytes[elem_type] + exit_bytes;
+    }
 };
 
 struct DeviceCaps {
@@ -112,6 +122,72 @@ dt_status upload_encoding(const dtree::WindowTables &wt, Encoding *enc) {
     enc->d_exit_class = reinterpret_cast<const int4 *>(base + exit_off);
     enc->d_exit_leaf = reinterpret_cast<const int4 *>(base + exit_off + enc->exit_bytes);
     return DT_OK;
+}
+
+// Upload the tree as node lists, one per record type (see walk_list).
+dt_status upload_list(const dt_node *nodes, int32_t n, Encoding *enc) {
+    enc->list = true;
+    const int64_t size = align16((int64_t(n) + 1) * 8);
+    std::vector<uint32_t> host(size_t(size / 4) * dtree::kElemTypes, 0u);
+    for (int xt = 0; xt < dtree::kElemTypes; ++xt) {
+        enc->slot_bytes[xt] = size;
+        uint32_t *w = host.data() + size_t(size / 4) * size_t(xt);
+        for (int32_t i = 0; i < n; ++i) {
+            const dt_node &t = nodes[i];
+            uint32_t key, link;
+            if (t.cls >= 0) {
+                key = uint32_t(i);
+                link = ~uint32_t(t.cls);
+            } else {
+                const uint32_t pair = uint32_t(t.left + 1) / 2;
+                if (xt == dtree::kXF32) {
+                    std::memcpy(&key, &t.threshold, 4);
+                    link = pair << 10 | uint32_t(4 * t.feature);
+                } else {
+                    key = uint32_t(t.feature) << 16 |
+                          dtree::narrow_key(t.threshold, static_cast<dt_dtype>(xt));
+                    link = pair;
+                }
+            }
+            w[2 * (i + 1)] = key;
+            w[2 * (i + 1) + 1] = link;
+        }
+    }
+    hipError_t e = hipMalloc(&enc->d_mem, host.size() * 4);
+    if (e != hipSuccess) {
+        enc->d_mem = nullptr;
+        return fail(DT_ERR_NO_MEMORY, std::string("hipMalloc: ") + hipGetErrorString(e));
+    }
+    e = hipMemcpy(enc->d_mem, host.data(), host.size() * 4, hipMemcpyHostToDevice);
+    if (e != hipSuccess) return hip_fail(e, "hipMemcpy(node lists)");
+    for (int xt = 0; xt < dtree::kElemTypes; ++xt)
+        enc->d_slots[xt] = reinterpret_cast<const int4 *>(static_cast<unsigned char *>(enc->d_mem) +
+                                                          size * xt);
+    return DT_OK;
+}
+
+// Whether the data decomposition walks the tree as a node list.  Windows pad every path to
+// whole windows and end each with an exit read, and sparse trees leave most of their slots
+// empty; the list takes a path's own steps and 8 bytes a node, at a slightly longer step (the
+// loop's test and the child's index).  So: the list where the windows do not fit their LDS
+// budget (20,000 random decision nodes, 1,000,000 x 16: 21.6 us against 32.1 us), or need
+// several levels (4,000 nodes: 11.6 us against 19.3 us; 300 nodes, 3,000,001 x 19: 37.6 us
+// against 40.1 us) unless the tree is chain-like, all of whose paths are long (a chain of
+// 64: 27.2 us against 24.1 us), or, in one level, take more than four times the list's
+// bytes (the 31-node tree of depth 11).  Only with the default window depth; n_features as
+// far as the kernels go.
+bool use_list(const dt_node *nodes, const dtree::TreeShape &shape, int32_t n_features,
+              const dt_tree_options *opt, int data_depth) {
+    if ((opt && opt->data_window_depth) || shape.n_nodes > kMaxTreeListNodes ||
+        n_features > dtree::kMaxRowStride)
+        return false;
+    const int64_t windows =
+        dtree::table_bytes(dtree::count_windows(nodes, shape, data_depth), data_depth);
+    if (windows > dtree::data_table_budget(n_features)) return true;
+    int log2_nodes = 1;
+    while ((int64_t(1) << log2_nodes) < shape.n_nodes) ++log2_nodes;
+    if (dtree::count_levels(nodes, shape, data_depth) > 1) return shape.depth <= 4 * log2_nodes;
+    return windows > 4 * 8 * (int64_t(shape.n_nodes) + 1);
 }
 
 void free_encoding(Encoding *enc) {
@@ -203,7 +279,7 @@ int target_waves_per_cu(int algo, int tile_rows, int tile_bytes) {
     int size = 256;
     while (size < tile_bytes) size <<= 1;
     const int hbm = tile_rows <= 16 ? 8 : std::max(2, std::min(32, (64 * 1024) / size));
-    if (algo == DT_ALGO_DATA) return hbm;
+    if (algo == DT_ALGO_DATA || algo == dtree::kAlgoList) return hbm;
     if (algo == DT_ALGO_SPECULATIVE)
         return std::min(16, hbm);
     return 8;
@@ -414,7 +490,8 @@ dt_status classify_impl(const dt_tree *tree, const void *d_x, dt_dtype x_type, i
     a.in = make_tile_rows(d_x, x_type, n, ld, tree->n_features, plan.tile);
     a.slots = enc.d_slots[x_type];
     a.exits = out_kind == DT_OUT_LEAF_I32 ? enc.d_exit_leaf : enc.d_exit_class;
-    a.slot_bytes = int32_t(enc.slot_bytes[x_type]);
+    a.slot_bytes = int32_t(enc.list ? enc.table_bytes(x_type) : enc.slot_bytes[x_type]);
+    a.want_leaf = out_kind == DT_OUT_LEAF_I32 ? 1 : 0;
     a.exit_bytes = int32_t(enc.exit_bytes);
     a.depth = enc.depth;
     a.levels = enc.levels;
@@ -454,9 +531,16 @@ dt_status create_impl(const dt_node *nodes, int32_t n_nodes, int32_t n_features,
     int depth[2];
     window_depths(nodes, shape, n_features, opt, &depth[0], &depth[1]);
     for (int e = 0; e < 2; ++e) {
-        dtree::WindowTables wt;
-        dtree::build_windows(nodes, shape, depth[e], &wt);
-        st = upload_encoding(wt, &t->enc[e]);
+        if (e == 0 && use_list(nodes, shape, n_features, opt, depth[0])) {
+            t->enc[0].depth = depth[0];
+            t->enc[0].n_windows = int32_t(dtree::count_windows(nodes, shape, depth[0]));
+            t->enc[0].levels = dtree::count_levels(nodes, shape, depth[0]);
+            st = upload_list(nodes, n_nodes, &t->enc[0]);
+        } else {
+            dtree::WindowTables wt;
+            dtree::build_windows(nodes, shape, depth[e], &wt);
+            st = upload_encoding(wt, &t->enc[e]);
+        }
         if (st != DT_OK) {
             free_encoding(&t->enc[0]);
             free_encoding(&t->enc[1]);
@@ -482,7 +566,7 @@ dt_status create_impl(const dt_node *nodes, int32_t n_nodes, int32_t n_features,
                 if (m == dtree::kLoadFlat && (n_features * es) % 16 == 0) continue;
                 if (m == dtree::kLoadBytes && es == 4) continue;
                 for (int o = 0; o < 2; ++o)
-                    make_plan(t->caps, algo, xt, n_features, m, enc.depth, enc.table_bytes(xt),
+                    make_plan(t->caps, enc.list ? int(dtree::kAlgoList) : algo, xt, n_features, m, enc.depth, enc.table_bytes(xt),
                               o == 0 ? 1 : 4, opt ? opt->waves_per_cu : 0, &pl[o]);
             }
         }

@@ -7,7 +7,8 @@
 
 namespace dtree {
 
-enum KernelAlgo { kAlgoData = 0, kAlgoSpec = 1, kAlgoPath = 2 };
+// kAlgoList: the data decomposition over a node list (single trees)
+enum KernelAlgo { kAlgoData = 0, kAlgoSpec = 1, kAlgoPath = 2, kAlgoList = 3 };
 
 constexpr int kTileRows = 64;          // records per wavefront tile (one per lane)
 constexpr int kMaxRowStride = 256;     // LDS row stride limit in floats (n_features <= 256)
@@ -49,7 +50,8 @@ struct Rows {
 // Single-tree kernel arguments (passed by value).
 struct KArgs {
     Rows in;
-    const int4 *slots;       // n_slots (threshold, feature) pairs, 8 bytes each
+    const int4 *slots;       // n_slots (threshold, feature) pairs, 8 bytes each; list_kernel:
+                             // the node list, slot_bytes of it staged in the LDS
     const int4 *exits;       // n_slots int32 exit codes
     int32_t slot_bytes;      // bytes of the slot region (multiple of 16)
     int32_t exit_bytes;      // bytes of the exit region (multiple of 16)
@@ -60,6 +62,7 @@ struct KArgs {
     int32_t out_cap;         // tiles of results each wavefront buffers in the LDS (>= 1)
     int32_t tile_bytes;      // LDS bytes of a wavefront's record tile (multiple of 16)
     int32_t out_vec;         // 1: `out` is 16-byte aligned (flushes use 16-byte stores)
+    int32_t want_leaf;       // list_kernel: 1: results are leaf indices, 0: classes
     int32_t hops;            // path-reduction kernel: further entries read per round
     void *out;
 };

@@ -12,6 +12,7 @@
 // threshold, which is the decision on the stored value.
 //
 //   data_kernel  (Section 3.2, Procedure 3): lane r evaluates record r of its tile.
+//   list_kernel  the same over a list of the tree's nodes instead of windows.
 //   spec_kernel  (Sections 3.3-3.4, Procedures 4-5): 2^D lanes evaluate all slots of a
 //                record's current window at once; a wavefront ballot gathers the outcomes
 //                and the exit is found by walking the bits.  The mask replaces the paper's
@@ -41,6 +42,25 @@ __global__ void __launch_bounds__(512) data_kernel(KArgs a) {
     const typename dev::Node<XT>::S root0 = slots[1];   // window 0's root, for every record
     dev::tile_loop<Tile>(a, tile, obuf, lane, lane < Tile::TR ? lane : -1, [&]() -> int32_t {
         return ~dev::walk_data<XT>(slots, exits, a.depth, a.levels, row, sw, root0);
+    });
+}
+
+// The data walk over a node list (see walk_list).
+template <int XT, class Tile>
+__global__ void __launch_bounds__(512) list_kernel(KArgs a) {
+    extern __shared__ int4 lds[];
+    dev::copy_to_lds(lds, a.slots, a.slot_bytes >> 4);
+    __syncthreads();
+    const int lane = threadIdx.x & 63;
+    float *tile;
+    uint8_t *obuf;
+    dev::wave_buffers(a, Tile::TR, reinterpret_cast<char *>(lds) + a.slot_bytes, tile, obuf);
+    const int r = lane & (Tile::TR - 1);     // record walked by this lane
+    const auto *row = Tile::row(a.in, tile, r);
+    const int sw = Tile::swizzle(r);
+    const int2 root = reinterpret_cast<const int2 *>(lds)[1];
+    dev::tile_loop<Tile>(a, tile, obuf, lane, lane < Tile::TR ? lane : -1, [&]() -> int32_t {
+        return dev::walk_list<XT>(lds, a.slots, a.slot_bytes >> 4, a.want_leaf != 0, row, sw, root);
     });
 }
 
@@ -76,6 +96,8 @@ using Exact = dev::ExactTile<XT, RS, D >= 5 ? dev::kRowFlat : dev::kRowMajor,
 
 template <int XT, int RS, bool TAB_LDS>
 const void *exact_for(int algo, int depth) {
+    if (algo == kAlgoList)
+        return reinterpret_cast<const void *>(&list_kernel<XT, Exact<XT, RS, 0>>);
     if (algo == kAlgoData)
         return reinterpret_cast<const void *>(&data_kernel<XT, Exact<XT, RS, 0>, TAB_LDS>);
     switch (depth) {
@@ -108,6 +130,7 @@ const void *row_for(int algo, int depth) {
             return reinterpret_cast<const void *>(&spec_kernel<XT, Tile, TAB_LDS, 6>);
     }
     if constexpr (TR == kTileRows || NV > kMaxVecs / 2) {   // 64 records, or wide rows
+        if (algo == kAlgoList) return reinterpret_cast<const void *>(&list_kernel<XT, Tile>);
         if (algo == kAlgoData)
             return reinterpret_cast<const void *>(&data_kernel<XT, Tile, TAB_LDS>);
         switch (depth) {
