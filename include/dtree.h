@@ -271,8 +271,7 @@ dt_status dt_classify(const dt_tree *tree, const float *d_x, int64_t n, int64_t 
 /*
  * dt_classify for narrow records (Section 2.1: ordered discrete attributes behave like the
  * real-valued ones).  Records of element type x_type (dt_dtype): d_x must be aligned to the
- * element size and ld counts elements.  Rows that are contiguous, 16-byte aligned and a
- * multiple of 16 bytes long take the vectorised load path.  Each element is widened
+ * element size and ld counts elements.  Each element is widened
  * exactly to fp32 before its comparison, so the labels equal those of dt_classify on the
  * widened records.  DT_ALGO_PATH reads DT_F32 records only (DT_ERR_UNSUPPORTED otherwise).
  * Errors: as dt_classify, and DT_ERR_INVALID_ARG for an unknown x_type or a misaligned d_x.

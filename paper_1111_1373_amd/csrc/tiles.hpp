@@ -55,7 +55,9 @@ inline bool exact_rows(int32_t n_features, int elem_bytes) {
 // Load path of a single-tree call for the layout of the features (see LoadMode).
 inline int load_mode_for(const void *d_x, int elem_type, int64_t ld, int32_t n_features) {
     const int es = elem_bytes(elem_type);
-    const bool words = reinterpret_cast<uintptr_t>(d_x) % 4 == 0;
+    // fp32 rows start on their own words, also off a base between words (forest calls take
+    // those; the loads then are off 4-byte boundaries, which global memory allows)
+    const bool words = es == 4 || reinterpret_cast<uintptr_t>(d_x) % 4 == 0;
     if (ld != n_features || !words) return words && ld * es % 4 == 0 ? kLoadRows : kLoadBytes;
     if ((n_features * es) % 16 != 0) return kLoadFlat;
     return exact_rows(n_features, es) && (reinterpret_cast<uintptr_t>(d_x) & 15u) == 0
@@ -90,7 +92,7 @@ inline Rows make_tile_rows(const void *d_x, int elem_type, int64_t n, int64_t ld
     r.magic_v = magic_div(s.row_vecs);
     r.tile_vecs = s.tile_vecs;
     r.lds_pitch = s.lds_pitch + (s.mode == kLoadBytes ? int32_t(r.row_pitch % 4) : 0);
-    r.lds_off = int32_t(reinterpret_cast<uintptr_t>(d_x) % 4);
+    r.lds_off = es == 4 ? 0 : int32_t(reinterpret_cast<uintptr_t>(d_x) % 4);
     // bytes that a row's vectors read past its end: row i's stay inside the input when at
     // least that many bytes follow it there, (n - 1 - i) * row_pitch of them
     const int64_t over = s.mode == kLoadRows || s.mode == kLoadBytes

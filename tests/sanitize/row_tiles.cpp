@@ -158,9 +158,27 @@ void one_case() {
     if (!ok) fail("no tile class", XT, F, ld, n, mode, off);
 }
 
+// Every base of fp32 records, those between words among them, has a plan of a forest, whose
+// tiles start at the LDS tile's first word.
+void forest_bases() {
+    for (int F : {1, 3, 4, 8, 19, 32, 64, 256})
+        for (int pad : {0, 1, 4})
+            for (uintptr_t base = 4096; base < 4112; ++base) {
+                const void *x = reinterpret_cast<const void *>(base);
+                const int mode = forest_load_mode(x, F + pad, F);
+                if (mode < 0 || mode >= kForestLoadModes || (mode == kLoadFlat && F % 4 == 0) ||
+                    (mode == kLoadExact && (base % 16 != 0 || F > 32)))
+                    fail("forest plan", kXF32, F, F + pad, 0, mode, int(base % 16));
+                const TileShape s = forest_tile_shape(kAlgoSpec, F, mode, false);
+                if (make_tile_rows(x, kXF32, 100, F + pad, F, s).lds_off != 0)
+                    fail("forest tile base", kXF32, F, F + pad, 0, mode, int(base % 16));
+            }
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
+    forest_bases();
     rng.seed(argc > 1 ? std::strtoull(argv[1], nullptr, 10) : 1);
     const int cases = argc > 2 ? std::atoi(argv[2]) : 1000;
     for (int i = 0; i < cases; ++i) {

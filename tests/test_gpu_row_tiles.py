@@ -99,3 +99,25 @@ def test_forest_lead_and_rest(dt, n):
     got = f.classify(torch.from_numpy(x).cuda(), out_kind="class_i32").cpu().numpy()
     at = np.concatenate([np.arange(0, n, 97), np.arange(n - 3000, n)])
     np.testing.assert_array_equal(got[at], oracle.forest_classes(nodes, offsets, x[at], 6, 9))
+
+
+@pytest.mark.parametrize("algo", ["data", "speculative"])
+@pytest.mark.parametrize("F,pad", [(3, 0), (19, 2), (32, 0), (64, 0)])
+def test_forest_base_between_words(dt, F, pad, algo):
+    """The C call takes fp32 records off a base between words."""
+    r = np.random.Generator(np.random.PCG64(F))
+    trees = [W.random_full_tree(r, 50, F, 5) for _ in range(9)]
+    nodes = np.concatenate(trees)
+    offsets = np.concatenate([[0], np.cumsum([len(t) for t in trees])]).astype(np.int32)
+    n, ld = 3000, F + pad
+    x = W.uniform_f32(r, (n, ld))
+    want = oracle.forest_classes(nodes, offsets, np.ascontiguousarray(x[:, :F]), F, 5)
+    block = torch.zeros(n * ld * 4 + 16, dtype=torch.uint8, device="cuda")
+    f = dt.Forest(nodes, offsets, F, 5)
+    for shift in (1, 2):
+        block[shift:shift + n * ld * 4] = torch.from_numpy(x.reshape(-1).view(np.uint8)).cuda()
+        out = torch.full((n,), -1, dtype=torch.int32, device="cuda")
+        dt._check(dt._lib.dt_forest_classify(
+            f._h, block.data_ptr() + shift, n, ld, out.data_ptr(), dt.OUT_KINDS["class_i32"],
+            dt.ALGOS[algo], torch.cuda.current_stream().cuda_stream), "dt_forest_classify")
+        np.testing.assert_array_equal(out.cpu().numpy(), want)
