@@ -1,6 +1,7 @@
 // Host-side choice of the record tiles (see LoadMode and TileShape in kernels.hpp).
 #pragma once
 
+#include <algorithm>
 #include <cstdint>
 
 #include "kernels.hpp"
@@ -58,7 +59,7 @@ inline int load_mode_for(const void *d_x, int elem_type, int64_t ld, int32_t n_f
     // fp32 rows start on their own words, also off a base between words (forest calls take
     // those; the loads then are off 4-byte boundaries, which global memory allows)
     const bool words = es == 4 || reinterpret_cast<uintptr_t>(d_x) % 4 == 0;
-    if (ld != n_features || !words) return words && ld * es % 4 == 0 ? kLoadRows : kLoadBytes;
+    if (ld != n_features || !words) return words && ld % 4 * es % 4 == 0 ? kLoadRows : kLoadBytes;
     if ((n_features * es) % 16 != 0) return kLoadFlat;
     return exact_rows(n_features, es) && (reinterpret_cast<uintptr_t>(d_x) & 15u) == 0
                ? kLoadExact
@@ -69,12 +70,14 @@ inline uint32_t magic_div(int32_t d) {
     return d >= 2 ? uint32_t(((uint64_t(1) << 32) + uint64_t(d) - 1) / uint64_t(d)) : 0u;
 }
 
+// A single record's stride is never used and may be any number; more records have none
+// whose bytes overflow (no memory holds them), and 2^60 elements stand for such a one.
 inline Rows make_rows(const void *d_x, int64_t n, int64_t ld, int32_t n_features,
                       int tile_rows = kTileRows) {
     Rows r{};
     r.x = d_x;
     r.n = n;
-    r.ld = ld;
+    r.ld = n > 1 ? std::min(ld, int64_t(1) << 60) : n_features;
     r.n_tiles = (n + tile_rows - 1) / tile_rows;
     r.n_features = n_features;
     r.magic_f = magic_div(n_features);
@@ -86,7 +89,7 @@ inline Rows make_tile_rows(const void *d_x, int elem_type, int64_t n, int64_t ld
                            int32_t n_features, const TileShape &s) {
     Rows r = make_rows(d_x, n, ld, n_features, s.tile_rows);
     const int es = elem_bytes(elem_type);
-    r.row_pitch = ld * es;
+    r.row_pitch = r.ld * es;
     r.row_vecs = s.row_vecs;
     r.row_gap = r.row_pitch - 16 * s.row_vecs;
     r.magic_v = magic_div(s.row_vecs);

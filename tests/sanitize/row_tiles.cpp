@@ -4,6 +4,7 @@
 // either one ends the run; then every feature of every staged record is read back through
 // the addresses the walks use.
 //   row_tiles SEED CASES
+#include <algorithm>
 #include <cstdio>
 #include <cstdlib>
 #include <memory>
@@ -133,8 +134,10 @@ template <int XT>
 void one_case() {
     using T = typename dev::Elem<XT>::T;
     const int F = pick(0, 2) ? pick(1, 40) : pick(1, kMaxRowStride);
-    const int64_t ld = F + (pick(0, 1) ? 0 : pick(0, 5) ? pick(0, 9) : pick(0, 700));
+    int64_t ld = F + (pick(0, 1) ? 0 : pick(0, 5) ? pick(0, 9) : pick(0, 700));
     const int64_t n = pick(0, 3) ? pick(1, 200) : pick(1, 20);
+    // a single record may come with any stride, also one whose bytes no 64-bit number holds
+    if (n == 1 && pick(0, 1)) ld = std::max<int64_t>(ld, INT64_MAX >> pick(0, 40)) - pick(0, 1);
     const int off = pick(0, 1) ? 0 : pick(0, 15);      // elements before the first record
     // the block starts on a 16-byte boundary and ends with the last record's last feature
     const size_t count = size_t(off) + size_t((n - 1) * ld + F);
