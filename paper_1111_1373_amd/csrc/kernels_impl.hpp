@@ -96,8 +96,13 @@ using Exact = dev::ExactTile<XT, RS, D >= 5 ? dev::kRowFlat : dev::kRowMajor,
 
 template <int XT, int RS, bool TAB_LDS>
 const void *exact_for(int algo, int depth) {
-    if (algo == kAlgoList)
-        return reinterpret_cast<const void *>(&list_kernel<XT, Exact<XT, RS, 0>>);
+    // the list kernel stages its list: there is none for tables read in place
+    if (algo == kAlgoList) {
+        if constexpr (TAB_LDS)
+            return reinterpret_cast<const void *>(&list_kernel<XT, Exact<XT, RS, 0>>);
+        else
+            return nullptr;
+    }
     if (algo == kAlgoData)
         return reinterpret_cast<const void *>(&data_kernel<XT, Exact<XT, RS, 0>, TAB_LDS>);
     switch (depth) {
@@ -130,7 +135,12 @@ const void *row_for(int algo, int depth) {
             return reinterpret_cast<const void *>(&spec_kernel<XT, Tile, TAB_LDS, 6>);
     }
     if constexpr (TR == kTileRows || NV > kMaxVecs / 2) {   // 64 records, or wide rows
-        if (algo == kAlgoList) return reinterpret_cast<const void *>(&list_kernel<XT, Tile>);
+        if (algo == kAlgoList) {
+            if constexpr (TAB_LDS)
+                return reinterpret_cast<const void *>(&list_kernel<XT, Tile>);
+            else
+                return nullptr;
+        }
         if (algo == kAlgoData)
             return reinterpret_cast<const void *>(&data_kernel<XT, Tile, TAB_LDS>);
         switch (depth) {

@@ -1,0 +1,25 @@
+"""The kernels that the launch plans can ask for exist, the list kernel only with its list in
+the LDS (tests/c/kernel_instances.cpp, host side only)."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+PKG = os.path.join(ROOT, "paper_1111_1373_amd")
+
+
+def test_every_planned_kernel_exists(tmp_path):
+    lib = os.path.join(PKG, "libdtree.so")
+    if shutil.which("g++") is None or not os.path.exists(lib):
+        pytest.skip("needs g++ and the built library")
+    import torch  # noqa: F401  (the HIP runtime that the library binds to)
+    exe = str(tmp_path / "kernel_instances")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                    "-I" + os.path.join(ROOT, "include"), "-I" + os.path.join(PKG, "csrc"),
+                    os.path.join(ROOT, "tests", "c", "kernel_instances.cpp"),
+                    "-L" + PKG, "-ldtree", "-Wl,-rpath," + PKG, "-o", exe],
+                   check=True, capture_output=True, text=True)
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0 and r.stdout.startswith("ok "), r.stdout + r.stderr
