@@ -26,7 +26,7 @@ constexpr int kMaxForestClasses = 64;  // 16 VGPRs of packed counters
 // Record element types (values of dt_dtype).  Each widens exactly to fp32.
 enum ElemType { kXF32 = 0, kXF16 = 1, kXBF16 = 2, kXU8 = 3, kElemTypes = 4 };
 
-__host__ __device__ inline int elem_bytes(int xt) { return xt == kXF32 ? 4 : xt == kXU8 ? 1 : 2; }
+__host__ __device__ constexpr int elem_bytes(int xt) { return xt == kXF32 ? 4 : xt == kXU8 ? 1 : 2; }
 
 // The record matrix a kernel reads.
 struct Rows {

@@ -20,6 +20,7 @@
 #pragma once
 
 #include "device_common.hpp"
+#include "tiles.hpp"
 
 namespace dtree {
 namespace {
@@ -125,24 +126,19 @@ const void *exact_kernel(int algo, bool tab_lds, int depth) {
         return tab_lds ? exact_for<XT, RS, true>(algo, depth) : exact_for<XT, RS, false>(algo, depth);
 }
 
+// One class of row tiles, where rows of some width have it.  (Data walk and node lists share
+// their tiles, and so do the speculative windows of depths 1 to 4 and those of 5 and 6.)
 template <int XT, bool FLAT, bool TAB_LDS, int NV, int TR>
 const void *row_for(int algo, int depth) {
     using Tile = dev::RowTile<XT, FLAT, NV, TR>;
-    if constexpr (TR < kTileRows) {   // the wide windows' tiles never have more records
-        if (depth == 5 && algo == kAlgoSpec)
-            return reinterpret_cast<const void *>(&spec_kernel<XT, Tile, TAB_LDS, 5>);
-        if (depth == 6 && algo == kAlgoSpec)
-            return reinterpret_cast<const void *>(&spec_kernel<XT, Tile, TAB_LDS, 6>);
-    }
-    if constexpr (TR == kTileRows || NV > kMaxVecs / 2) {   // 64 records, or wide rows
-        if (algo == kAlgoList) {
-            if constexpr (TAB_LDS)
-                return reinterpret_cast<const void *>(&list_kernel<XT, Tile>);
-            else
-                return nullptr;
-        }
+    if constexpr (row_class_used(kAlgoData, XT, 0, FLAT, NV, TR)) {
+        if constexpr (TAB_LDS)
+            if (algo == kAlgoList) return reinterpret_cast<const void *>(&list_kernel<XT, Tile>);
         if (algo == kAlgoData)
             return reinterpret_cast<const void *>(&data_kernel<XT, Tile, TAB_LDS>);
+    }
+    if (algo != kAlgoSpec) return nullptr;
+    if constexpr (row_class_used(kAlgoSpec, XT, 1, FLAT, NV, TR)) {
         switch (depth) {
             case 1: return reinterpret_cast<const void *>(&spec_kernel<XT, Tile, TAB_LDS, 1>);
             case 2: return reinterpret_cast<const void *>(&spec_kernel<XT, Tile, TAB_LDS, 2>);
@@ -151,43 +147,35 @@ const void *row_for(int algo, int depth) {
             default: break;
         }
     }
+    if constexpr (row_class_used(kAlgoSpec, XT, 5, FLAT, NV, TR)) {
+        if (depth == 5) return reinterpret_cast<const void *>(&spec_kernel<XT, Tile, TAB_LDS, 5>);
+        if (depth == 6) return reinterpret_cast<const void *>(&spec_kernel<XT, Tile, TAB_LDS, 6>);
+    }
     return nullptr;
+}
+
+template <int XT, bool FLAT, bool TAB_LDS, int TR>
+const void *row_tile_for(int algo, int vecs, int depth) {
+    switch (vecs) {
+        case 2: return row_for<XT, FLAT, TAB_LDS, 2, TR>(algo, depth);
+        case 3: return row_for<XT, FLAT, TAB_LDS, 3, TR>(algo, depth);
+        case 4: return row_for<XT, FLAT, TAB_LDS, 4, TR>(algo, depth);
+        case 6: return row_for<XT, FLAT, TAB_LDS, 6, TR>(algo, depth);
+        case 8: return row_for<XT, FLAT, TAB_LDS, 8, TR>(algo, depth);
+        case 12: return row_for<XT, FLAT, TAB_LDS, 12, TR>(algo, depth);
+        case 16: return row_for<XT, FLAT, TAB_LDS, 16, TR>(algo, depth);
+        default: return nullptr;
+    }
 }
 
 template <int XT, bool FLAT, bool TAB_LDS>
 const void *row_kernel(int algo, int vecs, int tile_rows, int depth) {
-    // tiles of 16 records exist only for rows of more than 32 vectors (256 16-bit features
-    // between words are 33)
-    constexpr int kWidest = kMaxRowStride * int(sizeof(typename dev::Elem<XT>::T));
-    if (tile_rows == 64) {
-        switch (vecs) {
-            case 2: return row_for<XT, FLAT, TAB_LDS, 2, 64>(algo, depth);
-            case 3: return row_for<XT, FLAT, TAB_LDS, 3, 64>(algo, depth);
-            case 4: return row_for<XT, FLAT, TAB_LDS, 4, 64>(algo, depth);
-            case 6: return row_for<XT, FLAT, TAB_LDS, 6, 64>(algo, depth);
-            case 8: return row_for<XT, FLAT, TAB_LDS, 8, 64>(algo, depth);
-            case 12: return row_for<XT, FLAT, TAB_LDS, 12, 64>(algo, depth);
-            case 16: return row_for<XT, FLAT, TAB_LDS, 16, 64>(algo, depth);
-            default: return nullptr;
-        }
+    switch (tile_rows) {
+        case 64: return row_tile_for<XT, FLAT, TAB_LDS, 64>(algo, vecs, depth);
+        case 32: return row_tile_for<XT, FLAT, TAB_LDS, 32>(algo, vecs, depth);
+        case 16: return row_tile_for<XT, FLAT, TAB_LDS, 16>(algo, vecs, depth);
+        default: return nullptr;
     }
-    if (tile_rows == 32) {
-        switch (vecs) {
-            case 2: return row_for<XT, FLAT, TAB_LDS, 2, 32>(algo, depth);
-            case 3: return row_for<XT, FLAT, TAB_LDS, 3, 32>(algo, depth);
-            case 4: return row_for<XT, FLAT, TAB_LDS, 4, 32>(algo, depth);
-            case 6: return row_for<XT, FLAT, TAB_LDS, 6, 32>(algo, depth);
-            case 8: return row_for<XT, FLAT, TAB_LDS, 8, 32>(algo, depth);
-            case 12: return row_for<XT, FLAT, TAB_LDS, 12, 32>(algo, depth);
-            case 16: return row_for<XT, FLAT, TAB_LDS, 16, 32>(algo, depth);
-            default: return nullptr;
-        }
-    }
-    if constexpr (kWidest >= 512) {
-        if (tile_rows == 16 && vecs == 12) return row_for<XT, FLAT, TAB_LDS, 12, 16>(algo, depth);
-        if (tile_rows == 16 && vecs == 16) return row_for<XT, FLAT, TAB_LDS, 16, 16>(algo, depth);
-    }
-    return nullptr;
 }
 
 template <int XT>

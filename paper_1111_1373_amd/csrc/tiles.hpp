@@ -8,13 +8,13 @@
 
 namespace dtree {
 
-inline int64_t align16(int64_t b) { return (b + 15) & ~int64_t(15); }
+constexpr int64_t align16(int64_t b) { return (b + 15) & ~int64_t(15); }
 
 // Record tile of a single-tree kernel for load mode `mode` (see LoadMode).  Row tiles hold
 // 64 records, or, so that a tile stays within kMaxVecs prefetch vectors per lane, 32 or 16
 // of wide rows.  The speculative walk of wide windows (depths 5 and 6) starts from 32, as
 // on exact rows; the path kernel walks 64 at a time and leaves the prefetch out instead.
-inline TileShape tile_shape(int algo, int elem_type, int n_features, int mode, int depth) {
+constexpr TileShape tile_shape(int algo, int elem_type, int n_features, int mode, int depth) {
     TileShape s;
     s.mode = mode;
     const int es = elem_bytes(elem_type);
@@ -45,6 +45,22 @@ inline TileShape tile_shape(int algo, int elem_type, int n_features, int mode, i
                                                : 16 * s.row_vecs + 4;
     s.tile_bytes = int(align16(s.tile_rows * (s.lds_pitch + (bytes ? 3 : 0)) + (bytes ? 3 : 0)));
     return s;
+}
+
+// Whether tile_shape gives row tiles of this class (flat or not, prefetch vectors, records)
+// for any width of rows: the instances that are compiled.
+constexpr bool row_class_used(int algo, int elem_type, int depth, bool flat, int vecs,
+                              int tile_rows) {
+    for (int f = 1; f <= kMaxRowStride; ++f) {
+        for (int mode : {kLoadFlat, kLoadRows, kLoadBytes}) {
+            if ((mode == kLoadFlat) != flat) continue;
+            if (flat && f * elem_bytes(elem_type) % 16 == 0) continue;
+            if (mode == kLoadBytes && elem_type == kXF32) continue;
+            const TileShape s = tile_shape(algo, elem_type, f, mode, depth);
+            if (s.vecs == vecs && s.tile_rows == tile_rows) return true;
+        }
+    }
+    return false;
 }
 
 inline bool exact_rows(int32_t n_features, int elem_bytes) {

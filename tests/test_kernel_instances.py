@@ -1,6 +1,8 @@
-"""The kernels that the launch plans can ask for exist, the list kernel only with its list in
-the LDS (tests/c/kernel_instances.cpp, host side only)."""
+"""The kernels that the library holds are the ones that its launch plans can ask for
+(tests/c/kernel_instances.cpp, host side only): none is missing and none is out of reach."""
+import collections
 import os
+import re
 import shutil
 import subprocess
 
@@ -10,7 +12,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 PKG = os.path.join(ROOT, "paper_1111_1373_amd")
 
 
-def test_every_planned_kernel_exists(tmp_path):
+def test_every_planned_kernel_exists_and_no_other(tmp_path):
     lib = os.path.join(PKG, "libdtree.so")
     if shutil.which("g++") is None or not os.path.exists(lib):
         pytest.skip("needs g++ and the built library")
@@ -23,3 +25,10 @@ def test_every_planned_kernel_exists(tmp_path):
                    check=True, capture_output=True, text=True)
     r = subprocess.run([exe], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0 and r.stdout.startswith("ok "), r.stdout + r.stderr
+    # kernel descriptors in the device code: one name per kernel, each as often as the others
+    # (in a code object's two symbol tables); a kernel that several units hold appears more often
+    with open(lib, "rb") as f:
+        names = collections.Counter(re.findall(rb"[\w.$]+\.kd\0", f.read()))
+    assert len(set(names.values())) == 1, names.most_common(1)
+    tree_kernels = [n for n in names if b"copy_kernel" not in n and b"read_kernel" not in n]
+    assert int(r.stdout.split()[1]) == len(tree_kernels)
