@@ -277,9 +277,9 @@ __device__ __forceinline__ int32_t walk_data(const typename Node<XT>::S *slots,
     return code;
 }
 
-// One record through a tree stored as a list of 8-byte nodes in pairs of siblings: pair k
-// holds entries 2k and 2k + 1, node i is entry i + 1 (siblings are neighbours from an odd
-// index on, so every pair is one aligned 16-byte read), entry 0 is unused.  A decision node is
+// One record through a tree stored as a list of 8-byte nodes in breadth-first order, in pairs
+// of siblings: pair k holds entries 2k and 2k + 1 (siblings are neighbours from an even entry
+// on, so every pair is one aligned 16-byte read), the root is entry 1, entry 0 is unused.  A decision node is
 // {threshold (fp32: its bits; narrow: feature << 16 | key, as in the windows' slots), link},
 // link = index of its children's pair, for fp32 records << 10 with the feature's byte offset
 // below.  A leaf is {leaf index, ~class}: its link is negative.
@@ -411,7 +411,7 @@ __device__ __forceinline__ void walk_data_k(const char *const (&base)[K],
 }
 
 // Data decomposition over K trees stored as node lists (irregular trees of forests): nodes
-// {t, link} in the order of the node array from index 1, link = left child's index << 10 |
+// {t, link} in breadth-first order from index 1, link = left child's index << 10 |
 // byte offset of the feature; one step is i <- left + !(x[f] < t).  A leaf is a node that
 // goes right to itself (its left is its own index - 1, its t a NaN), with the class in the
 // NaN's low bits, so finished chains need no test of their own.  A tree of n nodes takes 8 n

@@ -38,8 +38,6 @@ dt_status hip_fail(hipError_t e, const char *what) {
 
 // Most LDS a node list takes; the nodes of larger lists' lower levels stay in global memory.
 constexpr int64_t kListLdsBytes = 48 * 1024;
-// Node lists address 2^21 pairs of nodes.
-constexpr int32_t kMaxTreeListNodes = (1 << 22) - 2;
 
 // Device resources of one window encoding: the exits, and the slots once per record
 // type (8-byte fp32 slots; 4-byte words on each narrow type's grid).
@@ -127,31 +125,13 @@ dt_status upload_encoding(const dtree::WindowTables &wt, Encoding *enc) {
 // Upload the tree as node lists, one per record type (see walk_list).
 dt_status upload_list(const dt_node *nodes, int32_t n, Encoding *enc) {
     enc->list = true;
-    const int64_t size = align16((int64_t(n) + 1) * 8);
+    const int64_t size = dtree::list_bytes(n);
+    const std::vector<int32_t> order = dtree::breadth_first_order(nodes, n);
     std::vector<uint32_t> host(size_t(size / 4) * dtree::kElemTypes, 0u);
     for (int xt = 0; xt < dtree::kElemTypes; ++xt) {
         enc->slot_bytes[xt] = size;
-        uint32_t *w = host.data() + size_t(size / 4) * size_t(xt);
-        for (int32_t i = 0; i < n; ++i) {
-            const dt_node &t = nodes[i];
-            uint32_t key, link;
-            if (t.cls >= 0) {
-                key = uint32_t(i);
-                link = ~uint32_t(t.cls);
-            } else {
-                const uint32_t pair = uint32_t(t.left + 1) / 2;
-                if (xt == dtree::kXF32) {
-                    std::memcpy(&key, &t.threshold, 4);
-                    link = pair << 10 | uint32_t(4 * t.feature);
-                } else {
-                    key = uint32_t(t.feature) << 16 |
-                          dtree::narrow_key(t.threshold, static_cast<dt_dtype>(xt));
-                    link = pair;
-                }
-            }
-            w[2 * (i + 1)] = key;
-            w[2 * (i + 1) + 1] = link;
-        }
+        dtree::build_list(nodes, n, order, static_cast<dt_dtype>(xt),
+                          host.data() + size_t(size / 4) * size_t(xt));
     }
     hipError_t e = hipMalloc(&enc->d_mem, host.size() * 4);
     if (e != hipSuccess) {
@@ -178,7 +158,7 @@ dt_status upload_list(const dt_node *nodes, int32_t n, Encoding *enc) {
 // far as the kernels go.
 bool use_list(const dt_node *nodes, const dtree::TreeShape &shape, int32_t n_features,
               const dt_tree_options *opt, int data_depth) {
-    if ((opt && opt->data_window_depth) || shape.n_nodes > kMaxTreeListNodes ||
+    if ((opt && opt->data_window_depth) || shape.n_nodes > dtree::kMaxTreeListNodes ||
         n_features > dtree::kMaxRowStride)
         return false;
     const int64_t windows =
@@ -661,42 +641,29 @@ void encode_forest(const dt_node *nodes, const int32_t *offsets, int32_t n_trees
     enc->table_bytes = int64_t(bytes->size());
 }
 
-// Every tree as a node list (see walk_list_k): node i of the array is list entry i + 1.
+// Every tree as a node list (see walk_list_k).
 void list_forest(const dt_node *nodes, const int32_t *offsets, int32_t n_trees,
                  const std::vector<dtree::TreeShape> &shapes, std::vector<unsigned char> *bytes,
                  ForestEncoding *enc) {
     enc->depth = 0;
     enc->exit_mode = dtree::kExitList;
+    std::vector<uint32_t> list;
     for (int32_t k = 0; k < n_trees; ++k) {
         const dt_node *t = nodes + offsets[k];
         const int32_t n = offsets[k + 1] - offsets[k];
-        const int64_t off = int64_t(bytes->size()), size = align16((int64_t(n) + 1) * 8);
+        const int64_t off = int64_t(bytes->size()), size = dtree::list_bytes(n);
         bytes->resize(size_t(off + size), 0);
-        unsigned char *p = bytes->data() + off;
-        for (int32_t i = 0; i < n; ++i) {
-            uint32_t w[2];
-            if (t[i].cls < 0) {
-                std::memcpy(&w[0], &t[i].threshold, 4);
-                w[1] = uint32_t(t[i].left + 1) << 10 | uint32_t(4 * t[i].feature);
-            } else {
-                w[0] = 0x7FC00000u | uint32_t(t[i].cls);
-                w[1] = uint32_t(i) << 10;
-            }
-            std::memcpy(p + 8 * (int64_t(i) + 1), w, 8);
-        }
+        list.assign(size_t(size / 4), 0u);
+        dtree::build_forest_list(t, n, dtree::breadth_first_order(t, n), list.data());
+        std::memcpy(bytes->data() + off, list.data(), size_t(size));
         const int32_t depth = shapes[size_t(k)].depth;
         enc->trees.push_back(int4{int(off), int(size), depth, 0});
-        int2 root{0, 0};
-        std::memcpy(&root, p + 8, 8);
-        enc->roots.push_back(root);
+        enc->roots.push_back(int2{int(list[2]), int(list[3])});
         enc->max_tree_bytes = std::max(enc->max_tree_bytes, size);
         enc->max_levels = std::max(enc->max_levels, depth);
     }
     enc->table_bytes = int64_t(bytes->size());
 }
-
-// Node lists hold left indices of 22 bits.
-constexpr int32_t kMaxListNodes = (1 << 22) - 2;
 
 // Wavefronts per CU the forest kernel aims for by default (measured: 16 beat 8 by 5% on a
 // 32-tree forest; more gained nothing).
@@ -984,7 +951,7 @@ dt_status forest_create_impl(const dt_node *nodes, const int32_t *offsets, int32
         }
         for (int32_t k = 0; k < n_trees; ++k) {
             list_bytes += 8 * (int64_t(offsets[k + 1] - offsets[k]) + 1);
-            listable = listable && offsets[k + 1] - offsets[k] <= kMaxListNodes;
+            listable = listable && offsets[k + 1] - offsets[k] <= dtree::kMaxForestListNodes;
         }
         list = listable && (max_depth > data_d || best / 12 * 8 > list_bytes);
     }

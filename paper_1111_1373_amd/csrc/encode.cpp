@@ -241,6 +241,61 @@ void build_narrow_slots(const WindowTables &wt, dt_dtype type, std::vector<uint3
         (*out)[i] = (uint32_t(wt.feature[i]) << 16) | narrow_key(wt.threshold[i], type);
 }
 
+std::vector<int32_t> breadth_first_order(const dt_node *nodes, int32_t n) {
+    std::vector<int32_t> queue, order(static_cast<size_t>(n));
+    queue.reserve(size_t(n));
+    queue.push_back(0);
+    for (int32_t h = 0; h < n; ++h) {
+        const int32_t v = queue[size_t(h)];
+        order[size_t(v)] = h;
+        if (nodes[v].cls != -1) continue;
+        queue.push_back(nodes[v].left);
+        queue.push_back(nodes[v].left + 1);
+    }
+    return order;
+}
+
+void build_list(const dt_node *nodes, int32_t n, const std::vector<int32_t> &order, dt_dtype type,
+                uint32_t *out) {
+    for (int32_t i = 0; i < n; ++i) {
+        const dt_node &t = nodes[i];
+        uint32_t key, link;
+        if (t.cls != -1) {
+            key = uint32_t(i);
+            link = ~uint32_t(t.cls);
+        } else {
+            // siblings are neighbours from an odd place on: entries 2 pair and 2 pair + 1
+            const uint32_t pair = uint32_t(order[size_t(t.left)] + 1) / 2;
+            if (type == DT_F32) {
+                std::memcpy(&key, &t.threshold, 4);
+                link = pair << 10 | uint32_t(4 * t.feature);
+            } else {
+                key = uint32_t(t.feature) << 16 | narrow_key(t.threshold, type);
+                link = pair;
+            }
+        }
+        uint32_t *w = out + 2 * (size_t(order[size_t(i)]) + 1);
+        w[0] = key;
+        w[1] = link;
+    }
+}
+
+void build_forest_list(const dt_node *nodes, int32_t n, const std::vector<int32_t> &order,
+                       uint32_t *out) {
+    for (int32_t i = 0; i < n; ++i) {
+        const dt_node &t = nodes[i];
+        const uint32_t place = uint32_t(order[size_t(i)]);
+        uint32_t *w = out + 2 * (size_t(place) + 1);
+        if (t.cls == -1) {
+            std::memcpy(&w[0], &t.threshold, 4);
+            w[1] = uint32_t(order[size_t(t.left)] + 1) << 10 | uint32_t(4 * t.feature);
+        } else {
+            w[0] = 0x7FC00000u | uint32_t(t.cls);
+            w[1] = place << 10;
+        }
+    }
+}
+
 int64_t data_table_budget(int32_t n_features) {
     int rs = 4;
     while (rs < n_features) rs <<= 1;

@@ -66,6 +66,28 @@ void build_narrow_slots(const WindowTables &wt, dt_dtype type, std::vector<uint3
 // windows when that needs fewer windows.
 int first_window_depth(const dt_node *nodes, const TreeShape &shape, int depth);
 
+// Node lists (see walk_list and walk_list_k in device_common.hpp): entry 0 is unused, node v
+// is entry 1 + order[v], 8 bytes each.  The order is breadth-first whatever the order of the
+// caller's array, so that the first entries are the tree's upper levels, which every record
+// passes: the part of a large list that the LDS holds.
+std::vector<int32_t> breadth_first_order(const dt_node *nodes, int32_t n);
+
+// Of single trees, for records of type `type`: decision node {threshold (its bits, or the
+// narrow key with the feature above it), index of its children's pair (fp32: << 10 | byte
+// offset of the feature)}, leaf {leaf index, ~class}.  Links hold 21 bits of pairs.
+constexpr int32_t kMaxTreeListNodes = (1 << 22) - 2;
+void build_list(const dt_node *nodes, int32_t n, const std::vector<int32_t> &order, dt_dtype type,
+                uint32_t *out);
+
+// Of a forest's tree (fp32 records, classes below 256): decision node {threshold bits, left
+// child's entry << 10 | byte offset of the feature}, leaf {NaN with the class in its low
+// bits, own entry - 1, << 10}.  Links hold 22 bits of entries.
+constexpr int32_t kMaxForestListNodes = (1 << 22) - 2;
+void build_forest_list(const dt_node *nodes, int32_t n, const std::vector<int32_t> &order,
+                       uint32_t *out);
+
+inline int64_t list_bytes(int32_t n) { return (8 * (int64_t(n) + 1) + 15) & ~int64_t(15); }
+
 // Number of windows, and window levels on the longest path, for window depth D (without
 // building them).
 int64_t count_windows(const dt_node *nodes, const TreeShape &shape, int depth);

@@ -2,11 +2,14 @@
 // AddressSanitizer and UndefinedBehaviorSanitizer.  Random full trees in the breadth-first
 // layout of Procedure 1 are encoded at every window depth 1..8; walking each record
 // through the window tables (D heap steps per window, then the exit) must reach the leaf
-// a direct walk of the tree reaches.  Corrupted arrays must be rejected, not crash.
+// a direct walk of the tree reaches.  So must walks of the node lists, which are breadth-first
+// also for arrays in another order.  Corrupted arrays must be rejected, not crash.
 // Usage: encode_fuzz SEED TREES
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
+#include <cstring>
 #include <limits>
 #include <string>
 #include <vector>
@@ -97,9 +100,140 @@ int window_leaf(const dtree::WindowTables &wt, const float *x) {
     return -3;   // more windows on a path than `levels`
 }
 
+// The same tree with its nodes in depth-first order (siblings stay neighbours).
+std::vector<dt_node> depth_first(const std::vector<dt_node> &t) {
+    std::vector<dt_node> out(t.size());
+    std::vector<std::pair<int, int>> todo{{0, 0}};   // node, its place
+    int next = 1;
+    while (!todo.empty()) {
+        const auto [v, place] = todo.back();
+        todo.pop_back();
+        out[size_t(place)] = t[size_t(v)];
+        if (t[size_t(v)].cls >= 0) continue;
+        out[size_t(place)].left = next;
+        todo.emplace_back(t[size_t(v)].left + 1, next + 1);
+        todo.emplace_back(t[size_t(v)].left, next);
+        next += 2;
+    }
+    return out;
+}
+
+// Leaf index and ~class that a record of `type` reaches in the list of build_list.
+std::pair<uint32_t, int32_t> list_leaf(const std::vector<uint32_t> &list, dt_dtype type,
+                                       const float *x) {
+    size_t at = 1;
+    while (int32_t(list.at(2 * at + 1)) >= 0) {
+        const uint32_t key = list[2 * at], link = list[2 * at + 1];
+        bool right;
+        if (type == DT_F32) {
+            float t;
+            std::memcpy(&t, &key, 4);
+            right = !(x[(link & 1023) / 4] < t);
+        } else if (type == DT_U8) {
+            right = uint32_t(x[key >> 16]) >= (key & 0xFFFF);
+        } else {
+            const uint32_t bits = key << 16;          // bf16
+            float t;
+            std::memcpy(&t, &bits, 4);
+            right = !(x[key >> 16] < t);
+        }
+        at = 2 * size_t(type == DT_F32 ? link >> 10 : link) + size_t(right);
+    }
+    return {list[2 * at], int32_t(list[2 * at + 1])};
+}
+
+// Class that the walk of a forest's list ends in after `depth` steps.
+int forest_list_class(const std::vector<uint32_t> &list, int depth, const float *x) {
+    size_t at = 1;
+    float t = 0.0f;
+    for (int k = 0; k < depth; ++k) {
+        const uint32_t link = list.at(2 * at + 1);
+        std::memcpy(&t, &list[2 * at], 4);
+        at = size_t(link >> 10) + size_t(!(x[(link & 1023) / 4] < t));
+    }
+    return int(list.at(2 * at) & 0xFF);
+}
+
 int fail(const char *what, int a, int b) {
     std::fprintf(stderr, "FAIL %s (%d, %d)\n", what, a, b);
     return 1;
+}
+
+// Lists of one tree, and of the same tree depth-first: the walks, the order, the sizes.
+int check_lists(const std::vector<dt_node> &tree, const dtree::TreeShape &shape, int F,
+                const std::vector<float> &x) {
+    const std::vector<dt_node> orders[] = {tree, depth_first(tree)};
+    for (int o = 0; o < 2; ++o) {
+        const std::vector<dt_node> &t = orders[o];
+        const int n = int(t.size());
+        const std::vector<int32_t> order = dtree::breadth_first_order(t.data(), n);
+        std::vector<uint32_t> list(size_t(dtree::list_bytes(n) / 4), 0u);
+        for (dt_dtype type : {DT_F32, DT_BF16, DT_U8}) {
+            dtree::build_list(t.data(), n, order, type, list.data());
+            uint32_t pair = 0;       // breadth-first: the decision nodes' pairs in sequence
+            for (int i = 1; i <= n; ++i) {
+                const uint32_t link = list[size_t(2 * i + 1)];
+                if (int32_t(link) >= 0 && (type == DT_F32 ? link >> 10 : link) != ++pair)
+                    return fail("list order", o, i);
+            }
+            for (int r = 0; r < 64; ++r) {
+                std::vector<float> row(x.begin() + r * (F + 1), x.begin() + (r + 1) * (F + 1));
+                for (float &v : row) {               // records of the type, widened
+                    if (type == DT_U8) v = v > 0.0f && v <= 1.0f ? std::floor(v * 255.0f) : 0.0f;
+                    uint32_t bits;
+                    std::memcpy(&bits, &v, 4);
+                    if (type == DT_BF16 && v == v) bits &= 0xFFFF0000u;
+                    std::memcpy(&v, &bits, 4);
+                }
+                const int leaf = direct_leaf(t, row.data());
+                const auto got = list_leaf(list, type, row.data());
+                if (int(got.first) != leaf || ~got.second != t[size_t(leaf)].cls)
+                    return fail("list walk leaf", int(got.first), leaf);
+            }
+        }
+        std::vector<dt_node> small = t;             // forests: at most 64 classes
+        for (dt_node &v : small)
+            if (v.cls >= 0) v.cls %= 64;
+        dtree::build_forest_list(small.data(), n, order, list.data());
+        for (int r = 0; r < 64; ++r) {
+            const float *row = x.data() + r * (F + 1);
+            const int want = small[size_t(direct_leaf(small, row))].cls;
+            for (int extra : {0, 3})                // a walk that is over stays at its leaf
+                if (forest_list_class(list, std::max(1, shape.depth) + extra, row) != want)
+                    return fail("forest list walk class", r, want);
+        }
+    }
+    return 0;
+}
+
+// Lists at the largest size that their links can hold: every decision node leads to its
+// children.
+int check_list_limits() {
+    static_assert(dtree::kMaxTreeListNodes == dtree::kMaxForestListNodes, "one tree serves both");
+    const int n = dtree::kMaxTreeListNodes - 1;     // a full tree has an odd number of nodes
+    std::vector<dt_node> t(static_cast<size_t>(n));
+    for (int i = 0; i < n; ++i)
+        t[size_t(i)] = 2 * i + 2 < n ? dt_node{255, 0.5f, 2 * i + 1, -1} : dt_node{0, 0.0f, -1, 63};
+    const std::vector<int32_t> order = dtree::breadth_first_order(t.data(), n);
+    std::vector<uint32_t> list(size_t(dtree::list_bytes(n) / 4), 0u);
+    for (dt_dtype type : {DT_F32, DT_U8}) {
+        dtree::build_list(t.data(), n, order, type, list.data());
+        for (int i = 0; i < n; ++i) {
+            const uint32_t link = list[2 * (size_t(i) + 1) + 1];
+            if (t[size_t(i)].cls >= 0 ? link != ~63u
+                                      : int32_t(link) < 0 ||
+                                            (type == DT_F32 ? link >> 10 : link) != uint32_t(i + 1) ||
+                                            (type == DT_F32 && (link & 1023) != 1020))
+                return fail("list link", int(type), i);
+        }
+    }
+    dtree::build_forest_list(t.data(), n, order, list.data());
+    for (int i = 0; i < n; ++i) {
+        const uint32_t link = list[2 * (size_t(i) + 1) + 1];
+        if (link != (t[size_t(i)].cls >= 0 ? uint32_t(i) << 10 : uint32_t(2 * i + 2) << 10 | 1020))
+            return fail("forest list link", i, int(link));
+    }
+    return 0;
 }
 
 }  // namespace
@@ -109,6 +243,7 @@ int main(int argc, char **argv) {
     const int trees = argc > 2 ? std::atoi(argv[2]) : 200;
     const int sizes[] = {0, 1, 2, 3, 7, 15, 40, 63, 64, 200, 1000, 3000};
     long checked = 0;
+    if (const int bad = check_list_limits()) return bad;
     for (int it = 0; it < trees; ++it) {
         const int F = 1 + below(40), C = 1 + below(300);
         const int n_int = sizes[below(int(sizeof(sizes) / sizeof(sizes[0])))];
@@ -141,6 +276,7 @@ int main(int argc, char **argv) {
                 ++checked;
             }
         }
+        if (const int bad = check_lists(t, shape, F, x)) return bad;
         // corrupted copies: validation must reject them
         if (n_int > 0) {
             for (int kind = 0; kind < 5; ++kind) {
