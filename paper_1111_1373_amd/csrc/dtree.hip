@@ -12,6 +12,7 @@
 #include <vector>
 
 #include "dtree.h"
+#include "dtree_probe.h"
 #include "encode.hpp"
 #include "kernels.hpp"
 #include "library.hpp"
@@ -36,9 +37,6 @@ dt_status hip_fail(hipError_t e, const char *what) {
     return fail(DT_ERR_HIP, std::string(what) + ": " + hipGetErrorString(e));
 }
 
-// Most LDS a node list takes; the nodes of larger lists' lower levels stay in global memory.
-constexpr int64_t kListLdsBytes = 48 * 1024;
-
 // Device resources of one window encoding: the exits, and the slots once per record
 // type (8-byte fp32 slots; 4-byte words on each narrow type's grid).
 struct Encoding {
@@ -54,7 +52,22 @@ struct Encoding {
     // the lists, of slot_bytes each, and the first list_lds_bytes of one go to the LDS.
     bool list = false;
     int64_t table_bytes(int elem_type) const {
-        return list ? std::min(slot_bytes[elem_type], kListLdsBytes) : slot_bytes[elem_type] + exit_bytes;
+        return list ? std::min(slot_bytes[elem_type], dtree::kListLdsBytes)
+                    : slot_bytes[elem_type] + exit_bytes;
+    }
+    // Sizes of the window tables, and of a node list of n nodes.
+    void size_windows(int window_depth, int64_t windows, int32_t window_levels) {
+        depth = window_depth;
+        n_windows = int32_t(windows);
+        levels = window_levels;
+        const int64_t n_slots = windows << window_depth;
+        exit_bytes = align16(n_slots * 4);
+        for (int xt = 0; xt < dtree::kElemTypes; ++xt)
+            slot_bytes[xt] = align16(n_slots * (xt == dtree::kXF32 ? 8 : 4));
+    }
+    void size_list(int32_t n) {
+        list = true;
+        for (int64_t &b : slot_bytes) b = dtree::list_bytes(n);
     }
 };
 
@@ -80,15 +93,11 @@ dt_status query_device(DeviceCaps *caps) {
 }
 
 dt_status upload_encoding(const dtree::WindowTables &wt, Encoding *enc) {
-    enc->depth = wt.depth;
-    enc->n_windows = wt.n_windows;
-    enc->levels = wt.levels;
+    enc->size_windows(wt.depth, wt.n_windows, wt.levels);
     const int64_t n_slots = int64_t(wt.n_windows) * wt.slots;
-    enc->exit_bytes = align16(n_slots * 4);
     int64_t off[dtree::kElemTypes];
     int64_t total = 0;
     for (int xt = 0; xt < dtree::kElemTypes; ++xt) {
-        enc->slot_bytes[xt] = align16(n_slots * (xt == dtree::kXF32 ? 8 : 4));
         off[xt] = total;
         total += enc->slot_bytes[xt] + (xt == dtree::kXF32 ? 2 * enc->exit_bytes : 0);
     }
@@ -124,15 +133,13 @@ dt_status upload_encoding(const dtree::WindowTables &wt, Encoding *enc) {
 
 // Upload the tree as node lists, one per record type (see walk_list).
 dt_status upload_list(const dt_node *nodes, int32_t n, Encoding *enc) {
-    enc->list = true;
-    const int64_t size = dtree::list_bytes(n);
+    enc->size_list(n);
+    const int64_t size = enc->slot_bytes[0];
     const std::vector<int32_t> order = dtree::breadth_first_order(nodes, n);
     std::vector<uint32_t> host(size_t(size / 4) * dtree::kElemTypes, 0u);
-    for (int xt = 0; xt < dtree::kElemTypes; ++xt) {
-        enc->slot_bytes[xt] = size;
+    for (int xt = 0; xt < dtree::kElemTypes; ++xt)
         dtree::build_list(nodes, n, order, static_cast<dt_dtype>(xt),
                           host.data() + size_t(size / 4) * size_t(xt));
-    }
     hipError_t e = hipMalloc(&enc->d_mem, host.size() * 4);
     if (e != hipSuccess) {
         enc->d_mem = nullptr;
@@ -144,30 +151,6 @@ dt_status upload_list(const dt_node *nodes, int32_t n, Encoding *enc) {
         enc->d_slots[xt] = reinterpret_cast<const int4 *>(static_cast<unsigned char *>(enc->d_mem) +
                                                           size * xt);
     return DT_OK;
-}
-
-// Whether the data decomposition walks the tree as a node list.  Windows pad every path to
-// whole windows and end each with an exit read, and sparse trees leave most of their slots
-// empty; the list takes a path's own steps and 8 bytes a node, at a slightly longer step (the
-// loop's test and the child's index).  So: the list where the windows do not fit their LDS
-// budget (20,000 random decision nodes, 1,000,000 x 16: 21.6 us against 32.1 us), or need
-// several levels (4,000 nodes: 11.6 us against 19.3 us; 300 nodes, 3,000,001 x 19: 37.6 us
-// against 40.1 us) unless the tree is chain-like, all of whose paths are long (a chain of
-// 64: 27.2 us against 24.1 us), or, in one level, take more than four times the list's
-// bytes (the 31-node tree of depth 11).  Only with the default window depth; n_features as
-// far as the kernels go.
-bool use_list(const dt_node *nodes, const dtree::TreeShape &shape, int32_t n_features,
-              const dt_tree_options *opt, int data_depth) {
-    if ((opt && opt->data_window_depth) || shape.n_nodes > dtree::kMaxTreeListNodes ||
-        n_features > dtree::kMaxRowStride)
-        return false;
-    const int64_t windows =
-        dtree::table_bytes(dtree::count_windows(nodes, shape, data_depth), data_depth);
-    if (windows > dtree::data_table_budget(n_features)) return true;
-    int log2_nodes = 1;
-    while ((int64_t(1) << log2_nodes) < shape.n_nodes) ++log2_nodes;
-    if (dtree::count_levels(nodes, shape, data_depth) > 1) return shape.depth <= 4 * log2_nodes;
-    return windows > 4 * 8 * (int64_t(shape.n_nodes) + 1);
 }
 
 void free_encoding(Encoding *enc) {
@@ -233,6 +216,7 @@ struct Plan {
     int out_cap = 0;          // single-tree kernels: result tiles buffered per wavefront
     dtree::TileShape tile;    // single-tree kernels: the record tile
     int tables_in_lds = 0;
+    int enc = 0;              // single-tree kernels: the encoding (dt_tree::enc)
     dt_status status = DT_ERR_UNSUPPORTED;
     std::string why;
 };
@@ -367,13 +351,12 @@ struct dt_tree {
     dtree::TreeShape shape;
     int32_t n_features = 0, n_classes = 0;
     int path_hops = kDefaultPathHops;
-    Encoding enc[2];              // data windows, speculative windows (also the path kernel's)
+    // data windows, speculative windows (also the path kernel's), node list (data walk); those
+    // that a plan uses are uploaded
+    Encoding enc[3];
     // [algo][record element type][load mode][uint8 / int32 results]
     Plan plan[3][dtree::kElemTypes][dtree::kLoadModes][2];
 };
-
-// Encoding an algorithm runs on: the path kernel reduces the speculative windows.
-static inline int encoding_of(int algo) { return algo == DT_ALGO_DATA ? 0 : 1; }
 
 static bool single_tree_algo(dt_algo algo) {
     return algo == DT_ALGO_DATA || algo == DT_ALGO_SPECULATIVE || algo == DT_ALGO_PATH;
@@ -464,7 +447,7 @@ dt_status classify_impl(const dt_tree *tree, const void *d_x, dt_dtype x_type, i
     const int mode = load_mode_for(d_x, x_type, ld, tree->n_features);
     const Plan &plan = tree->plan[algo][x_type][mode][out_kind == DT_OUT_CLASS_U8 ? 0 : 1];
     if (plan.status != DT_OK) return fail(plan.status, plan.why);
-    const Encoding &enc = tree->enc[encoding_of(algo)];
+    const Encoding &enc = tree->enc[plan.enc];
 
     dtree::KArgs a{};
     a.in = make_tile_rows(d_x, x_type, n, ld, tree->n_features, plan.tile);
@@ -491,6 +474,35 @@ dt_status classify_impl(const dt_tree *tree, const void *d_x, dt_dtype x_type, i
     return DT_OK;
 }
 
+void destroy_impl(dt_tree *t) {
+    if (!t) return;
+    for (Encoding &e : t->enc) free_encoding(&e);
+    delete t;
+}
+
+// Plan of the data decomposition for records of type `xt`: over windows or over the node
+// list (data_walk_for has the rule).  `plan_on` plans for one encoding.
+template <class PlanOn>
+void plan_data(const dt_tree &t, int xt, bool listable, PlanOn plan_on, Plan *plan) {
+    const Encoding &windows = t.enc[0];
+    const int64_t list_bytes = t.enc[2].slot_bytes[xt];
+    const dtree::DataWalk walk =
+        listable ? dtree::data_walk_for(t.shape, windows.levels, windows.table_bytes(xt), list_bytes)
+                 : dtree::DataWalk::kWindows;
+    Plan list;
+    if (walk != dtree::DataWalk::kWindows) plan_on(2, dtree::kAlgoList, &list);
+    if (walk == dtree::DataWalk::kList && list.status == DT_OK) {
+        *plan = list;
+        return;
+    }
+    plan_on(0, DT_ALGO_DATA, plan);
+    if (list.status != DT_OK) return;
+    if (plan->status != DT_OK || !plan->tables_in_lds ||
+        dtree::list_is_faster(t.shape, windows.levels, windows.depth, list_bytes,
+                              plan->waves * plan->blocks_per_cu, list.waves * list.blocks_per_cu))
+        *plan = list;
+}
+
 dt_status create_impl(const dt_node *nodes, int32_t n_nodes, int32_t n_features,
                       int32_t n_classes, const dt_tree_options *opt, dt_tree **out) {
     if (!out) return fail(DT_ERR_INVALID_ARG, "out is NULL");
@@ -510,26 +522,15 @@ dt_status create_impl(const dt_node *nodes, int32_t n_nodes, int32_t n_features,
     if (opt && opt->path_hops) t->path_hops = opt->path_hops;
     int depth[2];
     window_depths(nodes, shape, n_features, opt, &depth[0], &depth[1]);
-    for (int e = 0; e < 2; ++e) {
-        if (e == 0 && use_list(nodes, shape, n_features, opt, depth[0])) {
-            t->enc[0].depth = depth[0];
-            t->enc[0].n_windows = int32_t(dtree::count_windows(nodes, shape, depth[0]));
-            t->enc[0].levels = dtree::count_levels(nodes, shape, depth[0]);
-            st = upload_list(nodes, n_nodes, &t->enc[0]);
-        } else {
-            dtree::WindowTables wt;
-            dtree::build_windows(nodes, shape, depth[e], &wt);
-            st = upload_encoding(wt, &t->enc[e]);
-        }
-        if (st != DT_OK) {
-            free_encoding(&t->enc[0]);
-            free_encoding(&t->enc[1]);
-            delete t;
-            return st;
-        }
-    }
+    t->enc[0].size_windows(depth[0], dtree::count_windows(nodes, shape, depth[0]),
+                           dtree::count_levels(nodes, shape, depth[0]));
+    t->enc[1].size_windows(depth[1], dtree::count_windows(nodes, shape, depth[1]),
+                           dtree::count_levels(nodes, shape, depth[1]));
+    // lists only with the default window depth
+    const bool listable = !(opt && opt->data_window_depth) && n_nodes <= dtree::kMaxTreeListNodes;
+    if (listable) t->enc[2].size_list(n_nodes);
+    bool used[3] = {false, true, false};
     for (int algo = 0; algo < 3; ++algo) {
-        const Encoding &enc = t->enc[encoding_of(algo)];
         for (int xt = 0; xt < dtree::kElemTypes; ++xt) {
             for (int m = 0; m < dtree::kLoadModes; ++m) {
                 Plan *pl = t->plan[algo][xt][m];
@@ -545,21 +546,39 @@ dt_status create_impl(const dt_node *nodes, int32_t n_nodes, int32_t n_features,
                 if (m == dtree::kLoadExact && !exact_rows(n_features, es)) continue;
                 if (m == dtree::kLoadFlat && (n_features * es) % 16 == 0) continue;
                 if (m == dtree::kLoadBytes && es == 4) continue;
-                for (int o = 0; o < 2; ++o)
-                    make_plan(t->caps, enc.list ? int(dtree::kAlgoList) : algo, xt, n_features, m, enc.depth, enc.table_bytes(xt),
-                              o == 0 ? 1 : 4, opt ? opt->waves_per_cu : 0, &pl[o]);
+                for (int o = 0; o < 2; ++o) {
+                    const auto plan_on = [&](int e, int kernel_algo, Plan *p) {
+                        p->enc = e;
+                        make_plan(t->caps, kernel_algo, xt, n_features, m, t->enc[e].depth,
+                                  t->enc[e].table_bytes(xt), o == 0 ? 1 : 4,
+                                  opt ? opt->waves_per_cu : 0, p);
+                    };
+                    if (algo == DT_ALGO_DATA)
+                        plan_data(*t, xt, listable, plan_on, &pl[o]);
+                    else
+                        plan_on(1, algo, &pl[o]);
+                    used[pl[o].enc] = true;
+                }
             }
+        }
+    }
+    if (!used[2]) used[0] = true;
+    for (int e = 0; e < 3; ++e) {
+        if (!used[e]) continue;
+        if (e == 2) {
+            st = upload_list(nodes, n_nodes, &t->enc[2]);
+        } else {
+            dtree::WindowTables wt;
+            dtree::build_windows(nodes, shape, depth[e], &wt);
+            st = upload_encoding(wt, &t->enc[e]);
+        }
+        if (st != DT_OK) {
+            destroy_impl(t);
+            return st;
         }
     }
     *out = t;
     return DT_OK;
-}
-
-void destroy_impl(dt_tree *t) {
-    if (!t) return;
-    free_encoding(&t->enc[0]);
-    free_encoding(&t->enc[1]);
-    delete t;
 }
 
 // ---- forests ---------------------------------------------------------------------------
@@ -991,6 +1010,17 @@ dt_status forest_create_impl(const dt_node *nodes, const int32_t *offsets, int32
     return DT_OK;
 }
 
+// Plans of a call's load mode, by split, and how its tiles are spread over them.
+ForestSpread spread_call(const dt_forest &f, const float *d_x, int64_t n, int64_t ld, dt_algo algo,
+                         const ForestPlan *(&plans)[kForestSplits]) {
+    // a split kernel reads exact rows as any others of a multiple of 16 bytes
+    const int mode = dtree::forest_load_mode(d_x, ld, f.n_features);
+    const int split_mode = mode == dtree::kLoadExact ? int(dtree::kLoadRows) : mode;
+    for (int sp = 0; sp < kForestSplits; ++sp)
+        plans[sp] = &f.plan[algo][sp == 0 ? mode : split_mode][sp];
+    return spread_forest(plans, f.caps.n_cu, (n + dtree::kTileRows - 1) / dtree::kTileRows);
+}
+
 dt_status forest_classify_impl(const dt_forest *f, const float *d_x, int64_t n, int64_t ld,
                                void *d_out, dt_output out_kind, dt_algo algo, void *stream) {
     if (!f) return fail(DT_ERR_INVALID_ARG, "forest is NULL");
@@ -1012,15 +1042,10 @@ dt_status forest_classify_impl(const dt_forest *f, const float *d_x, int64_t n, 
     if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
     if (dev != f->caps.device)
         return fail(DT_ERR_INVALID_ARG, "current device differs from the forest's device");
-    // a split kernel reads exact rows as any others of a multiple of 16 bytes
-    const int mode = dtree::forest_load_mode(d_x, ld, f->n_features);
-    const int split_mode = mode == dtree::kLoadExact ? int(dtree::kLoadRows) : mode;
     const ForestPlan *plans[kForestSplits];
-    for (int sp = 0; sp < kForestSplits; ++sp)
-        plans[sp] = &f->plan[algo][sp == 0 ? mode : split_mode][sp];
+    const ForestSpread spread = spread_call(*f, d_x, n, ld, algo, plans);
     const ForestEncoding &enc = f->enc[algo];
     const int64_t tiles = (n + dtree::kTileRows - 1) / dtree::kTileRows;
-    const ForestSpread spread = spread_forest(plans, f->caps.n_cu, tiles);
 
     for (int part = 0; part < 2; ++part) {
         const int64_t first = part == 0 ? 0 : spread.lead, end = part == 0 ? spread.lead : tiles;
@@ -1247,6 +1272,42 @@ dt_status dt_forest_classify(const dt_forest *f, const float *d_x, int64_t n, in
     } catch (...) {
         return fail(DT_ERR_INVALID_ARG, "unexpected internal error");
     }
+}
+
+dt_status dt_probe_tree_list(const dt_tree *t, const void *d_x, dt_dtype x_type, int64_t ld,
+                             dt_output out_kind, dt_algo algo, int32_t *list) {
+    dt_launch_info info;
+    const dt_status st = dt_tree_launch_info(t, d_x, x_type, ld, out_kind, algo, &info);
+    if (st != DT_OK) return st;
+    if (!list) return fail(DT_ERR_INVALID_ARG, "null argument");
+    const Plan &plan = t->plan[algo][x_type][info.load_mode][out_kind == DT_OUT_CLASS_U8 ? 0 : 1];
+    *list = t->enc[plan.enc].list ? 1 : 0;
+    return DT_OK;
+}
+
+dt_status dt_probe_forest_spread(const dt_forest *f, const float *d_x, int64_t n, int64_t ld,
+                                 dt_algo algo, dt_forest_spread *info) {
+    g_last_error.clear();
+    if (!f || !info || n < 1 || ld < f->n_features ||
+        (algo != DT_ALGO_DATA && algo != DT_ALGO_SPECULATIVE))
+        return fail(DT_ERR_INVALID_ARG, "null argument, n < 1, ld < n_features or unknown algo");
+    if (f->n_features > dtree::kMaxRowStride) return fail(DT_ERR_UNSUPPORTED, "n_features > 256");
+    const ForestPlan *plans[kForestSplits];
+    const ForestSpread spread = spread_call(*f, d_x, n, ld, algo, plans);
+    *info = dt_forest_spread{};
+    info->list = f->enc[algo].exit_mode == dtree::kExitList ? 1 : 0;
+    info->whole_tiles = spread.lead;
+    info->split_tiles = (n + dtree::kTileRows - 1) / dtree::kTileRows - spread.lead;
+    if (info->whole_tiles > 0) {
+        info->whole_waves = plans[0]->waves;
+        info->whole_blocks_per_cu = plans[0]->blocks_per_cu;
+    }
+    if (info->split_tiles > 0) {
+        info->split_waves = plans[spread.split]->waves;
+        info->split_blocks_per_cu = plans[spread.split]->blocks_per_cu;
+        info->waves_per_tile = 1 << spread.split;
+    }
+    return DT_OK;
 }
 
 }  // extern "C"

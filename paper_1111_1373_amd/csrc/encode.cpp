@@ -296,6 +296,27 @@ void build_forest_list(const dt_node *nodes, int32_t n, const std::vector<int32_
     }
 }
 
+DataWalk data_walk_for(const TreeShape &shape, int32_t levels, int64_t window_bytes,
+                       int64_t list_bytes) {
+    int log2_nodes = 1;
+    while ((int64_t(1) << log2_nodes) < shape.n_nodes) ++log2_nodes;
+    if (levels > 1) {
+        if (shape.depth >= 3 * log2_nodes && window_bytes <= kListLdsBytes) return DataWalk::kWindows;
+        return list_bytes <= kListLdsBytes ? DataWalk::kList : DataWalk::kEither;
+    }
+    if (window_bytes > kListLdsBytes) return DataWalk::kEither;
+    const bool chain = shape.depth >= 2 * log2_nodes && window_bytes <= 16 * 1024;
+    return window_bytes > 4 * list_bytes && !chain ? DataWalk::kList : DataWalk::kWindows;
+}
+
+bool list_is_faster(const TreeShape &shape, int32_t levels, int window_depth, int64_t list_bytes,
+                    int waves_windows, int waves_list) {
+    const double below = std::max(0.0, std::log2(double(list_bytes) / double(kListLdsBytes)));
+    const double list = (double(shape.depth) + 4.0 * below) / std::sqrt(double(waves_list));
+    const double windows = double(levels) * double(window_depth + 1) / std::sqrt(double(waves_windows));
+    return list <= windows;
+}
+
 int64_t data_table_budget(int32_t n_features) {
     int rs = 4;
     while (rs < n_features) rs <<= 1;

@@ -88,6 +88,39 @@ void build_forest_list(const dt_node *nodes, int32_t n, const std::vector<int32_
 
 inline int64_t list_bytes(int32_t n) { return (8 * (int64_t(n) + 1) + 15) & ~int64_t(15); }
 
+// Most LDS a node list takes; the nodes of larger lists' lower levels stay in global memory.
+constexpr int64_t kListLdsBytes = 48 * 1024;
+
+// Whether the data decomposition of a single tree walks windows or the node list, for tables
+// of these bytes (windows take 12 bytes a slot for fp32 records and 8 for narrow ones, the
+// list 8 a node).  Windows pad every path to whole windows and end each with an exit read,
+// and sparse trees leave most of their slots empty; the list takes a path's own steps, at a
+// slightly longer step (the loop's test and the child's index).  Measured over 1,000,000
+// records, the list against the windows:
+//   Several levels of windows: the list (300 random decision nodes, 32 fp32 features, 21.3
+//     against 21.9 us; 3,500 nodes, 16 features 15.6 against 20.2 us), unless the tree is
+//     chain-like, all of whose paths are long (depth of three times log2 of the nodes and
+//     more: a chain of 20, 19 features, 18.1 against 16.5 us).
+//   One level: the windows, whose tables then are about as large as the list's (a complete
+//     tree of depth 12 on 200 fp16 features 61.6 against 81.0 us), unless they take more than
+//     four times the list's bytes (20 random nodes, 8 fp32 features 0.84 of the time); chains
+//     (depth of twice log2 of the nodes and more: 10 decision nodes 1.05) keep up to 16 KiB.
+//   Lists, or one level of windows, of more than 48 KiB (kEither): by list_is_faster.
+enum class DataWalk { kWindows, kList, kEither };
+DataWalk data_walk_for(const TreeShape &shape, int32_t levels, int64_t window_bytes,
+                       int64_t list_bytes);
+
+// Of the two with windows in the LDS, by the steps of a path and the wavefronts that a CU
+// holds with each: the part of a list that is not in the LDS costs about four steps for each
+// of its levels, and the time of a step falls with about the root of the wavefronts.  The
+// choice was within 19% of the better walk on each of 663 trees, widths and types measured
+// (1,000,000 records; 651 of them within 3%): a complete tree of depth 13, 64 fp32 features
+// 47.9 us with the list and 41.2 with windows, 8 features (half the wavefronts) 11.5 and 13.0;
+// depth 14, 4 uint8 features 10.4 and 12.1 (windows taken); 5,000 random nodes, 64 fp32
+// features 43.8 and 63.7 us.
+bool list_is_faster(const TreeShape &shape, int32_t levels, int window_depth, int64_t list_bytes,
+                    int waves_windows, int waves_list);
+
 // Number of windows, and window levels on the longest path, for window depth D (without
 // building them).
 int64_t count_windows(const dt_node *nodes, const TreeShape &shape, int depth);

@@ -236,6 +236,48 @@ int check_list_limits() {
     return 0;
 }
 
+// Which trees walk lists: complete trees keep one level of windows while as many wavefronts
+// fit beside them, also where the list alone would be over its share of the LDS.
+int check_list_rule() {
+    struct Want {
+        int depth, nodes, levels, window_depth;
+        int64_t slots;
+        int slot_bytes, waves_windows, waves_list;   // wavefronts of a CU with either
+        bool list;
+    };
+    const Want want[] = {
+        {12, 8191, 1, 12, 4096, 12, 6, 6, false},      // complete, 200 fp32 features
+        {12, 8191, 1, 12, 4096, 8, 4, 4, false},       // 200 fp16 features
+        {13, 16383, 1, 13, 8192, 12, 3, 4, false},     // complete, 64 fp32 features
+        {13, 16383, 1, 13, 8192, 12, 8, 14, false},    // 16
+        {13, 16383, 1, 13, 8192, 12, 8, 16, true},     // 8: half the wavefronts
+        {13, 16383, 1, 13, 8192, 8, 16, 16, false},    // 16 uint8 features
+        {14, 32767, 1, 14, 16384, 8, 7, 14, false},    // 64 uint8 features
+        {14, 32767, 1, 14, 16384, 8, 3, 8, true},      // 64 fp16 features
+        {19, 601, 4, 5, 1920, 12, 8, 8, true},         // 300 random nodes
+        {9, 41, 1, 9, 512, 12, 32, 32, true},          // 20 random nodes
+        {29, 10001, 15, 2, 9988, 12, 3, 7, true},      // 5,000 random nodes
+        {14, 20157, 4, 4, 12000, 8, 4, 4, false},      // grown, 200 fp16 features
+        {14, 20157, 4, 4, 12000, 8, 8, 14, true},      // 32
+        {10, 21, 1, 10, 1024, 8, 32, 32, false},       // chains
+        {20, 41, 2, 10, 2048, 12, 8, 8, false},
+        {11, 31, 1, 11, 2048, 12, 16, 16, true},       // 24 KiB of windows for 15 nodes
+    };
+    for (const Want &w : want) {
+        dtree::TreeShape shape;
+        shape.depth = w.depth;
+        shape.n_nodes = w.nodes;
+        const int64_t list = dtree::list_bytes(w.nodes);
+        const auto walk = dtree::data_walk_for(shape, w.levels, w.slots * w.slot_bytes, list);
+        const bool got = walk == dtree::DataWalk::kEither
+                             ? dtree::list_is_faster(shape, w.levels, w.window_depth, list,
+                                                     w.waves_windows, w.waves_list)
+                             : walk == dtree::DataWalk::kList;
+        if (got != w.list) return fail("list rule", w.depth, w.nodes);
+    }
+    return 0;
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
@@ -244,6 +286,7 @@ int main(int argc, char **argv) {
     const int sizes[] = {0, 1, 2, 3, 7, 15, 40, 63, 64, 200, 1000, 3000};
     long checked = 0;
     if (const int bad = check_list_limits()) return bad;
+    if (const int bad = check_list_rule()) return bad;
     for (int it = 0; it < trees; ++it) {
         const int F = 1 + below(40), C = 1 + below(300);
         const int n_int = sizes[below(int(sizeof(sizes) / sizeof(sizes[0])))];

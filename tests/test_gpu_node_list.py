@@ -22,10 +22,20 @@ def dt():
     return dtree
 
 
+def _walks_list(dt, tree, x, out_kind="class_u8"):
+    import ctypes
+    got = ctypes.c_int32(-1)
+    dt._check(dt._lib.dt_probe_tree_list(tree._h, ctypes.c_void_p(x.data_ptr()), dt._x_type(x),
+                                         ctypes.c_int64(x.stride(0)), dt.OUT_KINDS[out_kind], 0,
+                                         ctypes.byref(got)), "dt_probe_tree_list")
+    return got.value == 1
+
+
 @pytest.mark.parametrize("x_type", ["f32", "f16", "bf16", "u8"])
 @pytest.mark.parametrize("shape,size", [("random", 20), ("random", 3070), ("random", 3071),
                                         ("random", 3072), ("random", 3073), ("random", 9000),
-                                        ("chain", 70), ("paper", 11), ("complete", 14)])
+                                        ("chain", 70), ("paper", 11), ("complete", 12),
+                                        ("complete", 13), ("complete", 14)])
 @pytest.mark.parametrize("F,pad", [(16, 0), (19, 0), (150, 3)])
 def test_node_lists(dt, x_type, shape, size, F, pad):
     r = np.random.Generator(np.random.PCG64(size * 1000 + F))
@@ -52,6 +62,24 @@ def test_node_lists(dt, x_type, shape, size, F, pad):
     rows = rows if x_type == "f32" else TU.widen(rows, x_type)
     leaf, cls = oracle.tree_leaves(nodes, rows, F), oracle.tree_classes(nodes, rows, F)
     tree = dt.Tree(nodes, F, C)
+    walks_list = _walks_list(dt, tree, xd)
+    if shape == "random" and 3000 < size < 4000:
+        assert walks_list
+    if shape == "chain" or (shape, size) == ("complete", 12):
+        assert not walks_list
     for n in (1, 65, 3000):
         np.testing.assert_array_equal(tree.classify(xd[:n], out_kind="leaf_i32").cpu().numpy(), leaf[:n])
         np.testing.assert_array_equal(tree.classify(xd[:n], out_kind="class_i32").cpu().numpy(), cls[:n])
+
+
+@pytest.mark.parametrize("x_type", ["f32", "f16", "u8"])
+@pytest.mark.parametrize("depth,F", [(12, 200), (13, 64), (13, 16)])
+def test_complete_trees_keep_one_window(dt, x_type, depth, F):
+    """One level of windows that fits the LDS whole stays, also where the list of the same
+    tree is over its share (complete depth 13, 1,000,000 x 64 fp32: 40.0 us against 47.5 us)."""
+    r = np.random.Generator(np.random.PCG64(depth))
+    tree = dt.Tree(W.narrow_tree(W.complete_tree(r, depth, F, 7), x_type), F, 7)
+    x = torch.zeros((64, F), dtype={"f32": torch.float32, "f16": torch.float16,
+                                    "u8": torch.uint8}[x_type], device="cuda")
+    for out_kind in ("class_u8", "class_i32"):
+        assert not _walks_list(dt, tree, x, out_kind)
