@@ -121,3 +121,20 @@ def test_forest_base_between_words(dt, F, pad, algo):
             f._h, block.data_ptr() + shift, n, ld, out.data_ptr(), dt.OUT_KINDS["class_i32"],
             dt.ALGOS[algo], torch.cuda.current_stream().cuda_stream), "dt_forest_classify")
         np.testing.assert_array_equal(out.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("F", [1, 3, 4, 6, 8, 16, 19, 64, 200])
+@pytest.mark.parametrize("size", [30, 1200, 2500, 3500])
+def test_planned_workgroups_fit_the_lds(dt, F, size):
+    """The workgroups that a plan counts on are resident together: a workgroup's LDS is
+    allocated in pieces of 1,280 bytes, of which a CU has 128."""
+    r = np.random.Generator(np.random.PCG64(size + F))
+    nodes = W.random_full_tree(r, size, F, 9)
+    for depth in (0, 4):
+        tree = dt.Tree(nodes, F, 9, data_window_depth=depth)
+        for x_type in (torch.float32, torch.float16, torch.uint8):
+            x = torch.zeros((64, F), dtype=x_type, device="cuda")
+            for algo in ("data", "speculative"):
+                for out_kind in ("class_u8", "leaf_i32"):
+                    li = tree.launch_info(x, algo=algo, out_kind=out_kind)
+                    assert li["workgroups_per_cu"] * -(-li["lds_bytes"] // 1280) <= 128, li
