@@ -383,7 +383,8 @@ struct ForestEncoding {
     std::vector<int4> chunks;    // host copy of the chunks, plan after plan
     int64_t table_bytes = 0;
     int64_t max_tree_bytes = 0;
-    int32_t max_levels = 0;      // most steps of a path: window levels x depth, or the depth
+    int32_t max_levels = 0;      // most steps of a path: window levels x depth
+    std::vector<double> steps;   // data walks: steps that a wavefront takes in each tree
     int exit_mode = dtree::kExitInt32;
 };
 
@@ -396,12 +397,15 @@ struct ForestPlan {
     int lds_bytes = 0;
     int chunk_lds_bytes = 0;     // LDS reserved for one chunk (0: tables read in place)
     int first_chunk = 0, n_chunks = 0;
-    double round_cost = 0.0;
+    std::vector<double> round_cost;   // estimated cycles of a round with b groups on a CU, at
+                                      // b - 1 (b up to blocks_per_cu),
+    double first_cost = 0.0;          // and of what comes before the first round
     dt_status status = DT_ERR_UNSUPPORTED;
     std::string why = "no kernel instance for this configuration";
 };
 
 constexpr int kForestSplits = 5;   // 1, 2, 4, 8 or 16 wavefronts per tile
+constexpr int kForestList = 2;     // the node lists' place among a forest's encodings
 
 void free_forest_encoding(ForestEncoding *e) {
     if (e->d_mem) (void)hipFree(e->d_mem);
@@ -414,8 +418,10 @@ struct dt_forest {
     DeviceCaps caps;
     int32_t n_trees = 0, n_features = 0, n_classes = 0;
     int vote_words = 0;
-    ForestEncoding enc[2];       // [DT_ALGO_DATA], [DT_ALGO_SPECULATIVE]
-    ForestPlan plan[2][dtree::kForestLoadModes][kForestSplits];   // [algo][load mode][log2 split]
+    // data windows, speculative windows, node lists (data walk); a forest may have data
+    // windows and lists, weighed at each call
+    ForestEncoding enc[3];
+    ForestPlan plan[3][dtree::kForestLoadModes][kForestSplits];   // [encoding][load mode][log2 split]
 };
 
 namespace {
@@ -588,6 +594,8 @@ dt_status create_impl(const dt_node *nodes, int32_t n_nodes, int32_t n_features,
 
 // ---- forests ---------------------------------------------------------------------------
 
+constexpr int64_t kMaxForestBytes = (int64_t(1) << 31) - 1;   // of tables (int32 offsets)
+
 // Speculative forests use windows of depth 2 (default) or 4.
 constexpr int kForestSpecDepth = 2;
 
@@ -661,6 +669,12 @@ void encode_forest(const dt_node *nodes, const int32_t *offsets, int32_t n_trees
         enc->roots[size_t(k)] = root;
         enc->max_tree_bytes = std::max(enc->max_tree_bytes, sb + eb);
         enc->max_levels = std::max(enc->max_levels, wt.levels * depth);
+        if (algo == DT_ALGO_DATA) {
+            // whole windows, and, where there are several, an exit to follow after each
+            const int reached = dtree::reached_depth(nodes + offsets[k], shapes[size_t(k)]);
+            const int levels = std::min(wt.levels, (reached + depth - 1) / depth);
+            enc->steps.push_back(double(levels) * (depth + (wt.levels > 1 ? 1 : 0)));
+        }
     }
     enc->table_bytes = int64_t(bytes->size());
 }
@@ -684,7 +698,7 @@ void list_forest(const dt_node *nodes, const int32_t *offsets, int32_t n_trees,
         enc->trees.push_back(int4{int(off), int(size), depth, 0});
         enc->roots.push_back(int2{int(list[2]), int(list[3])});
         enc->max_tree_bytes = std::max(enc->max_tree_bytes, size);
-        enc->max_levels = std::max(enc->max_levels, depth);
+        enc->steps.push_back(dtree::reached_depth(t, shapes[size_t(k)]));
     }
     enc->table_bytes = int64_t(bytes->size());
 }
@@ -782,28 +796,55 @@ dt_status upload_forest(const std::vector<unsigned char> &bytes, ForestEncoding 
     return DT_OK;
 }
 
-// Estimated time, in cycles, of one round of groups (every resident workgroup walks its tiles
-// through all trees).  A walk of 64 records takes the CU's LDS about 8 cycles per step
-// (speculative: 40), and its wavefront at least 260 cycles per step of four trees
-// (speculative: 300 of one), whichever is longer with this many wavefronts; each byte of
-// tables copied takes 1/64 cycle, each chunk its barriers, each group its staging, which
-// kernels without prefetch wait for.
-double round_cost(const ForestEncoding &enc, int algo, const ForestPlan &p, int split) {
-    const double steps = std::max(1, std::min(enc.max_levels, 16));
+// Estimated time, in cycles, of one round of groups (every resident workgroup, `blocks` to a
+// CU, walks its tiles through all trees).  A walk of 64 records takes the CU's LDS some
+// cycles per step and tree, and its wavefront at least some more per step (data: of four
+// trees together; speculative: of one, longer on rows whose pitch is no constant), whichever
+// is longer with this many wavefronts.  Tables read in place keep each workgroup waiting, a
+// second one as long again.  Each byte of tables copied takes 1/64 cycle, each chunk its
+// barriers, each group its staging, which kernels without prefetch wait for.  The constants
+// give the measured order, not the time (which is up to half as long again).  Of 876 data
+// walks measured with windows and with lists (mixed, irregular and chain-like forests of 6 to
+// 200 trees, 8 to 64 features, 1,000 to 600,000 records) the choice is the faster or within
+// 5% of it in 831, the worst 1.26 times as slow.  Speculative windows of depth 4, 100,001 records,
+// 30 complete trees of depth 8: 16 features 42.5 us with one wavefront per tile and 44.7 with
+// two, 19 features 54 and 44 us.
+double round_cost(const ForestEncoding &enc, int algo, const ForestPlan &p, int split, int blocks) {
+    const bool in_place = p.chunk_lds_bytes == 0, data = algo == DT_ALGO_DATA;
+    const double lds_step = data ? (in_place ? 20.0 : 10.0) : (in_place ? 100.0 : 40.0);
+    const double chain_step = data ? (in_place ? 650.0 : 260.0)
+                              : in_place ? 750.0
+                              : p.tile.mode == dtree::kLoadExact ? 300.0
+                                                                 : 400.0;
+    const double spec_steps = std::max(1, std::min(enc.max_levels, 16));
+    constexpr int kIlp = 4;                                 // trees walked together (data)
     const int parts = 1 << split;
     double walk = 0.0;
     for (int c = p.first_chunk; c < p.first_chunk + p.n_chunks; ++c) {
-        const int trees = enc.chunks[size_t(c)].y - enc.chunks[size_t(c)].x;
-        const int share = (trees + parts - 1) / parts;      // of a wavefront
-        const double lds = (algo == DT_ALGO_DATA ? 8.0 : 40.0) * steps * trees * p.tiles;
-        const double chain = algo == DT_ALGO_DATA ? 260.0 * steps * ((share + 3) / 4)
-                                                  : 300.0 * steps * share;
-        walk += std::max(lds, chain);
+        const int first = enc.chunks[size_t(c)].x, end = enc.chunks[size_t(c)].y;
+        const int share = (end - first + parts - 1) / parts;      // of a wavefront
+        double all = 0.0, longest = 0.0;     // steps of the trees, of a wavefront's groups
+        if (data) {
+            for (int k = first; k < end; ++k) all += enc.steps[size_t(k)];
+            for (int part = first; part < end; part += share) {
+                double steps = 0.0;
+                const int last = std::min(end, part + share);
+                for (int k = part; k < last; k += kIlp)
+                    steps += *std::max_element(enc.steps.begin() + k,
+                                               enc.steps.begin() + std::min(k + kIlp, last));
+                longest = std::max(longest, steps);
+            }
+        } else {
+            all = spec_steps * (end - first);
+            longest = spec_steps * share;
+        }
+        walk += std::max(lds_step * all * p.tiles * blocks,
+                         chain_step * longest * (in_place ? blocks : 1));
     }
-    const bool resident = p.chunk_lds_bytes > 0 && p.n_chunks == 1;
-    const double tables = resident ? 0.0 : double(enc.table_bytes) / 64.0 + 800.0 * p.n_chunks;
+    const double tables =
+        in_place || p.n_chunks == 1 ? 0.0 : double(enc.table_bytes) / 64.0 + 800.0 * p.n_chunks;
     const double wait = p.tile.vecs > 0 || p.tile.mode == dtree::kLoadExact ? 1500.0 : 7000.0;
-    return p.blocks_per_cu * (walk + p.tiles * (p.tile.tile_bytes / 64.0) + tables) + wait;
+    return walk + blocks * (p.tiles * (p.tile.tile_bytes / 64.0) + tables) + wait;
 }
 
 dt_status plan_forest(const DeviceCaps &caps, int algo, int n_features, int load_mode, int split,
@@ -865,7 +906,11 @@ dt_status plan_forest(const DeviceCaps &caps, int algo, int n_features, int load
         plan->why = "no workgroup shape fits this forest kernel";
         return plan->status = DT_ERR_UNSUPPORTED;
     }
-    plan->round_cost = round_cost(*enc, algo, *plan, split);
+    for (int b = 1; b <= plan->blocks_per_cu; ++b)
+        plan->round_cost.push_back(round_cost(*enc, algo, *plan, split, b));
+    // tables that stay in the LDS are copied once
+    if (plan->chunk_lds_bytes > 0 && plan->n_chunks == 1)
+        plan->first_cost = double(enc->table_bytes) / 64.0;
     plan->why.clear();
     return plan->status = DT_OK;
 }
@@ -873,8 +918,10 @@ dt_status plan_forest(const DeviceCaps &caps, int algo, int n_features, int load
 // How a call's tiles are spread: the first `lead` by the unsplit kernel, the rest by the
 // kernel of 2^split wavefronts per tile (split 0: none of them).
 struct ForestSpread {
+    int enc = 0;             // the encoding walked
     int64_t lead = 0;
     int split = 0;
+    double cost = -1.0;      // estimated cycles (-1: no plan holds)
 };
 
 // The unsplit kernel walks a tile per wavefront and is the most efficient with every
@@ -886,15 +933,16 @@ ForestSpread spread_forest(const ForestPlan *const (&plan)[kForestSplits], int n
                            int64_t tiles) {
     ForestSpread best;
     best.lead = tiles;          // where no plan holds, the unsplit one says why
-    double best_cost = -1.0;
     constexpr double kLaunch = 8000.0;   // a second launch: about 3 us
     const auto rounds = [&](const ForestPlan &p, int64_t t) {
         const int64_t groups = (t + p.tiles - 1) / p.tiles, slots = int64_t(p.blocks_per_cu) * n_cu;
-        return double((groups + slots - 1) / slots) * p.round_cost;
+        const int64_t rest = groups % slots;      // on as few to a CU as they go
+        return double(groups / slots) * p.round_cost.back() + p.first_cost +
+               (rest > 0 ? p.round_cost[size_t((rest - 1) / n_cu)] : 0.0);
     };
     const auto weigh = [&](double cost, int64_t lead, int split) {
-        if (best_cost >= 0.0 && cost >= best_cost) return;
-        best_cost = cost;
+        if (best.cost >= 0.0 && cost >= best.cost) return;
+        best.cost = cost;
         best.lead = lead;
         best.split = split;
     };
@@ -916,8 +964,7 @@ ForestSpread spread_forest(const ForestPlan *const (&plan)[kForestSplits], int n
 
 void forest_destroy_impl(dt_forest *f) {
     if (!f) return;
-    free_forest_encoding(&f->enc[0]);
-    free_forest_encoding(&f->enc[1]);
+    for (ForestEncoding &e : f->enc) free_forest_encoding(&e);
     delete f;
 }
 
@@ -960,9 +1007,9 @@ dt_status forest_create_impl(const dt_node *nodes, const int32_t *offsets, int32
     f->vote_words = vote_words_for(n_classes);
 
     // data windows: the depth that makes the forest's tables smallest; where no depth has
-    // every tree in one window, or the windows' slots take more than the nodes, node lists
+    // every tree in one window, or the windows' slots take more than the nodes, node lists too
     int data_d = opt && opt->data_window_depth ? opt->data_window_depth : 0;
-    bool list = false;
+    bool list = false, windows = true;
     if (!data_d) {
         int64_t best = -1, list_bytes = 0;
         bool listable = true;
@@ -978,23 +1025,26 @@ dt_status forest_create_impl(const dt_node *nodes, const int32_t *offsets, int32
             listable = listable && offsets[k + 1] - offsets[k] <= dtree::kMaxForestListNodes;
         }
         list = listable && (max_depth > data_d || best / 12 * 8 > list_bytes);
+        windows = !list || best < kMaxForestBytes;
     }
     const int spec_d = opt && opt->spec_window_depth ? opt->spec_window_depth : kForestSpecDepth;
-    const int depth[2] = {data_d, spec_d};
-    for (int algo = 0; algo < 2; ++algo) {
-        ForestEncoding *enc = &f->enc[algo];
+    for (int e = 0; e < 3; ++e) {
+        if (e == DT_ALGO_DATA ? !windows : e == kForestList && !list) continue;
+        const int algo = e == DT_ALGO_SPECULATIVE ? DT_ALGO_SPECULATIVE : DT_ALGO_DATA;
+        ForestEncoding *enc = &f->enc[e];
         std::vector<unsigned char> bytes;
-        if (list && algo == DT_ALGO_DATA)
+        if (e == kForestList)
             list_forest(nodes, offsets, n_trees, shapes, &bytes, enc);
         else
-            encode_forest(nodes, offsets, n_trees, shapes, algo, depth[algo], &bytes, enc);
-        if (enc->table_bytes > (int64_t(1) << 31) - 1) {
+            encode_forest(nodes, offsets, n_trees, shapes, algo, e == DT_ALGO_DATA ? data_d : spec_d,
+                          &bytes, enc);
+        if (enc->table_bytes > kMaxForestBytes) {
             forest_destroy_impl(f);
             return fail(DT_ERR_UNSUPPORTED, "forest tables exceed 2 GiB");
         }
         for (int m = 0; m < dtree::kForestLoadModes; ++m) {
             for (int sp = 0; sp < kForestSplits; ++sp) {
-                ForestPlan *p = &f->plan[algo][m][sp];
+                ForestPlan *p = &f->plan[e][m][sp];
                 if (n_features > dtree::kMaxRowStride) {
                     p->why = "n_features > 256";
                     continue;
@@ -1015,15 +1065,29 @@ dt_status forest_create_impl(const dt_node *nodes, const int32_t *offsets, int32
     return DT_OK;
 }
 
-// Plans of a call's load mode, by split, and how its tiles are spread over them.
+// How a call's tiles are spread, over the faster of the forest's encodings, and the plans of
+// that encoding for the call's load mode, by split.
 ForestSpread spread_call(const dt_forest &f, const float *d_x, int64_t n, int64_t ld, dt_algo algo,
                          const ForestPlan *(&plans)[kForestSplits]) {
     // a split kernel reads exact rows as any others of a multiple of 16 bytes
     const int mode = dtree::forest_load_mode(d_x, ld, f.n_features);
     const int split_mode = mode == dtree::kLoadExact ? int(dtree::kLoadRows) : mode;
-    for (int sp = 0; sp < kForestSplits; ++sp)
-        plans[sp] = &f.plan[algo][sp == 0 ? mode : split_mode][sp];
-    return spread_forest(plans, f.caps.n_cu, (n + dtree::kTileRows - 1) / dtree::kTileRows);
+    const int64_t tiles = (n + dtree::kTileRows - 1) / dtree::kTileRows;
+    ForestSpread best;
+    bool any = false;
+    for (int e : {int(algo), kForestList}) {
+        if (!f.enc[e].d_mem || (e == kForestList && algo != DT_ALGO_DATA)) continue;
+        const ForestPlan *of_enc[kForestSplits];
+        for (int sp = 0; sp < kForestSplits; ++sp)
+            of_enc[sp] = &f.plan[e][sp == 0 ? mode : split_mode][sp];
+        ForestSpread s = spread_forest(of_enc, f.caps.n_cu, tiles);
+        if (any && (s.cost < 0.0 || (best.cost >= 0.0 && s.cost >= best.cost))) continue;
+        any = true;
+        best = s;
+        best.enc = e;
+        std::copy(of_enc, of_enc + kForestSplits, plans);
+    }
+    return best;
 }
 
 dt_status forest_classify_impl(const dt_forest *f, const float *d_x, int64_t n, int64_t ld,
@@ -1049,7 +1113,7 @@ dt_status forest_classify_impl(const dt_forest *f, const float *d_x, int64_t n, 
         return fail(DT_ERR_INVALID_ARG, "current device differs from the forest's device");
     const ForestPlan *plans[kForestSplits];
     const ForestSpread spread = spread_call(*f, d_x, n, ld, algo, plans);
-    const ForestEncoding &enc = f->enc[algo];
+    const ForestEncoding &enc = f->enc[spread.enc];
     const int64_t tiles = (n + dtree::kTileRows - 1) / dtree::kTileRows;
 
     for (int part = 0; part < 2; ++part) {
@@ -1300,7 +1364,7 @@ dt_status dt_probe_forest_spread(const dt_forest *f, const float *d_x, int64_t n
     const ForestPlan *plans[kForestSplits];
     const ForestSpread spread = spread_call(*f, d_x, n, ld, algo, plans);
     *info = dt_forest_spread{};
-    info->list = f->enc[algo].exit_mode == dtree::kExitList ? 1 : 0;
+    info->list = spread.enc == kForestList ? 1 : 0;
     info->whole_tiles = spread.lead;
     info->split_tiles = (n + dtree::kTileRows - 1) / dtree::kTileRows - spread.lead;
     if (info->whole_tiles > 0) {

@@ -296,6 +296,15 @@ void build_forest_list(const dt_node *nodes, int32_t n, const std::vector<int32_
     }
 }
 
+int reached_depth(const dt_node *nodes, const TreeShape &shape) {
+    std::vector<int64_t> count(size_t(shape.depth) + 1, 0);
+    for (int32_t i = 0; i < shape.n_nodes; ++i)
+        if (nodes[i].cls == -1) ++count[size_t(shape.node_depth[size_t(i)])];
+    int levels = 0;
+    while (levels < shape.depth && std::ldexp(double(count[size_t(levels)]), 6 - levels) >= 1.0) ++levels;
+    return std::max(1, levels);
+}
+
 DataWalk data_walk_for(const TreeShape &shape, int32_t levels, int64_t window_bytes,
                        int64_t list_bytes) {
     int log2_nodes = 1;

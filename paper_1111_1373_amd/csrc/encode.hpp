@@ -121,6 +121,10 @@ DataWalk data_walk_for(const TreeShape &shape, int32_t levels, int64_t window_by
 bool list_is_faster(const TreeShape &shape, int32_t levels, int window_depth, int64_t list_bytes,
                     int waves_windows, int waves_list);
 
+// Levels of decision nodes that some record of a wavefront's 64 passes, if both branches of
+// every node are as likely: at least 1, at most the depth.
+int reached_depth(const dt_node *nodes, const TreeShape &shape);
+
 // Number of windows, and window levels on the longest path, for window depth D (without
 // building them).
 int64_t count_windows(const dt_node *nodes, const TreeShape &shape, int depth);

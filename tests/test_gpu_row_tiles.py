@@ -1,6 +1,8 @@
 """GPU parity on rows of every staging class: dense rows that are no multiple of 16 bytes,
 strided rows and bases between words or vectors, rows wide enough for tiles of 32 and 16
 records, and record counts around the tile edges.  Integer outputs: exact."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -19,6 +21,21 @@ def dt():
         pytest.skip("no GPU")
     from paper_1111_1373_amd import dtree
     return dtree
+
+
+class _Spread(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int32) for n in (
+        "list", "whole_waves", "split_waves", "waves_per_tile", "whole_blocks_per_cu",
+        "split_blocks_per_cu")] + [(n, ctypes.c_int64) for n in ("whole_tiles", "split_tiles")]
+
+
+def _spread(dt, forest, x, algo="data"):
+    """How a forest call on the records x is spread over kernels."""
+    s = _Spread()
+    dt._check(dt._lib.dt_probe_forest_spread(
+        forest._h, ctypes.c_void_p(x.data_ptr()), ctypes.c_int64(x.shape[0]),
+        ctypes.c_int64(x.stride(0)), dt.ALGOS[algo], ctypes.byref(s)), "dt_probe_forest_spread")
+    return s
 
 
 # features, columns beyond them, elements before the first record
@@ -96,9 +113,36 @@ def test_forest_lead_and_rest(dt, n):
     offsets = np.concatenate([[0], np.cumsum([len(t) for t in trees])]).astype(np.int32)
     x = W.uniform_f32(r, (n, 6))
     f = dt.Forest(nodes, offsets, 6, 9)
-    got = f.classify(torch.from_numpy(x).cuda(), out_kind="class_i32").cpu().numpy()
+    xd = torch.from_numpy(x).cuda()
+    s = _spread(dt, f, xd)
+    assert s.list == 1 and s.whole_tiles == 256 * 16 and s.split_tiles == -(-n // 64) - 256 * 16
+    assert s.waves_per_tile >= 2
+    got = f.classify(xd, out_kind="class_i32").cpu().numpy()
     at = np.concatenate([np.arange(0, n, 97), np.arange(n - 3000, n)])
     np.testing.assert_array_equal(got[at], oracle.forest_classes(nodes, offsets, x[at], 6, 9))
+
+
+@pytest.mark.parametrize("deep,size,want_list", [(11, 0, [0, 0, 0]), (14, 0, None), (0, 300, None)])
+def test_mixed_forest(dt, deep, size, want_list):
+    """Complete trees, which one packed window each holds, beside one that is deeper: windows
+    and node lists are weighed at each call (32 features, 1,500,000 records, one tree of depth
+    11: 155.6 us with windows, 208.5 us with lists)."""
+    r = np.random.Generator(np.random.PCG64(deep + size))
+    F, C = 32, 8
+    trees = [W.complete_tree(r, 10, F, C) for _ in range(31)]
+    trees.append(W.complete_tree(r, deep, F, C) if deep else W.random_full_tree(r, size, F, C))
+    nodes = np.concatenate(trees)
+    offsets = np.concatenate([[0], np.cumsum([len(t) for t in trees])]).astype(np.int32)
+    x = W.uniform_f32(r, (300_000, F))
+    f, xd = dt.Forest(nodes, offsets, F, C), torch.from_numpy(x).cuda()
+    at = np.arange(0, 20_000)
+    want = oracle.forest_classes(nodes, offsets, x[at], F, C)
+    lists = []
+    for n in (1000, 20_000, 300_000):
+        lists.append(_spread(dt, f, xd[:n]).list)
+        got = f.classify(xd[:n], out_kind="class_i32").cpu().numpy()
+        np.testing.assert_array_equal(got[:20_000], want[:n])
+    assert want_list is None or lists == want_list
 
 
 @pytest.mark.parametrize("algo", ["data", "speculative"])
