@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <climits>
 #include <cstdint>
 #include <cstring>
 #include <mutex>
@@ -718,11 +719,12 @@ void chunk_forest(const DeviceCaps &caps, int algo, int waves_per_cu, int split,
     // holds the largest tree; ties: larger chunk buffers (fewer passes).
     int best_w = 0, best_score = 0;
     int64_t best_budget = 0;
-    // Speculative walks of wide rows (more than 8 KiB a tile) keep to 8: a ninth tile would
+    // Speculative walks of wide rows (more than 9 KiB a tile) keep to 8: a ninth tile would
     // take half of the chunk (64 features, 100 trees: 331 us with 8, 400 us with 9).
-    const int most = algo == DT_ALGO_SPECULATIVE && split == 0 && tile_bytes > 9 * 1024
-                         ? dtree::kMaxWavesPerBlock
-                         : dtree::forest_max_waves(algo, enc->depth);
+    int most = algo == DT_ALGO_SPECULATIVE && split == 0 && tile_bytes > 9 * 1024
+                   ? dtree::kMaxWavesPerBlock
+                   : dtree::forest_max_waves(algo, enc->depth);
+    if (split > 0) most = std::min(most, target);   // (unsplit: fewer waves win the tie)
     for (int bpc = 1; bpc <= 4; ++bpc) {
         const int64_t per_block = std::min<int64_t>(caps.lds_per_block, caps.lds_per_cu / bpc);
         for (int w = most; w >= 1 << split; --w) {
@@ -881,7 +883,9 @@ dt_status plan_forest(const DeviceCaps &caps, int algo, int n_features, int load
     }
     int best_waves = 0;
     const int planned = plan->waves;
-    for (int w = dtree::forest_max_waves(algo, enc->depth); w >= 1 << split; --w) {
+    // a split kernel keeps to the caller's wavefronts per CU
+    const int limit = split > 0 && waves_per_cu > 0 ? waves_per_cu : INT_MAX;
+    for (int w = std::min(limit, dtree::forest_max_waves(algo, enc->depth)); w >= 1 << split; --w) {
         if (s.tables_in_lds && w != planned) continue;   // the chunks were cut for these
         const int tiles = w >> split;
         const int lds = int(plan->chunk_lds_bytes + tiles * (s.tile.tile_bytes + vote_bytes));
@@ -894,6 +898,7 @@ dt_status plan_forest(const DeviceCaps &caps, int algo, int n_features, int load
                         hipGetErrorString(e);
             return plan->status = DT_ERR_HIP;
         }
+        nb = std::min(nb, limit / w);
         if (nb >= 1 && nb * w > best_waves) {
             best_waves = nb * w;
             plan->waves = w;
@@ -1053,9 +1058,10 @@ dt_status forest_create_impl(const dt_node *nodes, const int32_t *offsets, int32
                     (!dtree::exact_rows(n_features, 4) || n_features > 32 || sp > 0))
                     continue;
                 if (m == dtree::kLoadFlat && n_features % 4 == 0) continue;
+                const int waves_per_cu = opt ? opt->waves_per_cu : 0;
                 if ((1 << sp) > dtree::forest_max_waves(algo, enc->depth)) continue;
-                plan_forest(f->caps, algo, n_features, m, sp, f->vote_words,
-                            opt ? opt->waves_per_cu : 0, enc, p);
+                if (waves_per_cu > 0 && (1 << sp) > waves_per_cu) continue;
+                plan_forest(f->caps, algo, n_features, m, sp, f->vote_words, waves_per_cu, enc, p);
             }
         }
         st = upload_forest(bytes, enc);

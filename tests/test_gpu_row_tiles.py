@@ -122,6 +122,30 @@ def test_forest_lead_and_rest(dt, n):
     np.testing.assert_array_equal(got[at], oracle.forest_classes(nodes, offsets, x[at], 6, 9))
 
 
+@pytest.mark.parametrize("waves", [1, 2, 3, 4, 7, 8])
+@pytest.mark.parametrize("algo", ["data", "speculative"])
+@pytest.mark.parametrize("shape", ["complete", "random", "large"])
+def test_split_forest_keeps_to_the_wavefronts_asked_for(dt, waves, algo, shape):
+    """waves_per_cu of the options bounds the resident wavefronts of a split kernel, with tables
+    in the LDS and in place."""
+    r = np.random.Generator(np.random.PCG64(waves))
+    F, C = 19, 5
+    make = {"complete": lambda: W.complete_tree(r, 6, F, C),
+            "random": lambda: W.random_full_tree(r, 100, F, C),
+            "large": lambda: W.random_full_tree(r, 25_000, F, C)}[shape]
+    trees = [make() for _ in range(3 if shape == "large" else 40)]
+    nodes = np.concatenate(trees)
+    offsets = np.concatenate([[0], np.cumsum([len(t) for t in trees])]).astype(np.int32)
+    x = W.uniform_f32(r, (5000, F))
+    want = oracle.forest_classes(nodes, offsets, x, F, C)
+    f, xd = dt.Forest(nodes, offsets, F, C, waves_per_cu=waves), torch.from_numpy(x).cuda()
+    for n in (64, 5000):
+        s = _spread(dt, f, xd[:n], algo)
+        assert s.split_waves * s.split_blocks_per_cu <= waves and s.waves_per_tile <= waves
+        got = f.classify(xd[:n], algo=algo, out_kind="class_i32").cpu().numpy()
+        np.testing.assert_array_equal(got, want[:n])
+
+
 @pytest.mark.parametrize("deep,size,want_list", [(11, 0, [0, 0, 0]), (14, 0, None), (0, 300, None)])
 def test_mixed_forest(dt, deep, size, want_list):
     """Complete trees, which one packed window each holds, beside one that is deeper: windows
