@@ -102,7 +102,9 @@ typedef struct dt_forest dt_forest;
  * slots.  0 selects the library's choice.
  *   data_window_depth: 1..16.  Default: the fewest window levels whose tables take at
  *     most 48 KiB (and leave the LDS room for two fp32 record tiles); ties go to smaller
- *     tables; if no depth fits, the depth with the smallest tables.
+ *     tables; if no depth fits, the depth with the smallest tables (forests: the depth with
+ *     the smallest tables).  With the default the data decomposition walks a list of the
+ *     tree's nodes instead of its windows where that is faster; with a depth given, windows.
  *   spec_window_depth: 1..6 (a window has at most 63 decision nodes, one 64-lane
  *     wavefront).  2^depth lanes evaluate one record, so 64 / 2^depth records share a
  *     wavefront instruction.  Default: 2 (4 lanes per record, measured fastest), or the
@@ -114,20 +116,23 @@ typedef struct {
     int32_t spec_window_depth;
     int32_t waves_per_cu;      /* launch tuning: resident wavefronts per compute unit
                                   (0 = the library's choice, about 64 KiB of record tiles in
-                                  flight per CU); limited by the LDS and registers */
+                                  flight per CU); limited by the LDS and registers.  Forest
+                                  kernels of several wavefronts per tile keep to it, others
+                                  take it as an aim for one workgroup */
     int32_t path_hops;         /* DT_ALGO_PATH: entries read further along per reduction
                                   round, 1..8 (0 = 2: path[i] <- path[path[path[i]]], the
                                   form printed in Procedure 5) */
 } dt_tree_options;
 
-/* Shape of a tree and of its two encodings. */
+/* Shape of a tree and of the windows of both decompositions.  (They are what the options
+ * cut the tree into, also where the data decomposition walks a list of the nodes.) */
 typedef struct {
     int32_t n_nodes, n_internal, n_leaves;
     int32_t depth;                  /* edges on the longest root-to-leaf path            */
     int32_t n_features, n_classes;
     int32_t data_window_depth, data_windows, data_levels;
     int32_t spec_window_depth, spec_windows, spec_levels;
-    int64_t data_table_bytes, spec_table_bytes;   /* bytes staged in LDS per workgroup  */
+    int64_t data_table_bytes, spec_table_bytes;   /* of the windows, for fp32 records     */
 } dt_tree_info;
 
 /* Version of this ABI (DT_ABI_VERSION of the header the library was built from). */
@@ -222,14 +227,16 @@ typedef struct {
     int32_t workgroups_per_cu;     /* resident workgroups per compute unit               */
     int32_t lds_bytes;             /* dynamic LDS per workgroup                          */
     int32_t result_buffer_tiles;   /* tiles of results each wavefront buffers           */
-    int32_t tables_in_lds;         /* 1: tree tables staged in the LDS, 0: read in place */
+    int32_t tables_in_lds;         /* 1: tree tables staged in the LDS, 0: read in place
+                                      (of a list of nodes larger than 48 KiB, the rest) */
     int32_t load_mode;             /* 0: dense rows of no multiple of 16 bytes, a tile
                                       copied as it lies; 1: other rows, row by row;
                                       2: dense rows of a power of two of words; 3: rows
                                       that start between words                           */
-    int32_t tile_rows;             /* records per wavefront tile: 64, 32 or 16 of wide
-                                      rows, 32 for the speculative walk of 32- and 64-slot
-                                      windows                                            */
+    int32_t tile_rows;             /* records per wavefront tile: 64, or 32 for the
+                                      speculative walk of 32- and 64-slot windows (64 of
+                                      load mode 2 under 32 bytes a row), fewer of wide rows:
+                                      as many as take 16 KiB, 16 at least                */
 } dt_launch_info;
 
 /* Fill *info with the launch shape of dt_classify_typed(tree, d_x, x_type, n, ld, ...,
@@ -246,9 +253,9 @@ dt_status dt_tree_launch_info(const dt_tree *tree, const void *d_x, dt_dtype x_t
  * Procedure 3 for DT_ALGO_DATA; Sections 3.3-3.4, Procedures 4-5 for DT_ALGO_SPECULATIVE
  * and DT_ALGO_PATH).  Asynchronous on `stream` (a hipStream_t; NULL = the null stream).
  *   d_x     device pointer, row-major fp32, record r at d_x + r*ld, columns
- *           0..n_features-1 are read.  Any alignment of 4 bytes; rows that are
- *           contiguous (ld == n_features), a multiple of 4 floats and 16-byte aligned
- *           take the vectorised load path.
+ *           0..n_features-1 are used.  Any alignment of 4 bytes.  (Rows are read in
+ *           16-byte vectors: of columns between n_features and ld, up to 18 bytes after a
+ *           row may be read too, never past the last record's last feature.)
  *   n       number of records, >= 0 (0: nothing is launched)
  *   ld      row stride in floats, >= n_features
  *   d_out   device pointer to n labels of the type named by out_kind
@@ -256,14 +263,15 @@ dt_status dt_tree_launch_info(const dt_tree *tree, const void *d_x, dt_dtype x_t
  *           results
  * Exactly n outputs are written; nothing is written on an error return.  Buffers are
  * owned by the caller and must stay valid until the work on `stream` completes.  The call
- * puts one kernel launch on `stream` and nothing else (no allocation, copy, memset or
- * synchronisation), so it may be captured in a HIP graph; a tree handle is never written
+ * puts one kernel launch (a forest: one or two) on `stream` and nothing else (no
+ * allocation, copy, memset or synchronisation), so it may be captured in a HIP graph; a tree handle is never written
  * after creation, so calls on several streams may use it at once.
  * Errors: DT_ERR_INVALID_ARG (null tree or pointers with n > 0, n < 0, ld < n_features,
  * unknown enum, DT_OUT_CLASS_U8 with n_classes > 256, device other than the tree's),
  * DT_ERR_UNSUPPORTED (n_features > 256, n > 2^37), DT_ERR_HIP (launch failure).
  * A tree's tables are staged in the LDS when they fit next to the record tiles and are
- * read from global memory otherwise; every valid tree is supported.
+ * read from global memory otherwise (a list of nodes: from its 48 KiB on); every valid tree
+ * is supported.
  */
 dt_status dt_classify(const dt_tree *tree, const float *d_x, int64_t n, int64_t ld,
                       void *d_out, dt_output out_kind, dt_algo algo, void *stream);
@@ -271,9 +279,9 @@ dt_status dt_classify(const dt_tree *tree, const float *d_x, int64_t n, int64_t 
 /*
  * dt_classify for narrow records (Section 2.1: ordered discrete attributes behave like the
  * real-valued ones).  Records of element type x_type (dt_dtype): d_x must be aligned to the
- * element size and ld counts elements.  Each element is widened
- * exactly to fp32 before its comparison, so the labels equal those of dt_classify on the
- * widened records.  DT_ALGO_PATH reads DT_F32 records only (DT_ERR_UNSUPPORTED otherwise).
+ * element size and ld counts elements.  (Where d_x lies between 4-byte words, the bytes of
+ * the word before it may be read too.)  Each element is widened exactly to fp32 before its
+ * comparison, so the labels equal those of dt_classify on the widened records.  DT_ALGO_PATH reads DT_F32 records only (DT_ERR_UNSUPPORTED otherwise).
  * Errors: as dt_classify, and DT_ERR_INVALID_ARG for an unknown x_type or a misaligned d_x.
  */
 dt_status dt_classify_typed(const dt_tree *tree, const void *d_x, dt_dtype x_type, int64_t n,

@@ -1297,7 +1297,9 @@ dt_status dt_tree_launch_info(const dt_tree *t, const void *d_x, dt_dtype x_type
     info->workgroups_per_cu = plan.blocks_per_cu;
     info->lds_bytes = plan.lds_bytes;
     info->result_buffer_tiles = plan.out_cap;
-    info->tables_in_lds = plan.tables_in_lds;
+    const Encoding &enc = t->enc[plan.enc];
+    const bool part = enc.list && enc.table_bytes(x_type) < enc.slot_bytes[x_type];
+    info->tables_in_lds = part ? 0 : plan.tables_in_lds;
     info->load_mode = mode;
     info->tile_rows = plan.tile.tile_rows;
     return DT_OK;

@@ -83,3 +83,15 @@ def test_complete_trees_keep_one_window(dt, x_type, depth, F):
                                     "u8": torch.uint8}[x_type], device="cuda")
     for out_kind in ("class_u8", "class_i32"):
         assert not _walks_list(dt, tree, x, out_kind)
+
+
+@pytest.mark.parametrize("size,whole", [(3070, 1), (3071, 1), (3072, 0), (20_000, 0)])
+def test_launch_info_of_lists(dt, size, whole):
+    """A list of which only the first 48 KiB are staged is not reported as staged."""
+    r = np.random.Generator(np.random.PCG64(size))
+    tree = dt.Tree(W.random_full_tree(r, size, 16, 7), 16, 7)
+    x = torch.zeros((64, 16), device="cuda")
+    assert _walks_list(dt, tree, x)
+    info = tree.launch_info(x)
+    assert info["tables_in_lds"] == whole
+    assert info["lds_bytes"] < 160 * 1024
