@@ -814,10 +814,7 @@ dt_status upload_forest(const std::vector<unsigned char> &bytes, ForestEncoding 
 double round_cost(const ForestEncoding &enc, int algo, const ForestPlan &p, int split, int blocks) {
     const bool in_place = p.chunk_lds_bytes == 0, data = algo == DT_ALGO_DATA;
     const double lds_step = data ? (in_place ? 20.0 : 10.0) : (in_place ? 100.0 : 40.0);
-    const double chain_step = data ? (in_place ? 650.0 : 260.0)
-                              : in_place ? 750.0
-                              : p.tile.mode == dtree::kLoadExact ? 300.0
-                                                                 : 400.0;
+    const double chain_step = data ? (in_place ? 650.0 : 260.0) : (in_place ? 750.0 : 400.0);
     const double spec_steps = std::max(1, std::min(enc.max_levels, 16));
     constexpr int kIlp = 4;                                 // trees walked together (data)
     const int parts = 1 << split;
@@ -1057,7 +1054,10 @@ dt_status forest_create_impl(const dt_node *nodes, const int32_t *offsets, int32
                 if (m == dtree::kLoadExact &&
                     (!dtree::exact_rows(n_features, 4) || n_features > 32 || sp > 0))
                     continue;
-                if (m == dtree::kLoadFlat && n_features % 4 == 0) continue;
+                if (m == dtree::kLoadFlat &&
+                    (n_features % 4 == 0 ||
+                     (algo == DT_ALGO_SPECULATIVE && n_features <= 4 * dtree::kMaxForestPitchVecs)))
+                    continue;
                 const int waves_per_cu = opt ? opt->waves_per_cu : 0;
                 if ((1 << sp) > dtree::forest_max_waves(algo, enc->depth)) continue;
                 if (waves_per_cu > 0 && (1 << sp) > waves_per_cu) continue;
@@ -1076,7 +1076,7 @@ dt_status forest_create_impl(const dt_node *nodes, const int32_t *offsets, int32
 ForestSpread spread_call(const dt_forest &f, const float *d_x, int64_t n, int64_t ld, dt_algo algo,
                          const ForestPlan *(&plans)[kForestSplits]) {
     // a split kernel reads exact rows as any others of a multiple of 16 bytes
-    const int mode = dtree::forest_load_mode(d_x, ld, f.n_features);
+    const int mode = dtree::forest_load_mode(algo, d_x, ld, f.n_features);
     const int split_mode = mode == dtree::kLoadExact ? int(dtree::kLoadRows) : mode;
     const int64_t tiles = (n + dtree::kTileRows - 1) / dtree::kTileRows;
     ForestSpread best;

@@ -121,6 +121,20 @@ inline Rows make_tile_rows(const void *d_x, int elem_type, int64_t n, int64_t ld
     return r;
 }
 
+// Row tiles of the speculative forest walk: 16-byte vectors of the LDS pitch for rows of
+// `row_vecs`.  Its rounds read 64 / S rows, a constant number of rows apart, so that with a
+// constant pitch a round's row is an instruction offset.  Hence classes, as far as the widest
+// class leaves the LDS 8 tiles; wider rows keep their own pitch, a register.  Measured with
+// 50 complete trees of depth 7, 1,000,001 records, windows of depth 4 (of depth 2), a row's
+// own pitch against the class's: 3 features 380 and 288 us (273 and 249), 20 features 391 and
+// 310 us (286 and 256), 36 features 435 and 355 us (323 and 294).
+constexpr int kMaxForestPitchVecs = 16;
+constexpr int forest_pitch_vecs(int row_vecs) {
+    for (int v : {1, 2, 4, 8, 12, kMaxForestPitchVecs})
+        if (row_vecs <= v) return v;
+    return row_vecs;
+}
+
 // Record tile of a forest kernel: 64 fp32 records.  Prefetched tiles (unsplit kernels) take
 // up to 8 vectors per lane, as many registers as 16 wavefronts per CU leave; the
 // speculative walk has them for exact tiles only.  The data walk's tiles are column-major.
@@ -143,15 +157,20 @@ inline TileShape forest_tile_shape(int algo, int n_features, int mode, bool pref
             s.vecs = v;
             break;
         }
-    s.lds_pitch = flat ? s.row_bytes : 16 * s.row_vecs + 4;
+    s.lds_pitch = flat ? s.row_bytes : 16 * forest_pitch_vecs(s.row_vecs) + 4;
     s.tile_bytes = kTileRows * (algo == kAlgoData ? s.row_bytes : s.lds_pitch);
     return s;
 }
 
-// Load path of a forest call.
-inline int forest_load_mode(const void *d_x, int64_t ld, int32_t n_features) {
+// Load path of a forest call.  The speculative walk takes dense rows of up to 64 features one
+// by one too: flat tiles have no constant pitch (see forest_pitch_vecs; 3 features 383 us
+// flat, 290 us as rows of one vector).
+inline int forest_load_mode(int algo, const void *d_x, int64_t ld, int32_t n_features) {
     const int mode = load_mode_for(d_x, kXF32, ld, n_features);
-    return mode == kLoadExact && n_features > 32 ? kLoadRows : mode;
+    if (mode == kLoadExact && n_features > 32) return kLoadRows;
+    return mode == kLoadFlat && algo == kAlgoSpec && n_features <= 4 * kMaxForestPitchVecs
+               ? int(kLoadRows)
+               : mode;
 }
 
 }  // namespace dtree

@@ -53,7 +53,9 @@ void forests() {
         for (int f = 1; f <= kMaxRowStride; ++f)
             for (int mode = 0; mode < kForestLoadModes; ++mode) {
                 if (mode == kLoadExact && (!exact_rows(f, 4) || f > 32)) continue;
-                if (mode == kLoadFlat && f % 4 == 0) continue;
+                if (mode == kLoadFlat &&
+                    (f % 4 == 0 || (algo == kAlgoSpec && f <= 4 * kMaxForestPitchVecs)))
+                    continue;
                 for (int split : {0, 1})
                     for (int votes : {2, 4, 16})
                         for (bool lds : {false, true})

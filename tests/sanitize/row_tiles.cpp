@@ -27,9 +27,9 @@ void fail(const char *what, int xt, int F, int64_t ld, int64_t n, int mode, int 
     std::exit(1);
 }
 
-template <int XT, bool FLAT, int NV, int TR>
-void drive(const Rows &in, const TileShape &s, int off) {
-    using Tile = dev::RowTile<XT, FLAT, NV, TR>;
+template <int XT, bool FLAT, int NV, int TR, int PITCH = row_tile_pitch(NV, TR)>
+void drive(const Rows &in, const TileShape &s, int off, int parts = 1) {
+    using Tile = dev::RowTile<XT, FLAT, NV, TR, PITCH>;
     using T = typename Tile::T;
     const T *x = static_cast<const T *>(in.x);
     const int64_t end = Tile::prefetch_end(in);
@@ -45,8 +45,9 @@ void drive(const Rows &in, const TileShape &s, int off) {
                 for (int l = 0; l < 64; ++l) lanes[size_t(l)].store(in, tile, l);
             } else {
                 for (int pass = 0; pass < 2; ++pass)   // lanes of a wavefront run together: the
-                    for (int l = 0; l < 64; ++l)       // element loads follow every vector
-                        Tile::stage(in, tile, t, l);
+                    for (int part = 0; part < parts; ++part)   // element loads follow every
+                        for (int l = 0; l < 64; ++l)           // vector
+                            Tile::stage(in, tile, t, l, part, parts);
             }
             for (int r = 0; r < TR && t * TR + r < in.n; ++r)
                 for (int f = 0; f < in.n_features; ++f) {
@@ -86,6 +87,33 @@ void drive_columns(const Rows &in, const TileShape &s, int off, int parts) {
             for (int f = 0; f < in.n_features; ++f)
                 if (std::memcmp(&tile[f * kTileRows + r], &x[(t * kTileRows + r) * in.ld + f], 4))
                     fail("column tile", kXF32, in.n_features, in.ld, in.n, s.mode, off);
+    }
+}
+
+// Row tiles of the speculative forest kernels, staged by one to sixteen wavefronts: classes of
+// a constant pitch, and wide rows with their own.
+void forest_rows(const void *x, int64_t n, int64_t ld, int F, int off) {
+    int mode = forest_load_mode(kAlgoSpec, x, ld, F);
+    if (mode == kLoadExact) mode = kLoadRows;
+    const TileShape s = forest_tile_shape(kAlgoSpec, F, mode, false);
+    const Rows in = make_tile_rows(x, kXF32, n, ld, F, s);
+    const int parts = 1 << pick(0, 4);
+    if (s.tile_bytes % 16 != 0) fail("forest tile size", kXF32, F, ld, n, mode, off);
+    if (mode == kLoadFlat) {
+        if (F <= 4 * kMaxForestPitchVecs) fail("flat forest tile", kXF32, F, ld, n, mode, off);
+        drive<kXF32, true, 0, kTileRows>(in, s, off, parts);
+    } else if (s.row_vecs > kMaxForestPitchVecs) {
+        drive<kXF32, false, 0, kTileRows>(in, s, off, parts);
+    } else {
+        switch (forest_pitch_vecs(s.row_vecs)) {
+            case 1: drive<kXF32, false, 0, kTileRows, 20>(in, s, off, parts); break;
+            case 2: drive<kXF32, false, 0, kTileRows, 36>(in, s, off, parts); break;
+            case 4: drive<kXF32, false, 0, kTileRows, 68>(in, s, off, parts); break;
+            case 8: drive<kXF32, false, 0, kTileRows, 132>(in, s, off, parts); break;
+            case 12: drive<kXF32, false, 0, kTileRows, 196>(in, s, off, parts); break;
+            case 16: drive<kXF32, false, 0, kTileRows, 260>(in, s, off, parts); break;
+            default: fail("no pitch class", kXF32, F, ld, n, mode, off);
+        }
     }
 }
 
@@ -138,7 +166,10 @@ void one_case() {
     const int64_t n = pick(0, 3) ? pick(1, 200) : pick(1, 20);
     // a single record may come with any stride, also one whose bytes no 64-bit number holds
     if (n == 1 && pick(0, 1)) ld = std::max<int64_t>(ld, INT64_MAX >> pick(0, 40)) - pick(0, 1);
-    const int off = pick(0, 1) ? 0 : pick(0, 15);      // elements before the first record
+    // elements before the first record: any, or only those of the word it lies in, whose bytes
+    // may be read; of the others none is
+    const int per_word = 4 / int(sizeof(T));
+    const int off = pick(0, 1) ? 0 : pick(0, 1) ? pick(0, per_word - 1) : pick(0, 15);
     // the block starts on a 16-byte boundary and ends with the last record's last feature
     const size_t count = size_t(off) + size_t((n - 1) * ld + F);
     std::unique_ptr<T[]> block(new T[count]);
@@ -151,7 +182,10 @@ void one_case() {
     const int algo = algos[XT == kXF32 ? pick(0, 2) : pick(0, 1)];
     const int depth = pick(1, 6);
     int mode = load_mode_for(x, XT, ld, F);
-    if (XT == kXF32) columns(x, n, ld, F, mode, off);
+    if (XT == kXF32) {
+        columns(x, n, ld, F, mode, off);
+        forest_rows(x, n, ld, F, off);
+    }
     if (mode == kLoadExact) mode = kLoadRows;           // such rows come strided, too
     const TileShape s = tile_shape(algo, XT, F, mode, depth);
     if (s.tile_bytes % 16 != 0) fail("tile size", XT, F, ld, n, mode, off);
@@ -168,13 +202,16 @@ void forest_bases() {
         for (int pad : {0, 1, 4})
             for (uintptr_t base = 4096; base < 4112; ++base) {
                 const void *x = reinterpret_cast<const void *>(base);
-                const int mode = forest_load_mode(x, F + pad, F);
-                if (mode < 0 || mode >= kForestLoadModes || (mode == kLoadFlat && F % 4 == 0) ||
-                    (mode == kLoadExact && (base % 16 != 0 || F > 32)))
-                    fail("forest plan", kXF32, F, F + pad, 0, mode, int(base % 16));
-                const TileShape s = forest_tile_shape(kAlgoSpec, F, mode, false);
-                if (make_tile_rows(x, kXF32, 100, F + pad, F, s).lds_off != 0)
-                    fail("forest tile base", kXF32, F, F + pad, 0, mode, int(base % 16));
+                for (int algo : {kAlgoData, kAlgoSpec}) {
+                    const int mode = forest_load_mode(algo, x, F + pad, F);
+                    if (mode < 0 || mode >= kForestLoadModes ||
+                        (mode == kLoadFlat && (F % 4 == 0 || (algo == kAlgoSpec && F <= 64))) ||
+                        (mode == kLoadExact && (base % 16 != 0 || F > 32)))
+                        fail("forest plan", kXF32, F, F + pad, 0, mode, int(base % 16));
+                    const TileShape s = forest_tile_shape(algo, F, mode, false);
+                    if (make_tile_rows(x, kXF32, 100, F + pad, F, s).lds_off != 0)
+                        fail("forest tile base", kXF32, F, F + pad, 0, mode, int(base % 16));
+                }
             }
 }
 
