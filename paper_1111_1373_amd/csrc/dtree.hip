@@ -23,7 +23,6 @@ namespace {
 
 using dtree::align16;
 using dtree::exact_rows;
-using dtree::load_mode_for;
 using dtree::make_tile_rows;
 using dtree::tile_shape;
 
@@ -456,7 +455,7 @@ dt_status classify_impl(const dt_tree *tree, const void *d_x, dt_dtype x_type, i
 
     if ((reinterpret_cast<uintptr_t>(d_x) % uintptr_t(dtree::elem_bytes(x_type))) != 0)
         return fail(DT_ERR_INVALID_ARG, "d_x is not aligned to its element size");
-    const int mode = load_mode_for(d_x, x_type, ld, tree->n_features);
+    const int mode = dtree::tree_load_mode(algo, d_x, x_type, ld, tree->n_features, tree->enc[1].depth);
     const Plan &plan = tree->plan[algo][x_type][mode][out_kind == DT_OUT_CLASS_U8 ? 0 : 1];
     if (plan.status != DT_OK) return fail(plan.status, plan.why);
     const Encoding &enc = tree->enc[plan.enc];
@@ -556,7 +555,7 @@ dt_status create_impl(const dt_node *nodes, int32_t n_nodes, int32_t n_features,
                 }
                 const int es = dtree::elem_bytes(xt);
                 if (m == dtree::kLoadExact && !exact_rows(n_features, es)) continue;
-                if (m == dtree::kLoadFlat && (n_features * es) % 16 == 0) continue;
+                if (m == dtree::kLoadFlat && !dtree::flat_rows(algo, xt, n_features, depth[1])) continue;
                 if (m == dtree::kLoadBytes && es == 4) continue;
                 for (int o = 0; o < 2; ++o) {
                     const auto plan_on = [&](int e, int kernel_algo, Plan *p) {
@@ -1290,7 +1289,7 @@ dt_status dt_tree_launch_info(const dt_tree *t, const void *d_x, dt_dtype x_type
     if (out_kind != DT_OUT_CLASS_U8 && out_kind != DT_OUT_CLASS_I32 && out_kind != DT_OUT_LEAF_I32)
         return fail(DT_ERR_INVALID_ARG, "unknown out_kind");
     if (ld < t->n_features) return fail(DT_ERR_INVALID_ARG, "ld must be >= n_features");
-    const int mode = load_mode_for(d_x, x_type, ld, t->n_features);
+    const int mode = dtree::tree_load_mode(algo, d_x, x_type, ld, t->n_features, t->enc[1].depth);
     const Plan &plan = t->plan[algo][x_type][mode][out_kind == DT_OUT_CLASS_U8 ? 0 : 1];
     if (plan.status != DT_OK) return fail(plan.status, plan.why);
     info->waves_per_workgroup = plan.waves;

@@ -127,67 +127,69 @@ const void *exact_kernel(int algo, bool tab_lds, int depth) {
 }
 
 // One class of row tiles, where rows of some width have it.  (Data walk and node lists share
-// their tiles, and so do the speculative windows of depths 1 to 4 and those of 5 and 6.)
-template <int XT, bool FLAT, bool TAB_LDS, int NV, int TR>
+// their tiles, and so do the speculative windows of depths 1 and 2, 3 and 4, 5 and 6.)
+template <int XT, bool FLAT, bool CONST, bool TAB_LDS, int NV, int TR>
 const void *row_for(int algo, int depth) {
-    using Tile = dev::RowTile<XT, FLAT, NV, TR>;
-    if constexpr (row_class_used(kAlgoData, XT, 0, FLAT, NV, TR)) {
+    using Tile = dev::RowTile<XT, FLAT, NV, TR, CONST ? row_tile_pitch(NV, TR) : 0>;
+    if constexpr (row_class_used(kAlgoData, XT, 0, FLAT, CONST, NV, TR)) {
         if constexpr (TAB_LDS)
             if (algo == kAlgoList) return reinterpret_cast<const void *>(&list_kernel<XT, Tile>);
         if (algo == kAlgoData)
             return reinterpret_cast<const void *>(&data_kernel<XT, Tile, TAB_LDS>);
     }
     if (algo != kAlgoSpec) return nullptr;
-    if constexpr (row_class_used(kAlgoSpec, XT, 1, FLAT, NV, TR)) {
-        switch (depth) {
-            case 1: return reinterpret_cast<const void *>(&spec_kernel<XT, Tile, TAB_LDS, 1>);
-            case 2: return reinterpret_cast<const void *>(&spec_kernel<XT, Tile, TAB_LDS, 2>);
-            case 3: return reinterpret_cast<const void *>(&spec_kernel<XT, Tile, TAB_LDS, 3>);
-            case 4: return reinterpret_cast<const void *>(&spec_kernel<XT, Tile, TAB_LDS, 4>);
-            default: break;
-        }
+    if constexpr (row_class_used(kAlgoSpec, XT, 1, FLAT, CONST, NV, TR)) {
+        if (depth == 1) return reinterpret_cast<const void *>(&spec_kernel<XT, Tile, TAB_LDS, 1>);
+        if (depth == 2) return reinterpret_cast<const void *>(&spec_kernel<XT, Tile, TAB_LDS, 2>);
     }
-    if constexpr (row_class_used(kAlgoSpec, XT, 5, FLAT, NV, TR)) {
+    if constexpr (row_class_used(kAlgoSpec, XT, 3, FLAT, CONST, NV, TR)) {
+        if (depth == 3) return reinterpret_cast<const void *>(&spec_kernel<XT, Tile, TAB_LDS, 3>);
+        if (depth == 4) return reinterpret_cast<const void *>(&spec_kernel<XT, Tile, TAB_LDS, 4>);
+    }
+    if constexpr (row_class_used(kAlgoSpec, XT, 5, FLAT, CONST, NV, TR)) {
         if (depth == 5) return reinterpret_cast<const void *>(&spec_kernel<XT, Tile, TAB_LDS, 5>);
         if (depth == 6) return reinterpret_cast<const void *>(&spec_kernel<XT, Tile, TAB_LDS, 6>);
     }
     return nullptr;
 }
 
-template <int XT, bool FLAT, bool TAB_LDS, int TR>
+template <int XT, bool FLAT, bool CONST, bool TAB_LDS, int TR>
 const void *row_tile_for(int algo, int vecs, int depth) {
     switch (vecs) {
-        case 2: return row_for<XT, FLAT, TAB_LDS, 2, TR>(algo, depth);
-        case 3: return row_for<XT, FLAT, TAB_LDS, 3, TR>(algo, depth);
-        case 4: return row_for<XT, FLAT, TAB_LDS, 4, TR>(algo, depth);
-        case 6: return row_for<XT, FLAT, TAB_LDS, 6, TR>(algo, depth);
-        case 8: return row_for<XT, FLAT, TAB_LDS, 8, TR>(algo, depth);
-        case 12: return row_for<XT, FLAT, TAB_LDS, 12, TR>(algo, depth);
-        case 16: return row_for<XT, FLAT, TAB_LDS, 16, TR>(algo, depth);
+        case 2: return row_for<XT, FLAT, CONST, TAB_LDS, 2, TR>(algo, depth);
+        case 3: return row_for<XT, FLAT, CONST, TAB_LDS, 3, TR>(algo, depth);
+        case 4: return row_for<XT, FLAT, CONST, TAB_LDS, 4, TR>(algo, depth);
+        case 6: return row_for<XT, FLAT, CONST, TAB_LDS, 6, TR>(algo, depth);
+        case 8: return row_for<XT, FLAT, CONST, TAB_LDS, 8, TR>(algo, depth);
+        case 12: return row_for<XT, FLAT, CONST, TAB_LDS, 12, TR>(algo, depth);
+        case 16: return row_for<XT, FLAT, CONST, TAB_LDS, 16, TR>(algo, depth);
         default: return nullptr;
     }
 }
 
-template <int XT, bool FLAT, bool TAB_LDS>
+template <int XT, bool FLAT, bool CONST, bool TAB_LDS>
 const void *row_kernel(int algo, int vecs, int tile_rows, int depth) {
     switch (tile_rows) {
-        case 64: return row_tile_for<XT, FLAT, TAB_LDS, 64>(algo, vecs, depth);
-        case 32: return row_tile_for<XT, FLAT, TAB_LDS, 32>(algo, vecs, depth);
-        case 16: return row_tile_for<XT, FLAT, TAB_LDS, 16>(algo, vecs, depth);
+        case 64: return row_tile_for<XT, FLAT, CONST, TAB_LDS, 64>(algo, vecs, depth);
+        case 32: return row_tile_for<XT, FLAT, CONST, TAB_LDS, 32>(algo, vecs, depth);
+        case 16: return row_tile_for<XT, FLAT, CONST, TAB_LDS, 16>(algo, vecs, depth);
         default: return nullptr;
     }
+}
+
+template <int XT, bool FLAT, bool CONST>
+const void *row_kernel_of(int algo, const TileShape &shape, bool tab_lds, int depth) {
+    return tab_lds ? row_kernel<XT, FLAT, CONST, true>(algo, shape.vecs, shape.tile_rows, depth)
+                   : row_kernel<XT, FLAT, CONST, false>(algo, shape.vecs, shape.tile_rows, depth);
 }
 
 template <int XT>
 const void *single_tree_kernel(int algo, const TileShape &shape, bool tab_lds, int depth) {
-    if (shape.mode != kLoadExact) {
-        const bool flat = shape.mode == kLoadFlat;
-        if (flat)
-            return tab_lds ? row_kernel<XT, true, true>(algo, shape.vecs, shape.tile_rows, depth)
-                           : row_kernel<XT, true, false>(algo, shape.vecs, shape.tile_rows, depth);
-        return tab_lds ? row_kernel<XT, false, true>(algo, shape.vecs, shape.tile_rows, depth)
-                       : row_kernel<XT, false, false>(algo, shape.vecs, shape.tile_rows, depth);
-    }
+    if (shape.mode == kLoadFlat) return row_kernel_of<XT, true, false>(algo, shape, tab_lds, depth);
+    if (shape.mode != kLoadExact)
+        return constant_pitch(algo, XT, shape.mode, depth)
+                   ? row_kernel_of<XT, false, true>(algo, shape, tab_lds, depth)
+                   : row_kernel_of<XT, false, false>(algo, shape, tab_lds, depth);
     switch (shape.row_stride) {
         case 4: return exact_kernel<XT, 4>(algo, tab_lds, depth);
         case 8: return exact_kernel<XT, 8>(algo, tab_lds, depth);

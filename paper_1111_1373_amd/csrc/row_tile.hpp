@@ -148,8 +148,8 @@ __device__ __forceinline__ f32x4 load16(const char *p) {
 //     bases between words): a row is the row_vecs vectors from the word its first element
 //     lies in, the last of which may read past its end.  Row r starts at LDS byte lds_off +
 //     r * lds_pitch; lds_pitch is 16 row_vecs + 4 (an odd number of words, so the 64 rows of
-//     a fixed column are on 64 banks; fp32: with the row_vecs of the class, a constant),
-//     plus what makes it equal to the input's pitch modulo 4, so that a vector's words stay
+//     a fixed column are on 64 banks; with the row_vecs of the class, a constant, where
+//     constant_pitch in tiles.hpp says so), plus what makes it equal to the input's pitch modulo 4, so that a vector's words stay
 //     words in the LDS.
 // Wide rows make tiles of TR = 32 or 16 records, so that a tile stays within 16 KiB of
 // registers and several fit the LDS: lanes share rows then (lane l walks row l % TR), which
@@ -274,9 +274,9 @@ struct RowTile : RowLoads<RowTile<XT, FLAT, NV, TRv, PITCH>, XT, FLAT, NV, TRv> 
     using Loads::kES;
     using Loads::row_of;
     using Loads::TR;
-    // fp32 rows: the pitch of the widest rows of the class, so that a row some constant
-    // number of rows further is an instruction offset away; 0: in.lds_pitch.
-    static constexpr int kPitch = FLAT || kES < 4 ? 0 : PITCH;
+    // The pitch of the widest rows of the class, so that a row some constant number of rows
+    // further is an instruction offset away (rows that start on words); 0: in.lds_pitch.
+    static constexpr int kPitch = FLAT ? 0 : PITCH;
 
     static __device__ __forceinline__ void put(const Rows &in, float *tile, int q, f32x4 x) {
         if constexpr (FLAT) {
@@ -306,7 +306,7 @@ struct RowTile : RowLoads<RowTile<XT, FLAT, NV, TRv, PITCH>, XT, FLAT, NV, TRv> 
     }
     static __device__ __forceinline__ const T *row(const Rows &in, const float *tile, int r) {
         if constexpr (kPitch > 0)
-            return tile + r * (kPitch / 4);
+            return reinterpret_cast<const T *>(tile + r * (kPitch / 4));
         else
             return reinterpret_cast<const T *>(reinterpret_cast<const char *>(tile) + in.lds_off +
                                                r * in.lds_pitch);

@@ -10,6 +10,25 @@ namespace dtree {
 
 constexpr int64_t align16(int64_t b) { return (b + 15) & ~int64_t(15); }
 
+// Whether a single-tree call copies dense rows of `n_features` as one run of bytes (flat
+// tiles), from a 4-byte-aligned base.  Not so windows of 8 lanes and more on narrow fp32
+// rows: their rounds are the time there, and are shorter where a row's pitch is a constant
+// (complete tree of depth 10, 3,000,000 records: depth 4, 3 features 43 us flat and 35 us
+// row by row, 19 features 66 and 47 us; depth 6, 3 features 74 and 64 us).  Smaller windows
+// and wider rows are bound by the stream (65,536 x 38: 6 us flat, 7 us).
+constexpr bool flat_rows(int algo, int elem_type, int n_features, int depth) {
+    if (n_features * elem_bytes(elem_type) % 16 == 0) return false;
+    return !(algo == kAlgoSpec && elem_type == kXF32 && depth >= 3 && n_features <= 32);
+}
+
+// Whether the LDS pitch of a single tree's row tiles is that of the widest rows of the class,
+// a constant: fp32 rows, and narrow rows that start on words where the rounds are the time
+// (windows of 8 lanes and more: 48 uint8 features, 3,000,000 records, depth 6, 80 us with a
+// row's own pitch, 70 us with the class's; 48 fp16 features, depth 4, 60 and 52 us).
+constexpr bool constant_pitch(int algo, int elem_type, int mode, int depth) {
+    return mode == kLoadRows && (elem_type == kXF32 || (algo == kAlgoSpec && depth >= 3));
+}
+
 // Record tile of a single-tree kernel for load mode `mode` (see LoadMode).  Row tiles hold
 // 64 records, or, so that a tile stays within kMaxVecs prefetch vectors per lane, 32 or 16
 // of wide rows.  The speculative walk of wide windows (depths 5 and 6) starts from 32, as
@@ -41,21 +60,23 @@ constexpr TileShape tile_shape(int algo, int elem_type, int n_features, int mode
     }
     s.prefetch_regs = 4 * s.vecs;
     s.lds_pitch = flat ? row_bytes
-                       : es == 4 && s.vecs > 0 ? row_tile_pitch(s.vecs, s.tile_rows)
-                                               : 16 * s.row_vecs + 4;
+                       : constant_pitch(algo, elem_type, mode, depth) && s.vecs > 0
+                           ? row_tile_pitch(s.vecs, s.tile_rows)
+                           : 16 * s.row_vecs + 4;
     s.tile_bytes = int(align16(s.tile_rows * (s.lds_pitch + (bytes ? 3 : 0)) + (bytes ? 3 : 0)));
     return s;
 }
 
-// Whether tile_shape gives row tiles of this class (flat or not, prefetch vectors, records)
-// for any width of rows: the instances that are compiled.
-constexpr bool row_class_used(int algo, int elem_type, int depth, bool flat, int vecs,
-                              int tile_rows) {
+// Whether tile_shape gives row tiles of this class (flat or not, with a constant pitch or not,
+// prefetch vectors, records) for any width of rows: the instances that are compiled.
+constexpr bool row_class_used(int algo, int elem_type, int depth, bool flat, bool constant,
+                              int vecs, int tile_rows) {
     for (int f = 1; f <= kMaxRowStride; ++f) {
         for (int mode : {kLoadFlat, kLoadRows, kLoadBytes}) {
             if ((mode == kLoadFlat) != flat) continue;
-            if (flat && f * elem_bytes(elem_type) % 16 == 0) continue;
+            if (flat && !flat_rows(algo, elem_type, f, depth)) continue;
             if (mode == kLoadBytes && elem_type == kXF32) continue;
+            if (constant_pitch(algo, elem_type, mode, depth) != constant) continue;
             const TileShape s = tile_shape(algo, elem_type, f, mode, depth);
             if (s.vecs == vecs && s.tile_rows == tile_rows) return true;
         }
@@ -69,7 +90,7 @@ inline bool exact_rows(int32_t n_features, int elem_bytes) {
            words <= kMaxExactWords;
 }
 
-// Load path of a single-tree call for the layout of the features (see LoadMode).
+// Load path of a call for the layout of the features (see LoadMode).
 inline int load_mode_for(const void *d_x, int elem_type, int64_t ld, int32_t n_features) {
     const int es = elem_bytes(elem_type);
     // fp32 rows start on their own words, also off a base between words (forest calls take
@@ -80,6 +101,14 @@ inline int load_mode_for(const void *d_x, int elem_type, int64_t ld, int32_t n_f
     return exact_rows(n_features, es) && (reinterpret_cast<uintptr_t>(d_x) & 15u) == 0
                ? kLoadExact
                : kLoadRows;
+}
+
+// Load path of a single-tree call with windows of `depth` levels.
+inline int tree_load_mode(int algo, const void *d_x, int elem_type, int64_t ld, int32_t n_features,
+                          int depth) {
+    const int mode = load_mode_for(d_x, elem_type, ld, n_features);
+    return mode == kLoadFlat && !flat_rows(algo, elem_type, n_features, depth) ? int(kLoadRows)
+                                                                               : mode;
 }
 
 inline uint32_t magic_div(int32_t d) {

@@ -30,10 +30,10 @@ void trees() {
                 for (int mode = 0; mode < kLoadModes; ++mode) {
                     const int es = elem_bytes(xt);
                     if (mode == kLoadExact && !exact_rows(f, es)) continue;
-                    if (mode == kLoadFlat && f * es % 16 == 0) continue;
                     if (mode == kLoadBytes && es == 4) continue;
                     for (int depth = 1; depth <= 6; ++depth)
                         for (bool lds : {false, true}) {
+                            if (mode == kLoadFlat && !flat_rows(algo, xt, f, depth)) continue;
                             const TileShape s = tile_shape(algo, xt, f, mode, depth);
                             const void *fn = kernel_for(algo, xt, s, lds, depth);
                             if ((algo == kAlgoPath && xt != kXF32) || (algo == kAlgoList && !lds)) {

@@ -133,27 +133,32 @@ void columns(const void *x, int64_t n, int64_t ld, int F, int mode, int off) {
     }
 }
 
-template <int XT, bool FLAT, int TR>
+template <int XT, bool FLAT, bool CONST, int NV, int TR>
+void drive_class(const Rows &in, const TileShape &s, int off) {
+    drive<XT, FLAT, NV, TR, CONST ? row_tile_pitch(NV, TR) : 0>(in, s, off);
+}
+
+template <int XT, bool FLAT, bool CONST, int TR>
 bool by_vecs(const Rows &in, const TileShape &s, int off) {
     switch (s.vecs) {
-        case 0: drive<XT, FLAT, 0, TR>(in, s, off); return true;
-        case 2: drive<XT, FLAT, 2, TR>(in, s, off); return true;
-        case 3: drive<XT, FLAT, 3, TR>(in, s, off); return true;
-        case 4: drive<XT, FLAT, 4, TR>(in, s, off); return true;
-        case 6: drive<XT, FLAT, 6, TR>(in, s, off); return true;
-        case 8: drive<XT, FLAT, 8, TR>(in, s, off); return true;
-        case 12: drive<XT, FLAT, 12, TR>(in, s, off); return true;
-        case 16: drive<XT, FLAT, 16, TR>(in, s, off); return true;
+        case 0: drive_class<XT, FLAT, CONST, 0, TR>(in, s, off); return true;
+        case 2: drive_class<XT, FLAT, CONST, 2, TR>(in, s, off); return true;
+        case 3: drive_class<XT, FLAT, CONST, 3, TR>(in, s, off); return true;
+        case 4: drive_class<XT, FLAT, CONST, 4, TR>(in, s, off); return true;
+        case 6: drive_class<XT, FLAT, CONST, 6, TR>(in, s, off); return true;
+        case 8: drive_class<XT, FLAT, CONST, 8, TR>(in, s, off); return true;
+        case 12: drive_class<XT, FLAT, CONST, 12, TR>(in, s, off); return true;
+        case 16: drive_class<XT, FLAT, CONST, 16, TR>(in, s, off); return true;
         default: return false;
     }
 }
 
-template <int XT, bool FLAT>
+template <int XT, bool FLAT, bool CONST>
 bool by_rows(const Rows &in, const TileShape &s, int off) {
     switch (s.tile_rows) {
-        case 64: return by_vecs<XT, FLAT, 64>(in, s, off);
-        case 32: return by_vecs<XT, FLAT, 32>(in, s, off);
-        case 16: return by_vecs<XT, FLAT, 16>(in, s, off);
+        case 64: return by_vecs<XT, FLAT, CONST, 64>(in, s, off);
+        case 32: return by_vecs<XT, FLAT, CONST, 32>(in, s, off);
+        case 16: return by_vecs<XT, FLAT, CONST, 16>(in, s, off);
         default: return false;
     }
 }
@@ -181,17 +186,18 @@ void one_case() {
     const int algos[] = {kAlgoData, kAlgoSpec, kAlgoPath};
     const int algo = algos[XT == kXF32 ? pick(0, 2) : pick(0, 1)];
     const int depth = pick(1, 6);
-    int mode = load_mode_for(x, XT, ld, F);
+    int mode = tree_load_mode(algo, x, XT, ld, F, depth);
     if (XT == kXF32) {
-        columns(x, n, ld, F, mode, off);
+        columns(x, n, ld, F, load_mode_for(x, XT, ld, F), off);
         forest_rows(x, n, ld, F, off);
     }
     if (mode == kLoadExact) mode = kLoadRows;           // such rows come strided, too
     const TileShape s = tile_shape(algo, XT, F, mode, depth);
     if (s.tile_bytes % 16 != 0) fail("tile size", XT, F, ld, n, mode, off);
     const Rows in = make_tile_rows(x, XT, n, ld, F, s);
-    const bool ok = mode == kLoadFlat ? by_rows<XT, true>(in, s, off)
-                                      : by_rows<XT, false>(in, s, off);
+    const bool ok = mode == kLoadFlat ? by_rows<XT, true, false>(in, s, off)
+                    : constant_pitch(algo, XT, mode, depth) ? by_rows<XT, false, true>(in, s, off)
+                                                            : by_rows<XT, false, false>(in, s, off);
     if (!ok) fail("no tile class", XT, F, ld, n, mode, off);
 }
 

@@ -206,3 +206,19 @@ def test_planned_workgroups_fit_the_lds(dt, F, size):
                 for out_kind in ("class_u8", "leaf_i32"):
                     li = tree.launch_info(x, algo=algo, out_kind=out_kind)
                     assert li["workgroups_per_cu"] * -(-li["lds_bytes"] // 1280) <= 128, li
+
+
+@pytest.mark.parametrize("F,depth,mode", [(3, 2, 0), (3, 3, 1), (19, 2, 0), (19, 4, 1), (30, 6, 1),
+                                          (33, 6, 0), (100, 4, 1), (101, 4, 0)])
+def test_narrow_rows_of_large_windows_are_read_row_by_row(dt, F, depth, mode):
+    """Dense fp32 rows of up to 32 features go one by one into tiles of a constant pitch for
+    windows of 8 lanes and more, and as one run of bytes otherwise (rows of no multiple of 16
+    bytes); the labels are the oracle's either way."""
+    r = np.random.Generator(np.random.PCG64(F * 10 + depth))
+    nodes = W.random_full_tree(r, 60, F, 5)
+    x = W.uniform_f32(r, (1003, F))
+    tree, xd = dt.Tree(nodes, F, 5, spec_window_depth=depth), torch.from_numpy(x).cuda()
+    assert tree.launch_info(xd, algo="speculative")["load_mode"] == mode
+    assert tree.launch_info(xd, algo="data")["load_mode"] == (1 if F == 100 else 0)
+    got = tree.classify(xd, algo="speculative", out_kind="leaf_i32").cpu().numpy()
+    np.testing.assert_array_equal(got, oracle.tree_leaves(nodes, x, F))
