@@ -237,8 +237,13 @@ uint32_t narrow_key(float t, dt_dtype type) {
 void build_narrow_slots(const WindowTables &wt, dt_dtype type, std::vector<uint32_t> *out) {
     const size_t n = wt.threshold.size();
     out->resize(n);
-    for (size_t i = 0; i < n; ++i)
-        (*out)[i] = (uint32_t(wt.feature[i]) << 16) | narrow_key(wt.threshold[i], type);
+    // most slots of a sparse tree's windows are padding
+    const float neg_inf = -std::numeric_limits<float>::infinity();
+    const uint32_t padding = narrow_key(neg_inf, type);
+    for (size_t i = 0; i < n; ++i) {
+        const float t = wt.threshold[i];
+        (*out)[i] = (uint32_t(wt.feature[i]) << 16) | (t == neg_inf ? padding : narrow_key(t, type));
+    }
 }
 
 std::vector<int32_t> breadth_first_order(const dt_node *nodes, int32_t n) {
@@ -314,7 +319,7 @@ DataWalk data_walk_for(const TreeShape &shape, int32_t levels, int64_t window_by
         return list_bytes <= kListLdsBytes ? DataWalk::kList : DataWalk::kEither;
     }
     if (window_bytes > kListLdsBytes) return DataWalk::kEither;
-    const bool chain = shape.depth >= 2 * log2_nodes && window_bytes <= 16 * 1024;
+    const bool chain = shape.depth >= 2 * log2_nodes && window_bytes <= 12 * 1024;
     return window_bytes > 4 * list_bytes && !chain ? DataWalk::kList : DataWalk::kWindows;
 }
 

@@ -104,7 +104,7 @@ constexpr int64_t kListLdsBytes = 48 * 1024;
 //   One level: the windows, whose tables then are about as large as the list's (a complete
 //     tree of depth 12 on 200 fp16 features 61.6 against 81.0 us), unless they take more than
 //     four times the list's bytes (20 random nodes, 8 fp32 features 0.84 of the time); chains
-//     (depth of twice log2 of the nodes and more: 10 decision nodes 1.05) keep up to 16 KiB.
+//     (depth of twice log2 of the nodes and more: 10 decision nodes 1.05) keep up to 12 KiB.
 //   Lists, or one level of windows, of more than 48 KiB (kEither): by list_is_faster.
 enum class DataWalk { kWindows, kList, kEither };
 DataWalk data_walk_for(const TreeShape &shape, int32_t levels, int64_t window_bytes,

@@ -261,7 +261,8 @@ int check_list_rule() {
         {14, 20157, 4, 4, 12000, 8, 8, 14, true},      // 32
         {10, 21, 1, 10, 1024, 8, 32, 32, false},       // chains
         {20, 41, 2, 10, 2048, 12, 8, 8, false},
-        {11, 31, 1, 11, 2048, 12, 16, 16, true},       // 24 KiB of windows for 15 nodes
+        {11, 31, 1, 11, 2048, 12, 16, 16, true},       // 24 KiB of windows for 15 nodes, or
+        {11, 31, 1, 11, 2048, 8, 16, 16, true},        // 16
     };
     for (const Want &w : want) {
         dtree::TreeShape shape;
