@@ -1,15 +1,15 @@
 // Device building blocks shared by the single-tree and forest kernels (gfx950).
 //
-// Record tiles: every wavefront owns a private tile of 64 records (one per lane) in the
-// LDS, in the records' own element type (fp32, fp16, bf16 or uint8).  Row r (record)
-// starts at element r*RS; the 4-byte word w of a row is stored at word w ^ swz(r), bytes
+// Record tiles: every wavefront owns a private tile of 64 records (one per lane; 32 or 16 of
+// wide rows) in the LDS, in the records' own element type (fp32, fp16, bf16 or uint8).  Row
+// r (record) of an exact tile starts at element r*RS; the 4-byte word w of a row is stored at word w ^ swz(r), bytes
 // within a word unchanged.  The XOR spreads the 64 rows over all 64 banks for a fixed
 // column, so the top levels of a tree (where every lane reads the same feature) are
 // conflict-free, and the staging stores land on distinct banks.  Staging moves whole
 // words and does not depend on the element type; a tree step widens the element it reads
 // to fp32 (exactly) and compares it with the fp32 threshold.  That layout needs rows of a
-// power of two of words; single-tree kernels keep every other row width, stride and
-// alignment in row tiles (RowTile below).
+// power of two of words; every other row width, stride and alignment is kept in row tiles
+// (RowTile in row_tile.hpp), or, for the data walk of forests, column by column (ColTile).
 //
 // Window tables (built on the host, see encode.hpp): for window w, slot p in [1, 2^D)
 // holds the (threshold, feature) of heap node p (children 2p, 2p+1; slot 0 is padding);

@@ -800,16 +800,16 @@ dt_status upload_forest(const std::vector<unsigned char> &bytes, ForestEncoding 
 // Estimated time, in cycles, of one round of groups (every resident workgroup, `blocks` to a
 // CU, walks its tiles through all trees).  A walk of 64 records takes the CU's LDS some
 // cycles per step and tree, and its wavefront at least some more per step (data: of four
-// trees together; speculative: of one, longer on rows whose pitch is no constant), whichever
-// is longer with this many wavefronts.  Tables read in place keep each workgroup waiting, a
-// second one as long again.  Each byte of tables copied takes 1/64 cycle, each chunk its
-// barriers, each group its staging, which kernels without prefetch wait for.  The constants
-// give the measured order, not the time (which is up to half as long again).  Of 876 data
-// walks measured with windows and with lists (mixed, irregular and chain-like forests of 6 to
-// 200 trees, 8 to 64 features, 1,000 to 600,000 records) the choice is the faster or within
-// 5% of it in 831, the worst 1.26 times as slow.  Speculative windows of depth 4, 100,001 records,
-// 30 complete trees of depth 8: 16 features 42.5 us with one wavefront per tile and 44.7 with
-// two, 19 features 54 and 44 us.
+// trees together; speculative: of one), whichever is longer with this many wavefronts.
+// Tables read in place keep each workgroup waiting, a second one as long again.  Each byte of
+// tables copied takes 1/64 cycle, each chunk its barriers, each group its staging, which
+// kernels without prefetch wait for.  The constants give the measured order, not the time
+// (which is up to half as long again).  Of 876 data walks measured with windows and with lists
+// (mixed, irregular and chain-like forests of 6 to 200 trees, 8 to 64 features, 1,000 to
+// 600,000 records) the choice was slower than the other by more than 5% in 36 to 45 (three
+// runs), 1.26 times at most.  Speculative windows of depth 4, 100,001 x 16 records, 30
+// complete trees of depth 8, 16 vote words: 42.4 us with one wavefront per tile, 36.6 us with
+// the two that are chosen.
 double round_cost(const ForestEncoding &enc, int algo, const ForestPlan &p, int split, int blocks) {
     const bool in_place = p.chunk_lds_bytes == 0, data = algo == DT_ALGO_DATA;
     const double lds_step = data ? (in_place ? 20.0 : 10.0) : (in_place ? 100.0 : 40.0);

@@ -130,7 +130,9 @@ struct FArgs {
 //   kLoadFlat   other dense rows whose width is no multiple of 16 bytes, 4-byte-aligned base
 //   kLoadRows   other rows that all start on 4-byte boundaries
 //   kLoadBytes  rows (of narrow records) that start between words
-// Forest kernels use the first two and kLoadExact for rows of 4 to 32 fp32 features.
+// Narrow fp32 rows of large windows are kLoadRows also where they could be flat (flat_rows).
+// Forest kernels use kLoadFlat (the speculative ones for more than 64 features), kLoadRows,
+// and kLoadExact for rows of 4 to 32 fp32 features.
 enum LoadMode { kLoadFlat = 0, kLoadRows = 1, kLoadExact = 2, kLoadBytes = 3, kLoadModes = 4 };
 constexpr int kForestLoadModes = 3;
 

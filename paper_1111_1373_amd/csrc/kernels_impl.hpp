@@ -2,14 +2,14 @@
 // element type is instantiated in a translation unit of its own (kernels.hip: fp32,
 // kernels_f16.hip, kernels_bf16.hip, kernels_u8.hip).
 //
-// Both kernels are persistent: each wavefront owns a private tile of 64 records in the
-// LDS and walks a contiguous range of record tiles, keeping the loads of its next tile in
-// flight in registers while it walks the current one, and writing its results in bursts
-// from an LDS buffer.  The tree's window tables (see encode.hpp) are staged into the LDS
-// once per workgroup, or, for trees whose tables do not fit next to the record tiles, read
-// from global memory (L2-resident).  Records stay in their own element type in the LDS;
-// every tree step widens the element it reads to fp32 and compares it with the fp32
-// threshold, which is the decision on the stored value.
+// The kernels are persistent: each wavefront owns a private tile of 64 records (32 or 16 of
+// wide rows and for wide windows) in the LDS and walks a contiguous range of record tiles,
+// keeping the loads of its next tile in flight in registers while it walks the current one,
+// and writing its results in bursts from an LDS buffer.  The tree's window tables (see
+// encode.hpp) are staged into the LDS once per workgroup, or, for trees whose tables do not
+// fit next to the record tiles, read from global memory (L2-resident).  Records stay in their
+// own element type in the LDS; every tree step widens the element it reads to fp32 and
+// compares it with the fp32 threshold, which is the decision on the stored value.
 //
 //   data_kernel  (Section 3.2, Procedure 3): lane r evaluates record r of its tile.
 //   list_kernel  the same over a list of the tree's nodes instead of windows.

@@ -136,7 +136,7 @@ __device__ __forceinline__ f32x4 load16(const char *p) {
 
 // Rows of any width, stride and alignment.  What bounded them was the load path: one
 // element per load, each waited for (3,000,001 x 19 fp32 rows took 244 us, 0.98 TB/s; now
-// 45 us).  Here 16-byte vectors are loaded and the next tile's stay in flight in registers,
+// 40 us over the same windows and 37.5 us over a node list).  Here 16-byte vectors are loaded and the next tile's stay in flight in registers,
 // as for the exact tiles.  Vectors lie on 4-byte boundaries: loads off them measured 1.5
 // times the time (rows of 20 of 25 fp16 elements, 15.7 us against 9 us).
 //   FLAT: dense rows whose width is no multiple of 16 bytes, 4-byte-aligned base.  A tile of

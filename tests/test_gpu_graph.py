@@ -106,3 +106,52 @@ def test_one_handle_on_several_streams(dt):
                                       wf.n_classes)
         np.testing.assert_array_equal(res[k][0].cpu().numpy().astype(np.int32), want)
         np.testing.assert_array_equal(res[k][1].cpu().numpy().astype(np.int32), wantf)
+
+
+def test_forest_call_of_two_kernels_in_a_hip_graph(dt):
+    """A forest call whose last, partly filled round goes to a split kernel is two launches;
+    captured, both replay."""
+    import ctypes
+    r = np.random.Generator(np.random.PCG64(77))
+    trees = [W.random_full_tree(r, 255, 6, 9) for _ in range(60)]
+    nodes = np.concatenate(trees)
+    offsets = np.concatenate([[0], np.cumsum([len(t) for t in trees])]).astype(np.int32)
+    n = 256 * 16 * 64 + 40 * 64
+    x = W.uniform_f32(r, (n, 6))
+    f, xd = dt.Forest(nodes, offsets, 6, 9), _gpu(x)
+    spread = (ctypes.c_int64 * 5)()            # six int32, then the tiles of either kernel
+    dt._check(dt._lib.dt_probe_forest_spread(
+        f._h, ctypes.c_void_p(xd.data_ptr()), ctypes.c_int64(n), ctypes.c_int64(6), 0, spread),
+        "dt_probe_forest_spread")
+    assert spread[3] > 0 and spread[4] > 0
+    out = torch.empty(n, dtype=torch.uint8, device="cuda")
+    f.classify(xd, out=out)
+    torch.cuda.synchronize()
+    eager = out.cpu().numpy().astype(np.int32)
+    at = np.concatenate([np.arange(0, n, 211), np.arange(n - 3000, n)])
+    np.testing.assert_array_equal(eager[at], oracle.forest_classes(nodes, offsets, x[at], 6, 9))
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        f.classify(xd, out=out)
+    _replay_and_check(g, {"data": out}, {"data": eager})
+
+
+def test_stream_of_a_call_with_and_without_the_raw_handle(dt, monkeypatch):
+    """The binding asks torch for the current stream's raw handle, or, where torch has no such
+    function, for the stream object: both name the same stream, the default one or another."""
+    side = torch.cuda.Stream()
+    w = W.config(1, n_samples=5000)
+    x = w.features()
+    t, xd = dt.Tree(w.nodes, w.n_features, w.n_classes), _gpu(x)
+    want = oracle.tree_classes(w.nodes, x, w.n_features)
+    torch.cuda.synchronize()
+    for raw in (True, False):
+        if not raw:
+            monkeypatch.setattr(dt, "_raw_stream", None)
+        for stream in (torch.cuda.default_stream(), side):
+            with torch.cuda.stream(stream):
+                assert (dt._stream_handle(None) or 0) == stream.cuda_stream
+                out = t.classify(xd)
+            assert dt._stream_handle(stream) == stream.cuda_stream
+            stream.synchronize()
+            np.testing.assert_array_equal(out.cpu().numpy(), want)

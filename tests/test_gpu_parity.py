@@ -164,8 +164,8 @@ def test_ragged_sizes(dt, n):
 def test_ragged_sizes_32_record_tiles(dt, sd, n):
     """Speculative windows of depth 5 and 6 (32- and 64-lane record groups, Section 3.4)
     run on tiles of 32 records; at depth 5 records 16-31 of a tile are walked in lanes
-    32-47 and moved back to record order at the end.  Inputs whose last tile is partial
-    in either half of it, or a single record."""
+    32-47, each of which writes its record's label.  Inputs whose last tile is partial in
+    either half of it, or a single record."""
     w = W.config(2, n_samples=n)
     x = w.features()
     t = dt.Tree(w.nodes, w.n_features, w.n_classes, spec_window_depth=sd)
