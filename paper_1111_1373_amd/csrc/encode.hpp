@@ -143,7 +143,9 @@ constexpr int64_t kLdsBytes = 160 * 1024;
 constexpr int64_t kDataTableBudget = 48 * 1024;
 
 // Table bytes the default data window depth may use for records of n_features: at most
-// kDataTableBudget, and room left for two fp32 record tiles.
+// kDataTableBudget, and room left for two fp32 record tiles (of 64 rows of the next power of
+// two of features, whatever tiles a launch then uses: the cut of a tree is the same for every
+// record type and layout; data_walk_for decides for each whether it is walked).
 int64_t data_table_budget(int32_t n_features);
 
 // Library's default window depths (see dt_tree_options in dtree.h).  Data: the fewest

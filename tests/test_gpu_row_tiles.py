@@ -222,3 +222,30 @@ def test_narrow_rows_of_large_windows_are_read_row_by_row(dt, F, depth, mode):
     assert tree.launch_info(xd, algo="data")["load_mode"] == (1 if F == 100 else 0)
     got = tree.classify(xd, algo="speculative", out_kind="leaf_i32").cpu().numpy()
     np.testing.assert_array_equal(got, oracle.tree_leaves(nodes, x, F))
+
+
+@pytest.mark.parametrize("x_type", ["f32", "f16", "u8"])
+@pytest.mark.parametrize("ld", [1 << 40, 1 << 61, 1 << 62, (1 << 63) - 1])
+def test_one_record_with_any_stride(dt, x_type, ld):
+    """The stride of a single record is never used, also where its bytes overflow 64 bits."""
+    r = np.random.Generator(np.random.PCG64(9))
+    F, C = 19, 5
+    nodes = W.narrow_tree(W.random_full_tree(r, 60, F, C), x_type)
+    x = W.uniform_f32(r, (1, F))
+    xn = x if x_type == "f32" else W.narrow_records(x, x_type)
+    want = oracle.tree_classes(nodes, x if x_type == "f32" else TU.widen(xn, x_type), F)
+    tree, xd = dt.Tree(nodes, F, C, spec_window_depth=4), torch.from_numpy(xn).cuda()
+    forest = dt.Forest(nodes, [0, len(nodes)], F, C)
+    stream = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    for algo in ("data", "speculative"):
+        out = torch.full((1,), -1, dtype=torch.int32, device="cuda")
+        args = (ctypes.c_int64(1), ctypes.c_int64(ld), ctypes.c_void_p(out.data_ptr()),
+                dt.OUT_KINDS["class_i32"], dt.ALGOS[algo], stream)
+        dt._check(dt._lib.dt_classify_typed(tree._h, ctypes.c_void_p(xd.data_ptr()),
+                                            dt.X_TYPES[x_type], *args), "dt_classify_typed")
+        assert int(out[0]) == want[0]
+        if x_type == "f32":
+            out.fill_(-1)
+            dt._check(dt._lib.dt_forest_classify(forest._h, ctypes.c_void_p(xd.data_ptr()), *args),
+                      "dt_forest_classify")
+            assert int(out[0]) == want[0]
